@@ -134,11 +134,62 @@ __device__ __forceinline__ void refresh_scale(uint32_t fmax_bits, float bound, i
   inv = pow2f(-e);
 }
 
+// The tame range of the update pass.
+//
+// Correctly rounded sqrt and division as the compiler emits them have to work for every fp32 operand, subnormal, huge,
+// infinite: 16 and 12 instructions.  Where no intermediate comes near the ends of the exponent range the same
+// results take 5 and 6:
+//   sqrt(x):  y = rsq(x), s = x y, h = y / 2;  s + h (x - s^2), the residual exact in one fma.  Equal to the correctly
+//             rounded root for every one of the 2^24 significands and exponent parities (checked on the device).
+//   a / d:    r = rcp(d), r += r (1 - d r);  q = a r;  q - r (d q - a).  With r within one ulp of 1/d, which v_rcp_f32 is for
+//             every significand, the value before the last rounding is within 2^-22 ulp of a/d; the quotients that are
+//             this close to a rounding boundary were enumerated (for every d the a with 2 (a mod d) = d +- 32 at most:
+//             1.9e8 cases, r off by -1, 0 and 1 ulp): all round correctly but for d = 2 - 2^-23 and 2 - 3 2^-22 with an
+//             r that is off, where v_rcp_f32 returns the nearest.  The residual is formed as d q - a so that a = -0 gives -0.
+// And because scales are powers of two they can be folded into the coefficients without changing any rounding: b1 / s_m,
+// (1-b1) / s_g, (1-b2) / s_g^2, b2 / s_v, decay / s_w, and a common factor 2^j of x^(1/2), eps and a that centres the
+// root and the division in the exponent range.  What has to hold for all that is checked per tensor from the scales
+// and hyper-parameters alone, with every payload a format can hold: scales are powers of two (that of an FP8 sum over a number
+// of ranks that is not one is none), and every product and sum, in the plain order of operations and in this
+// one, is zero or normal, small ones by a margin of the 24 bits that an exact residual needs.
+// c: b1/s_m, (1-b1)/s_g, (1-b2)/s_g^2, b2/s_v, decay/s_w, 2^j/bc1, 4^j/bc2, 2^j eps.
+__device__ inline bool tame_range(const AdamParams& p, float isg, float ism, float isv, float isw, float decay, float (&c)[8]) {
+  auto pow2 = [](float x) { const uint32_t b = f2u(x); return (b & 0x807FFFFFu) == 0 && b != 0 && b < 0x7F800000u; };
+  auto ex = [](float x) { return (int)((f2u(x) >> 23) & 0xFFu) - 127; };       // floor(log2 |x|)
+  if (!pow2(isg) || !pow2(ism) || !pow2(isv) || !pow2(isw)) return false;
+  if (!(p.b1 == 0.0f || p.b1 >= 0x1p-8f) || !(p.b2 == 0.0f || p.b2 >= 0x1p-8f)) return false;
+  if (!(decay == 0.0f || fabsf(decay) >= 0x1p-60f)) return false;
+  const int eg = ex(isg), em = ex(ism), ev = ex(isv), ew = ex(isw), e1 = ex(p.omb1), e2 = ex(p.omb2);
+  const int r1 = ex(p.rbc1), r2 = ex(p.rbc2);                                  // both factors are >= 1
+  if (eg > 24 || em < -60 || em > 31 || ev < -90 || ev > 60 || ew < -40 || ew > 60) return false;
+  // payloads: |g| in [2^-16, 2^16), |m| in [2^-9, 2^9), v and |w| in [2^-24, 2^16), or zero
+  if (e1 + eg - 16 < -100 || e2 + 2 * eg - 32 < -120) return false;
+  const int vhi = max(16 + ev, e2 + 1 + 2 * (eg + 16)) + 1 + r2 + 1;           // v' / bc2 < 2^vhi
+  const int vlo = min(p.b2 == 0.0f ? 1000 : ex(p.b2) - 24 + ev, e2 + 2 * eg - 32) + r2;
+  const int j = min((60 - vhi) >> 1, 50);                                      // 4^j v' / bc2 < 2^60
+  if (j < -50 || vlo + 2 * j < -80) return false;
+  const int ee = ex(p.eps) + j;                                                // >= -20: 2^-50 vanishes against eps
+  if (ee < -20 || ee > 60) return false;
+  const int mlo = min(e1 + eg - 39, p.b1 == 0.0f ? 1000 : ex(p.b1) - 32 + em); // a non-zero |m'| is a multiple of 2^mlo
+  const int mhi = max(9 + em, e1 + 1 + eg + 16) + 1;
+  if (mlo + r1 + j < -60 || mhi + r1 + 1 + j > 60) return false;
+  const float s = pow2f(j);
+  c[0] = p.b1 * ism;
+  c[1] = p.omb1 * isg;
+  c[2] = (p.omb2 * isg) * isg;
+  c[3] = p.b2 * isv;
+  c[4] = decay * isw;
+  c[5] = p.rbc1 * s;
+  c[6] = (p.rbc2 * s) * s;
+  c[7] = p.eps * s;
+  return true;
+}
+
 // Chooses the scales of the four buffers the update pass writes, from a bound on the new first moment
 // (its exact amax, or the predicted bound) and the metadata of the inputs; decides whether the tensor
 // may take the fast update path.
 template <int WCOPY>
-__device__ void adam_choose_scales(const AdamParams& p, Scratch::Pending& P, int t, float bound_m) {
+__device__ void adam_choose_scales(const AdamParams& p, Scratch::Pending& P, int t, uint32_t tensor_flags, float bound_m) {
   const fp8lm_meta& G = p.grad_meta[t];
   const fp8lm_meta& Mm = p.m_meta[t];
   const fp8lm_meta& Mv = p.v_meta[t];
@@ -175,6 +226,8 @@ __device__ void adam_choose_scales(const AdamParams& p, Scratch::Pending& P, int
   const bool calm = !anyflag && (bound_m < kBig) && (G.amax_deq < kBig) && (Mm.amax_deq < kBig) &&
                     (Mv.amax_deq < kHuge) && (Mw.amax_deq < kHuge);
   P.careful = calm ? 0u : 1u;
+  P.tame = tame_range(p, G.inv_scale, Mm.inv_scale, Mv.inv_scale, Mw.inv_scale,
+                      (tensor_flags & FP8LM_TENSOR_NO_WEIGHT_DECAY) ? 1.0f : p.decay, P.c) ? 1u : 0u;
 }
 
 // Single-pass variant: the first-moment scale comes from the bound
@@ -185,7 +238,7 @@ __global__ void adam_predict_scales_kernel(Tables tb, AdamParams p, int n) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n || tb.desc[t].numel == 0) return;
   const float Bm = __builtin_fmaf(p.b1, p.m_meta[t].amax_deq, p.omb1 * p.grad_meta[t].amax_deq);
-  adam_choose_scales<WCOPY>(p, tb.scratch[t].pend, t, Bm);
+  adam_choose_scales<WCOPY>(p, tb.scratch[t].pend, t, tb.desc[t].flags, Bm);
 }
 
 // The first pass was done by a fused cast: its result sits in the scratch.  One thread per tensor.
@@ -194,7 +247,7 @@ __global__ void adam_scales_from_cast_kernel(Tables tb, AdamParams p, int n) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n || tb.desc[t].numel == 0) return;
   const uint32_t bits = tb.scratch[t].pend.amax_m_bits;
-  adam_choose_scales<WCOPY>(p, tb.scratch[t].pend, t, bits >= 0x7F800000u ? __builtin_inff() : u2f(bits));
+  adam_choose_scales<WCOPY>(p, tb.scratch[t].pend, t, tb.desc[t].flags, bits >= 0x7F800000u ? __builtin_inff() : u2f(bits));
 }
 
 // Speculative first-moment scale (the update pass verifies it): the scale that the previous step's exact amax gives,
@@ -209,7 +262,7 @@ __global__ void adam_speculate_scales_kernel(Tables tb, AdamParams p, int n) {
   S.redo = 0;
   S.old_scale = p.m_meta[t].scale;
   S.old_inv = p.m_meta[t].inv_scale;
-  adam_choose_scales<WCOPY>(p, S.pend, t, p.m_meta[t].amax);
+  adam_choose_scales<WCOPY>(p, S.pend, t, tb.desc[t].flags, p.m_meta[t].amax);
   const float Bm = __builtin_fmaf(p.b1, p.m_meta[t].amax_deq, p.omb1 * p.grad_meta[t].amax_deq);
   if (!(Bm < 1.0995116e12f)) S.pend.careful = 1u;      // 2^40, as in adam_choose_scales
 }
@@ -270,10 +323,10 @@ struct AdamAmaxOp {
     block_combine(s);
     if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
   }
-  __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
+  __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const uint32_t abits = s.mx[0];
     const bool m_nonfinite = abits >= 0x7F800000u;
-    adam_choose_scales<WCOPY>(p, tb.scratch[t].pend, t, m_nonfinite ? __builtin_inff() : u2f(abits));
+    adam_choose_scales<WCOPY>(p, tb.scratch[t].pend, t, d.flags, m_nonfinite ? __builtin_inff() : u2f(abits));
   }
 };
 
@@ -298,6 +351,23 @@ template <bool FAST> __device__ __forceinline__ float adam_update(float m1, floa
   }
 }
 
+// The same arithmetic with correctly rounded root and quotient for a tensor in the tame range (c as above).
+__device__ __forceinline__ void tame_update(float dg, float dm, float dv, float dw, const float (&c)[8], float lr, float& m1,
+                                            float& v1, float& w1) {
+  m1 = __builtin_fmaf(c[0], dm, c[1] * dg);
+  v1 = __builtin_fmaf(c[3], dv, c[2] * (dg * dg));
+  const float x = fmaxf(v1 * c[6], 0x1p-100f);           // zero: the root of 2^-100 vanishes against eps
+  const float y = __builtin_amdgcn_rsqf(x);
+  const float s0 = x * y;
+  const float s = __builtin_fmaf(__builtin_fmaf(-s0, s0, x), 0.5f * y, s0);
+  const float d = s + c[7], a = m1 * c[5];
+  const float r0 = __builtin_amdgcn_rcpf(d);
+  const float r = __builtin_fmaf(__builtin_fmaf(-d, r0, 1.0f), r0, r0);
+  const float q = a * r;
+  const float upd = __builtin_fmaf(-__builtin_fmaf(d, q, -a), r, q);
+  w1 = __builtin_fmaf(-lr, upd, dw * c[4]);
+}
+
 template <int GFMT, int WCOPY, bool FAST, bool STATS>
 struct AdamUpdateOp {
   const AdamParams& p;
@@ -305,7 +375,8 @@ struct AdamUpdateOp {
   float inv_sg, inv_sm, inv_sv, inv_sw;   // scales of the inputs
   float sm, sv, sw, sq;                   // scales of the outputs
   float decay;                            // 1 - lr * weight_decay, or 1 for a tensor that is exempt
-  bool careful;
+  bool careful, tame;
+  float c[8];                             // coefficients of the tame range
   float vmax, wmax, mmax;                 // running maxima of v', |w'| (and |m'| on the careful path)
   uint32_t nf;
   uint32_t cnt[8];                        // sat m,v,w,q ; underflow m,v,w,q: per lane (tails, careful path)
@@ -320,6 +391,9 @@ struct AdamUpdateOp {
     inv_sw = p.w_meta[t].inv_scale;
     sm = P.sm; sv = P.sv; sw = P.sw; sq = P.sq;
     careful = P.careful != 0;
+    tame = !FAST && P.tame != 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = P.c[i];
     vmax = wmax = mmax = 0.0f;
     nf = 0;
 #pragma unroll
@@ -361,7 +435,7 @@ struct AdamUpdateOp {
   struct Quad { uint32_t m, v01, v23, w01, w23, q, q2; };
 
   // four elements: one word of gradient codes, one of moment codes, two words each of v and w
-  template <bool WAVE>
+  template <bool WAVE, bool TAME>
   __device__ __forceinline__ Quad quad(uint32_t gw, uint32_t mw, uint32_t v01, uint32_t v23, uint32_t w01, uint32_t w23) {
     const float2_t dg01 = fp8x2_to_f32<GFMT, false>(gw), dg23 = fp8x2_to_f32<GFMT, true>(gw);
     const float2_t dm01 = fp8x2_to_f32<kE4M3, false>(mw), dm23 = fp8x2_to_f32<kE4M3, true>(mw);
@@ -374,10 +448,15 @@ struct AdamUpdateOp {
     float tm[4], tv[4], tw[4], tq[4], w1s[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const float g = dg[j] * inv_sg, m0 = dm[j] * inv_sm, v0 = dv[j] * inv_sv, w0 = dw[j] * inv_sw;
-      const float m1 = __builtin_fmaf(p.b1, m0, p.omb1 * g);
-      const float v1 = __builtin_fmaf(p.b2, v0, p.omb2 * (g * g));
-      const float w1 = adam_update<FAST>(m1, v1, w0, decay, p);
+      float m1, v1, w1;
+      if constexpr (TAME) {
+        tame_update(dg[j], dm[j], dv[j], dw[j], c, p.lr, m1, v1, w1);
+      } else {
+        const float g = dg[j] * inv_sg, m0 = dm[j] * inv_sm, v0 = dv[j] * inv_sv, w0 = dw[j] * inv_sw;
+        m1 = __builtin_fmaf(p.b1, m0, p.omb1 * g);
+        v1 = __builtin_fmaf(p.b2, v0, p.omb2 * (g * g));
+        w1 = adam_update<FAST>(m1, v1, w0, decay, p);
+      }
       vmax = fmaxf(vmax, v1);
       wmax = fmaxf(wmax, fabsf(w1));
       mmax = fmaxf(mmax, fabsf(m1));
@@ -435,7 +514,7 @@ struct AdamUpdateOp {
   // Split layout: the 16-bit streams are walked with 128-bit accesses that are contiguous over the whole
   // workgroup (4 KiB per instruction) instead of pairs of adjacent ones; the 8-bit streams then take
   // 64-bit accesses.  Measured 1.6 % faster in a memory-only skeleton of this kernel.
-  template <int UN> __device__ __forceinline__ void tiles_split(long long tile0) {
+  template <int UN, bool TAME> __device__ __forceinline__ void tiles_split(long long tile0) {
     uint2 ga[UN], gb[UN], ma[UN], mb[UN];
     uint4 va[UN], vb[UN], wa[UN], wb[UN];
     const long long pos0 = tile0 + threadIdx.x * 8;
@@ -456,10 +535,10 @@ struct AdamUpdateOp {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       const long long a = pos0 + u * kTile, b = a + kTile / 2;
-      const Quad q0 = quad<true>(ga[u].x, ma[u].x, va[u].x, va[u].y, wa[u].x, wa[u].y);
-      const Quad q1 = quad<true>(ga[u].y, ma[u].y, va[u].z, va[u].w, wa[u].z, wa[u].w);
-      const Quad q2 = quad<true>(gb[u].x, mb[u].x, vb[u].x, vb[u].y, wb[u].x, wb[u].y);
-      const Quad q3 = quad<true>(gb[u].y, mb[u].y, vb[u].z, vb[u].w, wb[u].z, wb[u].w);
+      const Quad q0 = quad<true, TAME>(ga[u].x, ma[u].x, va[u].x, va[u].y, wa[u].x, wa[u].y);
+      const Quad q1 = quad<true, TAME>(ga[u].y, ma[u].y, va[u].z, va[u].w, wa[u].z, wa[u].w);
+      const Quad q2 = quad<true, TAME>(gb[u].x, mb[u].x, vb[u].x, vb[u].y, wb[u].x, wb[u].y);
+      const Quad q3 = quad<true, TAME>(gb[u].y, mb[u].y, vb[u].z, vb[u].w, wb[u].z, wb[u].w);
       st8<kNtStoreRW>(p.m + a, make_uint2(q0.m, q1.m));
       st8<kNtStoreRW>(p.m + b, make_uint2(q2.m, q3.m));
       st16<kNtStoreRW>(pv + a, make_uint4(q0.v01, q0.v23, q1.v01, q1.v23));
@@ -478,8 +557,8 @@ struct AdamUpdateOp {
     }
   }
   template <int UN> __device__ __forceinline__ void tiles(long long tile0) {
-    if constexpr (FP8LM_UPDATE_SPLIT) tiles_split<UN>(tile0);
-    else tiles_plain<UN>(tile0);
+    if (!FAST && tame) tiles_split<UN, !FAST>(tile0);
+    else tiles_split<UN, false>(tile0);
   }
   // a thread takes 16 consecutive elements of the tile
   template <int UN> __device__ __forceinline__ void tiles_plain(long long tile0) {
@@ -500,10 +579,10 @@ struct AdamUpdateOp {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       const long long pos = pos0 + u * kTile;
-      const Quad q0 = quad<true>(g[u].x, m[u].x, va[u].x, va[u].y, wa[u].x, wa[u].y);
-      const Quad q1 = quad<true>(g[u].y, m[u].y, va[u].z, va[u].w, wa[u].z, wa[u].w);
-      const Quad q2 = quad<true>(g[u].z, m[u].z, vb[u].x, vb[u].y, wb[u].x, wb[u].y);
-      const Quad q3 = quad<true>(g[u].w, m[u].w, vb[u].z, vb[u].w, wb[u].z, wb[u].w);
+      const Quad q0 = quad<true, false>(g[u].x, m[u].x, va[u].x, va[u].y, wa[u].x, wa[u].y);
+      const Quad q1 = quad<true, false>(g[u].y, m[u].y, va[u].z, va[u].w, wa[u].z, wa[u].w);
+      const Quad q2 = quad<true, false>(g[u].z, m[u].z, vb[u].x, vb[u].y, wb[u].x, wb[u].y);
+      const Quad q3 = quad<true, false>(g[u].w, m[u].w, vb[u].z, vb[u].w, wb[u].z, wb[u].w);
       st16<kNtStoreRW>(p.m + pos, make_uint4(q0.m, q1.m, q2.m, q3.m));
       st16<kNtStoreRW>(pv + pos, make_uint4(q0.v01, q0.v23, q1.v01, q1.v23));
       st16<kNtStoreRW>(pv + pos + 8, make_uint4(q2.v01, q2.v23, q3.v01, q3.v23));
@@ -527,7 +606,7 @@ struct AdamUpdateOp {
       uint16_t* pw = static_cast<uint16_t*>(p.w);
       for (int j = 0; j < valid; ++j) {
         const long long i = pos + j;
-        const Quad o = quad<false>(p.grad[i], p.m_in[i], pv[i], 0u, pw[i], 0u);
+        const Quad o = quad<false, false>(p.grad[i], p.m_in[i], pv[i], 0u, pw[i], 0u);
         p.m[i] = (uint8_t)o.m;
         pv[i] = (uint16_t)o.v01;
         pw[i] = (uint16_t)o.w01;

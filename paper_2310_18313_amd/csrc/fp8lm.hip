@@ -49,7 +49,7 @@ constexpr int kStaticMaxGrid = 4096;                      // workgroups of a lau
 constexpr int kStaticChunkElems = 16384;
 struct StaticArena {
   TensorDesc desc[FP8LM_STATIC_MAX_TENSORS];              // 128 KiB
-  Scratch scratch[FP8LM_STATIC_MAX_TENSORS];              // 288 KiB
+  Scratch scratch[FP8LM_STATIC_MAX_TENSORS];              // 512 KiB
   Partial partials[kStaticMaxGrid + FP8LM_STATIC_MAX_TENSORS + 1];   // 1 MiB
   int32_t chunk_tensor[FP8LM_STATIC_MAX_CHUNKS];          // 4 MiB
 };

@@ -28,7 +28,7 @@ struct TensorDesc {
 
 // Per-tensor scratch.  The ticket is zero between launches; the `pend` block carries the scales chosen
 // by the first Adam pass to the second.
-struct Scratch {
+struct alignas(128) Scratch {
   uint32_t ticket;                // chunks finished
   uint32_t redo;                  // speculative quantisation: 1 if the tensor has to be cast again with the scale now in its meta
   float old_scale, old_inv;       // ... and the scale the meta held before the speculation
@@ -37,6 +37,8 @@ struct Scratch {
     uint32_t fm, fv, fw, fq;      // flags gathered while choosing the scales
     uint32_t careful;
     uint32_t amax_m_bits;   // written by a fused cast: bit pattern of max |m'|
+    uint32_t tame;          // the update may take the short arithmetic, with these coefficients (tame_range)
+    float c[8];
   } pend;
 };
 
