@@ -156,9 +156,10 @@ fp8lm_status fp8lm_create(fp8lm_ctx** out, const fp8lm_tensor* tensors /*host*/,
 fp8lm_status fp8lm_destroy(fp8lm_ctx* ctx);
 
 /*
- * Launch tuning (optional; defaults 16384, 16, 2^30).  chunk_elems: elements per work unit, a multiple of
- * 4096 in [4096, 1048576]; a chunk never spans two tensors and each workgroup walks one contiguous range
- * of chunks.  blocks_per_cu: 256-thread workgroups per compute unit that a launch uses at most, 1..16.
+ * Launch tuning (optional; defaults 16384, 16, 2^30).  chunk_elems: granularity of the work, a multiple of
+ * 4096 in [4096, 1048576]; a chunk never spans two tensors.  blocks_per_cu: 256-thread workgroups per compute unit
+ * that a launch uses at most, 1..15, each walking one contiguous range of chunks; 16 = no limit: chunks are cut into
+ * units of one to four tiles of 4096 elements, one workgroup each (measured faster at every size on MI355X).
  * single_pass_min_chunks: how the per-tensor statistics of the workgroups are combined.  With at least
  * this many chunks per workgroup, in the same launch (each workgroup bumps a per-tensor ticket, the one
  * that completes it finishes the tensor); with fewer, in a second tiny launch, because the tickets then
@@ -409,7 +410,7 @@ fp8lm_status fp8lm_get_moment_speculation_stats(fp8lm_ctx* ctx, uint64_t* calls 
  * forbid allocation.  Same arithmetic, same kernels, same results, bit for bit; what a context keeps in
  * hipMalloc'd memory (tensor and chunk tables, the per-tensor scales that the first pass hands to the second,
  * the per-workgroup reduction records) lives in a fixed array inside the library's device image instead (about
- * 5.4 MiB, held by every GPU the library runs on until the process ends).  Every call rebuilds the tables in
+ * 6.2 MiB, held by every GPU the library runs on until the process ends).  Every call rebuilds the tables in
  * that array from `tensors` with small kernels on `stream` (arguments travel as kernel arguments: no copy from
  * host memory), then runs the two passes.  The call itself calls no allocator of any kind.
  *   device       : GPU that owns all buffers; tensors, tensor_flags: host arrays of n entries, read during the
@@ -490,11 +491,15 @@ fp8lm_status fp8lm_copy_bytes(fp8lm_ctx* ctx, const void* src /*device*/, void* 
  *   UPDATE_READS / UPDATE_WRITES  same bufs as UPDATE: only its four read streams (6 B/element), only its four
  *                                               write streams (6): what the two directions reach when they do not
  *                                               share the memory with each other
+ *   UPDATE_RANGES  UPDATE walked by a persistent grid, every workgroup through a range of its own instead of the chip
+ *                                               sweeping through the buffers in order: slower than the kernel, and more
+ *                                               sensitive to where the buffers lie in HBM (fp8lm_vmm_*), so this is the
+ *                                               shape to find that out with
  *   bufs : host array of device pointers, each covering n_elems elements; n_elems a multiple of 4096.
  */
 typedef enum { FP8LM_SKEL_READ16 = 0, FP8LM_SKEL_READ8X2 = 1, FP8LM_SKEL_WRITE16 = 2, FP8LM_SKEL_WRITE8 = 3,
                FP8LM_SKEL_CAST = 4, FP8LM_SKEL_UPDATE = 5, FP8LM_SKEL_UPDATE_READS = 6,
-               FP8LM_SKEL_UPDATE_WRITES = 7 } fp8lm_skeleton;
+               FP8LM_SKEL_UPDATE_WRITES = 7, FP8LM_SKEL_UPDATE_RANGES = 8 } fp8lm_skeleton;
 fp8lm_status fp8lm_memory_skeleton(fp8lm_ctx* ctx, int32_t shape, void* const* bufs /*host -> device*/,
                                    int64_t n_elems, void* stream);
 
@@ -503,7 +508,7 @@ fp8lm_status fp8lm_memory_skeleton(fp8lm_ctx* ctx, int32_t shape, void* const* b
  * lay their flat buffers out over the regions of HBM.  On MI355X a kernel that writes (the update pass, the cast)
  * runs up to 20 % slower while everything it writes lies in one 96 GiB region of the physical address space; a buffer
  * whose address range alternates between pieces from two regions does not have that problem wherever a kernel is in
- * it.  Where a piece lies can only be measured (fp8lm_memory_skeleton across two pieces is faster than inside one
+ * it.  Where a piece lies can only be measured (fp8lm_memory_skeleton, UPDATE_RANGES, across two pieces is faster than inside one
  * region), so the steps are separate: create pieces, map each somewhere, time it against a reference piece, then map
  * the pieces wanted into one reserved range in alternating order and destroy the others.  None of these calls is on
  * the path of a training step; they allocate, and fp8lm_vmm_unmap waits for the device.

@@ -27,9 +27,9 @@ struct InitCastOp {
   uint32_t n_sat, n_und;
   bool careful;
   __device__ InitCastOp(const InitParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
-  __device__ __forceinline__ void begin(int t, const TensorDesc&) {
-    scale = p.meta[t].scale;
-    careful = (p.meta[t].flags & FP8LM_FLAG_NONFINITE) != 0;   // set by the amax pass just before
+  __device__ __forceinline__ void begin(int t) {
+    scale = uniform_load(&p.meta[t].scale);
+    careful = (uniform_load(&p.meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0;   // set by the amax pass just before
     vmax = 0.0f;
     n_sat = n_und = 0;
   }
@@ -42,10 +42,16 @@ struct InitCastOp {
     n_sat += (c & WT::kMagMask) == WT::kTopCode;
     n_und += nonzero_in && ((c & WT::kMagMask) == 0);
   }
-  template <int UN> __device__ __forceinline__ void tiles(long long pos0) {
+  template <int UN> struct Regs { uint4 a, b; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& g, long long pos0) {
     static_assert(UN == 1, "one group at a time");
     const long long pos = pos0 + threadIdx.x * kGroup;
-    const uint4 a = ld16<kNtLoadRO>(p.src + pos), b = ld16<kNtLoadRO>(p.src + pos + 8);
+    g.a = ld16<kNtLoadRO>(p.src + pos);
+    g.b = ld16<kNtLoadRO>(p.src + pos + 8);
+  }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& g, long long pos0) {
+    const long long pos = pos0 + threadIdx.x * kGroup;
+    const uint4 a = g.a, b = g.b;
     const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
     float y[kGroup];
 #pragma unroll
@@ -58,7 +64,11 @@ struct InitCastOp {
     st_store16<MASTER>(p.dst, pos, y);
   }
   // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
-  __device__ __forceinline__ void full_group(long long pos) { tiles<1>(pos - (long long)threadIdx.x * kGroup); }
+  __device__ __forceinline__ void full_group(long long pos) {
+    Regs<1> g;
+    load(g, pos - (long long)threadIdx.x * kGroup);
+    tiles(g, pos - (long long)threadIdx.x * kGroup);
+  }
   __device__ __forceinline__ void group(long long pos, int valid) {
     for (int j = 0; j < valid; ++j) {
       const uint32_t bits = p.src[pos + j];
@@ -72,14 +82,13 @@ struct InitCastOp {
     }
   }
   using Stats = BlockStats<1, 2>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
+  __device__ __forceinline__ void flush(int t, long long u) {
+    BlockStats<1, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.ct[0] = n_sat;
     s.ct[1] = n_und;
     s.orv = 0;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+    collect(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -94,7 +103,7 @@ struct InitCastOp {
 template <int MASTER>
 __global__ __launch_bounds__(kThreads) void init_master_cast_kernel(Tables tb, InitParams p) {
   InitCastOp<MASTER> op(p, tb);
-  walk_chunks<1>(tb, op);
+  walk_units<1>(tb, op);
 }
 
 // ================================================================================================
@@ -226,8 +235,9 @@ __device__ void adam_choose_scales(const AdamParams& p, Scratch::Pending& P, int
   const bool calm = !anyflag && (bound_m < kBig) && (G.amax_deq < kBig) && (Mm.amax_deq < kBig) &&
                     (Mv.amax_deq < kHuge) && (Mw.amax_deq < kHuge);
   P.careful = calm ? 0u : 1u;
-  P.tame = tame_range(p, G.inv_scale, Mm.inv_scale, Mv.inv_scale, Mw.inv_scale,
-                      (tensor_flags & FP8LM_TENSOR_NO_WEIGHT_DECAY) ? 1.0f : p.decay, P.c) ? 1u : 0u;
+  P.decay = (tensor_flags & FP8LM_TENSOR_NO_WEIGHT_DECAY) ? 1.0f : p.decay;
+  P.inv_sg = G.inv_scale; P.inv_sm = Mm.inv_scale; P.inv_sv = Mv.inv_scale; P.inv_sw = Mw.inv_scale;
+  P.tame = tame_range(p, P.inv_sg, P.inv_sm, P.inv_sv, P.inv_sw, P.decay, P.c) ? 1u : 0u;
 }
 
 // Single-pass variant: the first-moment scale comes from the bound
@@ -275,9 +285,9 @@ struct AdamAmaxOp {
   float inv_sg, inv_sm;
   uint32_t acc;
   __device__ AdamAmaxOp(const AdamParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
-  __device__ __forceinline__ void begin(int t, const TensorDesc&) {
-    inv_sg = p.grad_meta[t].inv_scale;
-    inv_sm = p.m_meta[t].inv_scale;
+  __device__ __forceinline__ void begin(int t) {
+    inv_sg = uniform_load(&p.grad_meta[t].inv_scale);
+    inv_sm = uniform_load(&p.m_meta[t].inv_scale);
     acc = 0;
   }
   __device__ __forceinline__ void elem(float dg, float dm) {
@@ -294,34 +304,39 @@ struct AdamAmaxOp {
     elem(g23.y, m23.y);
   }
   __device__ __forceinline__ bool fast() const { return true; }
-  template <int UN> __device__ __forceinline__ void tiles(long long pos0) {
-    uint4 g[UN], m[UN];
+  template <int UN> struct Regs { uint4 g[UN], m[UN]; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& r, long long pos0) {
     const long long pos = pos0 + threadIdx.x * kGroup;
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      g[u] = ld16<kNtLoadRO>(p.grad + pos + u * kTile);
-      m[u] = ld16<kNtLoadRO>(p.m + pos + u * kTile);
+      r.g[u] = ld16<kNtLoadRO>(p.grad + pos + u * kTile);
+      r.m[u] = ld16<kNtLoadRO>(p.m + pos + u * kTile);
     }
+  }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& r, long long) {
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
-      word(g[u].x, m[u].x);
-      word(g[u].y, m[u].y);
-      word(g[u].z, m[u].z);
-      word(g[u].w, m[u].w);
+      word(r.g[u].x, r.m[u].x);
+      word(r.g[u].y, r.m[u].y);
+      word(r.g[u].z, r.m[u].z);
+      word(r.g[u].w, r.m[u].w);
     }
   }
   // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
-  __device__ __forceinline__ void full_group(long long pos) { tiles<1>(pos - (long long)threadIdx.x * kGroup); }
+  __device__ __forceinline__ void full_group(long long pos) {
+    Regs<1> g;
+    load(g, pos - (long long)threadIdx.x * kGroup);
+    tiles(g, pos - (long long)threadIdx.x * kGroup);
+  }
   __device__ __forceinline__ void group(long long pos, int valid) {
     for (int j = 0; j < valid; ++j) elem(fp8_to_f32<GFMT>(p.grad[pos + j]), fp8_to_f32<kE4M3>(p.m[pos + j]));
   }
   using Stats = BlockStats<1, 0>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
+  __device__ __forceinline__ void flush(int t, long long u) {
+    BlockStats<1, 0, uint32_t> s;
     s.mx[0] = acc;
     s.orv = 0;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+    collect(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const uint32_t abits = s.mx[0];
@@ -333,7 +348,7 @@ struct AdamAmaxOp {
 template <int GFMT, int WCOPY>
 __global__ __launch_bounds__(kThreads) void adam_amax_kernel(Tables tb, AdamParams p) {
   AdamAmaxOp<GFMT, WCOPY> op(p, tb);
-  walk_chunks<FP8LM_UN_READ>(tb, op);
+  walk_units<kUnRead>(tb, op);
 }
 
 // ---- pass B: the update ----------------------------------------------------------------------------
@@ -382,13 +397,10 @@ struct AdamUpdateOp {
   uint32_t cnt[8];                        // sat m,v,w,q ; underflow m,v,w,q: per lane (tails, careful path)
   uint32_t wcnt[8];                       // the same for whole tiles: wave totals, identical in every lane
   __device__ AdamUpdateOp(const AdamParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
-  __device__ __forceinline__ void begin(int t, const TensorDesc& d) {
-    const Scratch::Pending& P = tb.scratch[t].pend;
-    decay = (d.flags & FP8LM_TENSOR_NO_WEIGHT_DECAY) ? 1.0f : p.decay;
-    inv_sg = p.grad_meta[t].inv_scale;
-    inv_sm = p.m_meta[t].inv_scale;
-    inv_sv = p.v_meta[t].inv_scale;
-    inv_sw = p.w_meta[t].inv_scale;
+  __device__ __forceinline__ void begin(int t) {
+    const Scratch::Pending P = uniform_load(&tb.scratch[t].pend);
+    decay = P.decay;
+    inv_sg = P.inv_sg; inv_sm = P.inv_sm; inv_sv = P.inv_sv; inv_sw = P.inv_sw;
     sm = P.sm; sv = P.sv; sw = P.sw; sq = P.sq;
     careful = P.careful != 0;
     tame = !FAST && P.tame != 0;
@@ -513,92 +525,58 @@ struct AdamUpdateOp {
   __device__ __forceinline__ bool fast() const { return !careful; }
   // Split layout: the 16-bit streams are walked with 128-bit accesses that are contiguous over the whole
   // workgroup (4 KiB per instruction) instead of pairs of adjacent ones; the 8-bit streams then take
-  // 64-bit accesses.  Measured 1.6 % faster in a memory-only skeleton of this kernel.
-  template <int UN, bool TAME> __device__ __forceinline__ void tiles_split(long long tile0) {
-    uint2 ga[UN], gb[UN], ma[UN], mb[UN];
-    uint4 va[UN], vb[UN], wa[UN], wb[UN];
-    const long long pos0 = tile0 + threadIdx.x * 8;
+  // 64-bit accesses.  Measured 1.6 % faster in a memory-only skeleton of this kernel.  kSplit = false: a thread takes
+  // 16 consecutive elements (it is alone with them).
+  template <int UN> struct Regs { uint2 ga, gb, ma, mb; uint4 va, vb, wa, wb; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& r, long long tile0) { load_as<true>(r, tile0 + threadIdx.x * 8); }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& r, long long tile0) {
+    if (!FAST && tame) update_as<true, !FAST>(r, tile0 + threadIdx.x * 8);
+    else update_as<true, false>(r, tile0 + threadIdx.x * 8);
+  }
+  template <bool kSplit, int UN> __device__ __forceinline__ void load_as(Regs<UN>& r, long long a) {
+    static_assert(UN == 1, "one tile at a time");
+    const long long b = a + (kSplit ? kTile / 2 : 8);
+    const uint16_t* pv = static_cast<const uint16_t*>(p.v);
+    const uint16_t* pw = static_cast<const uint16_t*>(p.w);
+    r.ga = ld8<kNtLoadRO>(p.grad + a);
+    r.gb = ld8<kNtLoadRO>(p.grad + b);
+    r.ma = ld8<kNtLoadRW>(p.m_in + a);
+    r.mb = ld8<kNtLoadRW>(p.m_in + b);
+    r.va = ld16<kNtLoadRW>(pv + a);
+    r.vb = ld16<kNtLoadRW>(pv + b);
+    r.wa = ld16<kNtLoadRW>(pw + a);
+    r.wb = ld16<kNtLoadRW>(pw + b);
+  }
+  template <bool kSplit, bool TAME, int UN> __device__ __forceinline__ void update_as(const Regs<UN>& r, long long a) {
+    const long long b = a + (kSplit ? kTile / 2 : 8);
     uint16_t* pv = static_cast<uint16_t*>(p.v);
     uint16_t* pw = static_cast<uint16_t*>(p.w);
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const long long a = pos0 + u * kTile, b = a + kTile / 2;
-      ga[u] = ld8<kNtLoadRO>(p.grad + a);
-      gb[u] = ld8<kNtLoadRO>(p.grad + b);
-      ma[u] = ld8<kNtLoadRW>(p.m_in + a);
-      mb[u] = ld8<kNtLoadRW>(p.m_in + b);
-      va[u] = ld16<kNtLoadRW>(pv + a);
-      vb[u] = ld16<kNtLoadRW>(pv + b);
-      wa[u] = ld16<kNtLoadRW>(pw + a);
-      wb[u] = ld16<kNtLoadRW>(pw + b);
-    }
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const long long a = pos0 + u * kTile, b = a + kTile / 2;
-      const Quad q0 = quad<true, TAME>(ga[u].x, ma[u].x, va[u].x, va[u].y, wa[u].x, wa[u].y);
-      const Quad q1 = quad<true, TAME>(ga[u].y, ma[u].y, va[u].z, va[u].w, wa[u].z, wa[u].w);
-      const Quad q2 = quad<true, TAME>(gb[u].x, mb[u].x, vb[u].x, vb[u].y, wb[u].x, wb[u].y);
-      const Quad q3 = quad<true, TAME>(gb[u].y, mb[u].y, vb[u].z, vb[u].w, wb[u].z, wb[u].w);
-      st8<kNtStoreRW>(p.m + a, make_uint2(q0.m, q1.m));
-      st8<kNtStoreRW>(p.m + b, make_uint2(q2.m, q3.m));
-      st16<kNtStoreRW>(pv + a, make_uint4(q0.v01, q0.v23, q1.v01, q1.v23));
-      st16<kNtStoreRW>(pv + b, make_uint4(q2.v01, q2.v23, q3.v01, q3.v23));
-      st16<kNtStoreRW>(pw + a, make_uint4(q0.w01, q0.w23, q1.w01, q1.w23));
-      st16<kNtStoreRW>(pw + b, make_uint4(q2.w01, q2.w23, q3.w01, q3.w23));
-      if constexpr (WCOPY == FP8LM_WCOPY_E4M3) {
-        uint8_t* q = static_cast<uint8_t*>(p.wcopy);
-        st8<kNtStoreWO>(q + a, make_uint2(q0.q, q1.q));
-        st8<kNtStoreWO>(q + b, make_uint2(q2.q, q3.q));
-      } else {
-        uint16_t* q = static_cast<uint16_t*>(p.wcopy);
-        st16<kNtStoreWO>(q + a, make_uint4(q0.q, q0.q2, q1.q, q1.q2));
-        st16<kNtStoreWO>(q + b, make_uint4(q2.q, q2.q2, q3.q, q3.q2));
-      }
+    const Quad q0 = quad<kSplit, TAME>(r.ga.x, r.ma.x, r.va.x, r.va.y, r.wa.x, r.wa.y);
+    const Quad q1 = quad<kSplit, TAME>(r.ga.y, r.ma.y, r.va.z, r.va.w, r.wa.z, r.wa.w);
+    const Quad q2 = quad<kSplit, TAME>(r.gb.x, r.mb.x, r.vb.x, r.vb.y, r.wb.x, r.wb.y);
+    const Quad q3 = quad<kSplit, TAME>(r.gb.y, r.mb.y, r.vb.z, r.vb.w, r.wb.z, r.wb.w);
+    st8<kNtStoreRW>(p.m + a, make_uint2(q0.m, q1.m));
+    st8<kNtStoreRW>(p.m + b, make_uint2(q2.m, q3.m));
+    st16<kNtStoreRW>(pv + a, make_uint4(q0.v01, q0.v23, q1.v01, q1.v23));
+    st16<kNtStoreRW>(pv + b, make_uint4(q2.v01, q2.v23, q3.v01, q3.v23));
+    st16<kNtStoreRW>(pw + a, make_uint4(q0.w01, q0.w23, q1.w01, q1.w23));
+    st16<kNtStoreRW>(pw + b, make_uint4(q2.w01, q2.w23, q3.w01, q3.w23));
+    if constexpr (WCOPY == FP8LM_WCOPY_E4M3) {
+      uint8_t* q = static_cast<uint8_t*>(p.wcopy);
+      st8<kNtStoreWO>(q + a, make_uint2(q0.q, q1.q));
+      st8<kNtStoreWO>(q + b, make_uint2(q2.q, q3.q));
+    } else {
+      uint16_t* q = static_cast<uint16_t*>(p.wcopy);
+      st16<kNtStoreWO>(q + a, make_uint4(q0.q, q0.q2, q1.q, q1.q2));
+      st16<kNtStoreWO>(q + b, make_uint4(q2.q, q2.q2, q3.q, q3.q2));
     }
   }
-  template <int UN> __device__ __forceinline__ void tiles(long long tile0) {
-    if (!FAST && tame) tiles_split<UN, !FAST>(tile0);
-    else tiles_split<UN, false>(tile0);
+  // 16 consecutive elements at `pos`, by this thread alone
+  __device__ __forceinline__ void full_group(long long pos) {
+    Regs<1> r;
+    load_as<false>(r, pos);
+    update_as<false, false>(r, pos);
   }
-  // a thread takes 16 consecutive elements of the tile
-  template <int UN> __device__ __forceinline__ void tiles_plain(long long tile0) {
-    uint4 g[UN], m[UN], va[UN], vb[UN], wa[UN], wb[UN];
-    const long long pos0 = tile0 + threadIdx.x * kGroup;
-    uint16_t* pv = static_cast<uint16_t*>(p.v);
-    uint16_t* pw = static_cast<uint16_t*>(p.w);
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const long long pos = pos0 + u * kTile;
-      g[u] = ld16<kNtLoadRO>(p.grad + pos);
-      m[u] = ld16<kNtLoadRW>(p.m_in + pos);
-      va[u] = ld16<kNtLoadRW>(pv + pos);
-      vb[u] = ld16<kNtLoadRW>(pv + pos + 8);
-      wa[u] = ld16<kNtLoadRW>(pw + pos);
-      wb[u] = ld16<kNtLoadRW>(pw + pos + 8);
-    }
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const long long pos = pos0 + u * kTile;
-      const Quad q0 = quad<true, false>(g[u].x, m[u].x, va[u].x, va[u].y, wa[u].x, wa[u].y);
-      const Quad q1 = quad<true, false>(g[u].y, m[u].y, va[u].z, va[u].w, wa[u].z, wa[u].w);
-      const Quad q2 = quad<true, false>(g[u].z, m[u].z, vb[u].x, vb[u].y, wb[u].x, wb[u].y);
-      const Quad q3 = quad<true, false>(g[u].w, m[u].w, vb[u].z, vb[u].w, wb[u].z, wb[u].w);
-      st16<kNtStoreRW>(p.m + pos, make_uint4(q0.m, q1.m, q2.m, q3.m));
-      st16<kNtStoreRW>(pv + pos, make_uint4(q0.v01, q0.v23, q1.v01, q1.v23));
-      st16<kNtStoreRW>(pv + pos + 8, make_uint4(q2.v01, q2.v23, q3.v01, q3.v23));
-      st16<kNtStoreRW>(pw + pos, make_uint4(q0.w01, q0.w23, q1.w01, q1.w23));
-      st16<kNtStoreRW>(pw + pos + 8, make_uint4(q2.w01, q2.w23, q3.w01, q3.w23));
-      if constexpr (WCOPY == FP8LM_WCOPY_E4M3) {
-        st16<kNtStoreWO>(static_cast<uint8_t*>(p.wcopy) + pos, make_uint4(q0.q, q1.q, q2.q, q3.q));
-      } else {
-        uint16_t* q = static_cast<uint16_t*>(p.wcopy);
-        st16<kNtStoreWO>(q + pos, make_uint4(q0.q, q0.q2, q1.q, q1.q2));
-        st16<kNtStoreWO>(q + pos + 8, make_uint4(q2.q, q2.q2, q3.q, q3.q2));
-      }
-    }
-  }
-  // 16 consecutive elements at `pos`, by this thread alone (the layout without the split)
-  __device__ __forceinline__ void full_group(long long pos) { tiles_plain<1>(pos - (long long)threadIdx.x * kGroup); }
   __device__ __forceinline__ void group(long long pos, int valid) {
     if (!careful) {
       // ragged tail of a tensor: same arithmetic, element by element
@@ -619,8 +597,8 @@ struct AdamUpdateOp {
   }
 
   using Stats = BlockStats<3, STATS ? 8 : 0>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
+  __device__ __forceinline__ void flush(int t, long long u) {
+    BlockStats<3, STATS ? 8 : 0, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = f2u(wmax);
     s.mx[2] = f2u(mmax);
@@ -630,8 +608,7 @@ struct AdamUpdateOp {
       for (int i = 0; i < 8; ++i) s.ct[i] = cnt[i] + (first_lane ? wcnt[i] : 0u);
     }
     s.orv = nf;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+    collect(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     unsigned long long c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -705,7 +682,7 @@ struct AdamUpdateOp {
 template <int GFMT, int WCOPY, bool FAST, bool STATS>
 __global__ __launch_bounds__(kThreads) void adam_update_kernel(Tables tb, AdamParams p) {
   AdamUpdateOp<GFMT, WCOPY, FAST, STATS> op(p, tb);
-  walk_chunks<FP8LM_UN_UPDATE>(tb, op);
+  walk_units<kUnUpdate>(tb, op);
 }
 
 // ---- repair of a failed first-moment speculation ---------------------------------------------------
@@ -718,7 +695,7 @@ struct AdamMomentRedoOp {
   float inv_sg, inv_sm, sm;
   bool careful;
   __device__ AdamMomentRedoOp(const AdamParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
-  __device__ __forceinline__ void begin(int t, const TensorDesc&) {
+  __device__ __forceinline__ void begin(int t) {
     inv_sg = p.grad_meta[t].inv_scale;
     inv_sm = tb.scratch[t].old_inv;                 // the scale m_in is stored with (m_meta already holds the new one)
     sm = tb.scratch[t].pend.sm;
@@ -734,15 +711,21 @@ struct AdamMomentRedoOp {
                               moment(g23.y, m23.y) * sm);
   }
   __device__ __forceinline__ bool fast() const { return !careful; }
-  template <int UN> __device__ __forceinline__ void tiles(long long pos0) {
+  template <int UN> struct Regs { uint4 g, m; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& r, long long pos0) {
+    static_assert(UN == 1, "one tile at a time");
     const long long pos = pos0 + threadIdx.x * kGroup;
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const uint4 g = ld16<kNtLoadRO>(p.grad + pos + u * kTile), m = ld16<kNtLoadRO>(p.m_in + pos + u * kTile);
-      st16<kNtStoreWO>(p.m + pos + u * kTile, make_uint4(word(g.x, m.x), word(g.y, m.y), word(g.z, m.z), word(g.w, m.w)));
-    }
+    r.g = ld16<kNtLoadRO>(p.grad + pos);
+    r.m = ld16<kNtLoadRO>(p.m_in + pos);
   }
-  __device__ __forceinline__ void full_group(long long pos) { tiles<1>(pos - (long long)threadIdx.x * kGroup); }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& r, long long pos0) {
+    st16<kNtStoreWO>(p.m + pos0 + threadIdx.x * kGroup, make_uint4(word(r.g.x, r.m.x), word(r.g.y, r.m.y), word(r.g.z, r.m.z), word(r.g.w, r.m.w)));
+  }
+  __device__ __forceinline__ void full_group(long long pos) {
+    Regs<1> g;
+    load(g, pos - (long long)threadIdx.x * kGroup);
+    tiles(g, pos - (long long)threadIdx.x * kGroup);
+  }
   __device__ __forceinline__ void group(long long pos, int valid) {
     for (int j = 0; j < valid; ++j) {
       const long long i = pos + j;
@@ -750,14 +733,14 @@ struct AdamMomentRedoOp {
     }
   }
   using Stats = BlockStats<1, 0>;
-  __device__ __forceinline__ void flush(int, const TensorDesc&, int) {}      // nothing to reduce: the metadata is complete
+  __device__ __forceinline__ void flush(int, long long) {}      // nothing to reduce: the metadata is complete
   __device__ void finalize(int, const TensorDesc&, const Stats&) {}
 };
 
 template <int GFMT>
 __global__ __launch_bounds__(kThreads) void adam_moment_redo_kernel(Tables tb, AdamParams p) {
   AdamMomentRedoOp<GFMT> op(p, tb);
-  walk_chunks<2>(tb, op);
+  walk_units<1>(tb, op);
 }
 
 // ---- pass B for the other storage formats of the precision-decoupling study ----------------------
@@ -775,13 +758,10 @@ struct AdamUpdateVarOp {
   float vmax, wmax, mmax;
   uint32_t nf;
   __device__ AdamUpdateVarOp(const AdamParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
-  __device__ __forceinline__ void begin(int t, const TensorDesc& d) {
-    const Scratch::Pending& P = tb.scratch[t].pend;
-    decay = (d.flags & FP8LM_TENSOR_NO_WEIGHT_DECAY) ? 1.0f : p.decay;
-    inv_sg = p.grad_meta[t].inv_scale;
-    inv_sm = p.m_meta[t].inv_scale;
-    inv_sv = p.v_meta[t].inv_scale;
-    inv_sw = p.w_meta[t].inv_scale;
+  __device__ __forceinline__ void begin(int t) {
+    const Scratch::Pending P = uniform_load(&tb.scratch[t].pend);
+    decay = P.decay;
+    inv_sg = P.inv_sg; inv_sm = P.inv_sm; inv_sv = P.inv_sv; inv_sw = P.inv_sw;
     sm = P.sm; sv = P.sv; sw = P.sw; sq = P.sq;
     careful = P.careful != 0;
     vmax = wmax = mmax = 0.0f;
@@ -796,13 +776,21 @@ struct AdamUpdateVarOp {
     const float upd = (m1 * p.rbc1) / den;
     w1 = __builtin_fmaf(-p.lr, upd, w0 * decay);
   }
-  template <int UN> __device__ __forceinline__ void tiles(long long tile0) {
+  template <int UN> struct Regs { uint4 gq, mq; float dv[kGroup], dw[kGroup]; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& r, long long tile0) {
     static_assert(UN == 1, "one group at a time");
     const long long pos = tile0 + threadIdx.x * kGroup;
-    const uint4 gq = ld16<kNtLoadRO>(p.grad + pos), mq = ld16<false>(p.m + pos);
+    r.gq = ld16<kNtLoadRO>(p.grad + pos);
+    r.mq = ld16<false>(p.m + pos);
+    st_load16<VFMT>(p.v, pos, r.dv);
+    st_load16<MASTER>(p.w, pos, r.dw);
+  }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& r, long long tile0) {
+    const long long pos = tile0 + threadIdx.x * kGroup;
+    const uint4 gq = r.gq, mq = r.mq;
     float dv[kGroup], dw[kGroup], dg[kGroup], dm[kGroup];
-    st_load16<VFMT>(p.v, pos, dv);
-    st_load16<MASTER>(p.w, pos, dw);
+#pragma unroll
+    for (int j = 0; j < kGroup; ++j) { dv[j] = r.dv[j]; dw[j] = r.dw[j]; }
     const uint32_t gw[4] = {gq.x, gq.y, gq.z, gq.w}, mw[4] = {mq.x, mq.y, mq.z, mq.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -830,7 +818,11 @@ struct AdamUpdateVarOp {
     st_store16<kStE4M3>(p.wcopy, pos, tq);
   }
   // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
-  __device__ __forceinline__ void full_group(long long pos) { tiles<1>(pos - (long long)threadIdx.x * kGroup); }
+  __device__ __forceinline__ void full_group(long long pos) {
+    Regs<1> g;
+    load(g, pos - (long long)threadIdx.x * kGroup);
+    tiles(g, pos - (long long)threadIdx.x * kGroup);
+  }
   __device__ __forceinline__ void group(long long pos, int valid) {
     for (int j = 0; j < valid; ++j) {
       const long long i = pos + j;
@@ -863,14 +855,13 @@ struct AdamUpdateVarOp {
     M.n_underflow = 0;
   }
   using Stats = BlockStats<3, 0>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
+  __device__ __forceinline__ void flush(int t, long long u) {
+    BlockStats<3, 0, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = f2u(wmax);
     s.mx[2] = f2u(mmax);
     s.orv = nf;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+    collect(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float A_v = u2f(s.mx[0]), A_w = u2f(s.mx[1]), A_m = u2f(s.mx[2]);
@@ -886,7 +877,7 @@ struct AdamUpdateVarOp {
 template <int GFMT, int MASTER, int VFMT>
 __global__ __launch_bounds__(kThreads) void adam_update_var_kernel(Tables tb, AdamParams p) {
   AdamUpdateVarOp<GFMT, MASTER, VFMT> op(p, tb);
-  walk_chunks<1>(tb, op);
+  walk_units<1>(tb, op);
 }
 
 }  // namespace fp8lm

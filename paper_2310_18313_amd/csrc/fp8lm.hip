@@ -8,14 +8,14 @@
 //   formats.hpp   FP8 / FP16 / bf16 conversions and the power-of-two scale rule
 //
 // Shape of every hot kernel
-//   * The tensor list is cut into chunks of `chunk_elems` elements that never straddle a tensor.  A grid
-//     of 256-thread workgroups (up to 16 per compute unit) walks contiguous ranges of the chunk table,
-//     so a 5 K-element bias and a 250 M-element matrix are served by the same launch.
-//   * A thread handles 16 elements of a 4096-element tile per iteration, with 128-bit (64-bit on 8-bit
+//   * The tensor list is cut into chunks of `chunk_elems` elements that never straddle a tensor, a chunk into units
+//     of one tile (four in the read-only kernels).  A 256-thread workgroup takes one unit and ends, so that the chip
+//     sweeps through the buffers in order; a 5 K-element bias and a 250 M-element matrix are served by the same launch.
+//   * A thread handles 16 elements of a 4096-element tile, with 128-bit (64-bit on 8-bit
 //     streams of the update and cast kernels) accesses that are contiguous over the whole workgroup.
 //   * Per-tensor statistics (amax, counters) stay in registers while a workgroup is inside one tensor,
-//     then go wavefront -> LDS -> one record per (workgroup, tensor).  A second, tiny launch (one
-//     workgroup per tensor) combines the records and runs the scalar epilogue (scale update,
+//     then go wavefront -> LDS -> one record per unit.  A second, tiny launch (one workgroup per tensor, more
+//     for a large one) combines the records and runs the scalar epilogue (scale update,
 //     auto-scaling state, metadata); a single-pass form with a per-tensor ticket is selectable.
 //   * These kernels are HBM-bandwidth bound (2..12 bytes per element against ~10-60 ALU operations); no
 //     matrix cores are involved.
@@ -45,13 +45,17 @@
 namespace fp8lm {
 
 // Everything a context keeps in hipMalloc'd memory, at fixed maximum sizes.
-constexpr int kStaticMaxGrid = 4096;                      // workgroups of a launch: bounds the reduction records
 constexpr int kStaticChunkElems = 16384;
+constexpr int kStaticRecords = 4 << 20;                   // bytes of records
+constexpr int kStaticChunks = kStaticRecords / 64;        // chunks of a launch; longer lists have larger chunks
+constexpr int kStaticEpilogue = FP8LM_STATIC_MAX_TENSORS + kStaticChunks / kEpilogueChunks;
 struct StaticArena {
   TensorDesc desc[FP8LM_STATIC_MAX_TENSORS];              // 128 KiB
   Scratch scratch[FP8LM_STATIC_MAX_TENSORS];              // 512 KiB
-  Partial partials[kStaticMaxGrid + FP8LM_STATIC_MAX_TENSORS + 1];   // 1 MiB
-  int32_t chunk_tensor[FP8LM_STATIC_MAX_CHUNKS];          // 4 MiB
+  unsigned char records[kStaticRecords];                  // 4 MiB
+  unsigned long long totals[(size_t)kStaticEpilogue * kTotalWords];   // 528 KiB
+  int32_t epi_tensor[kStaticEpilogue];                    // 16.5 KiB
+  ChunkDesc chunks[kStaticChunks];                        // 1 MiB
 };
 
 // A batch of tensor descriptors travels as kernel arguments: no copy from host memory is enqueued.
@@ -64,15 +68,6 @@ __global__ void static_desc_kernel(DescBatch b, TensorDesc* desc) {
   const int i = threadIdx.x;
   if (i < b.count) desc[b.first + i] = b.d[i];
 }
-// Workgroup t (and t + grid, ...) writes tensor t's id into its chunks; also returns the tickets to zero.
-__global__ void static_chunks_kernel(const TensorDesc* desc, int32_t* chunk_tensor, Scratch* scratch, int n) {
-  for (int t = blockIdx.x; t < n; t += gridDim.x) {
-    const TensorDesc d = desc[t];
-    for (int i = threadIdx.x; i < d.n_chunks; i += blockDim.x) chunk_tensor[d.first_chunk + i] = t;
-    if (threadIdx.x == 0) scratch[t].ticket = 0;
-  }
-}
-
 }  // namespace fp8lm
 
 // The array itself.  In host code this name is only a handle for hipGetSymbolAddress: the device address is
@@ -94,16 +89,21 @@ struct fp8lm_ctx {
   std::vector<uint32_t> tensor_flags;   // FP8LM_TENSOR_* per tensor
   int32_t chunk_elems = 16384;
   int32_t blocks_per_cu = kMaxBlocksPerCu;
-  int32_t single_pass_min_chunks = FP8LM_SINGLE_PASS_MIN_CHUNKS;
+  int32_t single_pass_min_chunks = 1 << 30;
   int32_t n_chunks = 0;
   TensorDesc* d_desc = nullptr;
-  int32_t* d_chunk_tensor = nullptr;
+  ChunkDesc* d_chunks = nullptr;
   Scratch* d_scratch = nullptr;
-  Partial* d_partials = nullptr;    // [num_cus * kMaxBlocksPerCu + n_tensors]
+  unsigned char* d_records = nullptr;   // one record per unit
+  size_t record_bytes = 0;
+  unsigned long long* d_totals = nullptr;
+  int32_t* d_epi_tensor = nullptr;
+  int32_t n_epi = 0;
+  Partial* d_partials = nullptr;    // [num_cus * kMaxBlocksPerCu + n_tensors], error statistics
   // speculative quantisation: tensor and chunk tables of the tensors that have to be cast again, their chunk
   // count, and running totals (calls, tensors cast twice, elements cast twice)
   TensorDesc* d_redo_desc = nullptr;
-  int32_t* d_redo_chunk_tensor = nullptr;
+  ChunkDesc* d_redo_chunks = nullptr;
   int32_t* d_redo_count = nullptr;
   unsigned long long* d_spec_totals = nullptr;
   // what the last fused cast measured for (checked by the Adam step that wants to use it)
@@ -138,77 +138,126 @@ struct DeviceGuard {
   ~DeviceGuard() { if (prev >= 0) (void)hipSetDevice(prev); }
 };
 
+void free_tables(fp8lm_ctx* c) {
+  for (void* p : {(void*)c->d_desc, (void*)c->d_chunks, (void*)c->d_epi_tensor, (void*)c->d_redo_desc,
+                  (void*)c->d_redo_chunks, (void*)c->d_records, (void*)c->d_totals})
+    if (p) (void)hipFree(p);
+}
+
 // Builds the tensor and chunk tables for chunks of chunk_elems elements and installs them.  On failure the
 // context keeps the tables (and the chunk size) it had.
 fp8lm_status build_tables(fp8lm_ctx* c, int32_t chunk_elems) {
   std::vector<TensorDesc> desc(c->n_tensors);
-  std::vector<int32_t> chunk_tensor;
   long long total_chunks = 0;
+  int32_t n_epi = 0;
   for (int t = 0; t < c->n_tensors; ++t) {
     const long long n = c->tensors[t].numel;
     const long long nc = (n + chunk_elems - 1) / chunk_elems;
     if (total_chunks + nc > 0x7FFFFFF0LL) return FP8LM_ERR_TOO_LARGE;
-    desc[t] = TensorDesc{c->tensors[t].offset, n, (int32_t)total_chunks, (int32_t)nc, c->tensor_flags[t], 0u};
+    desc[t] = TensorDesc{c->tensors[t].offset, n, (int32_t)total_chunks, (int32_t)nc, c->tensor_flags[t], n_epi};
+    if (nc > 0) n_epi += epilogue_groups((int32_t)nc);
     total_chunks += nc;
   }
-  chunk_tensor.resize((size_t)total_chunks);
-  for (int t = 0; t < c->n_tensors; ++t)
-    std::fill(chunk_tensor.begin() + desc[t].first_chunk, chunk_tensor.begin() + desc[t].first_chunk + desc[t].n_chunks, t);
+  // records: 32 bytes for each 4096 elements (units are not smaller than that), and a chunk can always be one unit
+  const size_t record_bytes = std::max<size_t>(1, (size_t)total_chunks) * std::max(64, chunk_elems / kTile * 32);
+  // everything in one list, so that a failure gives back what had been allocated
+  struct Piece { void** at; size_t bytes; const void* from; };
   TensorDesc* d_desc = nullptr;
   TensorDesc* d_redo_desc = nullptr;
-  int32_t* d_chunk_tensor = nullptr;
-  int32_t* d_redo_chunk_tensor = nullptr;
-  hipError_t e = hipMalloc((void**)&d_desc, std::max<size_t>(1, desc.size()) * sizeof(TensorDesc));
-  if (e == hipSuccess) e = hipMalloc((void**)&d_chunk_tensor, std::max<size_t>(1, chunk_tensor.size()) * sizeof(int32_t));
-  if (e == hipSuccess) e = hipMalloc((void**)&d_redo_desc, std::max<size_t>(1, desc.size()) * sizeof(TensorDesc));
-  if (e == hipSuccess) e = hipMalloc((void**)&d_redo_chunk_tensor, std::max<size_t>(1, chunk_tensor.size()) * sizeof(int32_t));
-  if (e == hipSuccess && !desc.empty())
-    e = hipMemcpy(d_desc, desc.data(), desc.size() * sizeof(TensorDesc), hipMemcpyHostToDevice);
-  if (e == hipSuccess && !chunk_tensor.empty())
-    e = hipMemcpy(d_chunk_tensor, chunk_tensor.data(), chunk_tensor.size() * sizeof(int32_t), hipMemcpyHostToDevice);
+  ChunkDesc* d_chunks = nullptr;
+  ChunkDesc* d_redo_chunks = nullptr;
+  int32_t* d_epi_tensor = nullptr;
+  unsigned char* d_records = nullptr;
+  unsigned long long* d_totals = nullptr;
+  const Piece pieces[] = {
+      {(void**)&d_desc, desc.size() * sizeof(TensorDesc), desc.data()},
+      {(void**)&d_chunks, (size_t)total_chunks * sizeof(ChunkDesc), nullptr},
+      {(void**)&d_epi_tensor, (size_t)n_epi * sizeof(int32_t), nullptr},
+      {(void**)&d_redo_desc, desc.size() * sizeof(TensorDesc), nullptr},
+      {(void**)&d_redo_chunks, (size_t)total_chunks * sizeof(ChunkDesc), nullptr},
+      {(void**)&d_records, record_bytes, nullptr},
+      {(void**)&d_totals, (size_t)n_epi * kTotalWords * sizeof(unsigned long long), nullptr},
+  };
+  hipError_t e = hipSuccess;
+  for (const Piece& q : pieces) {
+    if (e == hipSuccess) e = hipMalloc(q.at, std::max<size_t>(16, q.bytes));
+    if (e == hipSuccess && q.from && q.bytes) e = hipMemcpy(*q.at, q.from, q.bytes, hipMemcpyHostToDevice);
+  }
+  if (e == hipSuccess && total_chunks > 0) {     // the per-chunk tables are written on the device
+    hipLaunchKernelGGL(chunk_tables_kernel, dim3(std::min(c->n_tensors, 1024)), dim3(kThreads), 0, nullptr, d_desc, d_chunks,
+                       d_epi_tensor, c->d_scratch, chunk_elems, c->n_tensors);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+  }
   if (e != hipSuccess) {
     g_hip_error = std::string("chunk tables: ") + hipGetErrorString(e);
-    if (d_desc) (void)hipFree(d_desc);
-    if (d_chunk_tensor) (void)hipFree(d_chunk_tensor);
-    if (d_redo_desc) (void)hipFree(d_redo_desc);
-    if (d_redo_chunk_tensor) (void)hipFree(d_redo_chunk_tensor);
+    for (const Piece& q : pieces)
+      if (*q.at) (void)hipFree(*q.at);
     return FP8LM_ERR_HIP;
   }
-  if (c->d_desc) (void)hipFree(c->d_desc);
-  if (c->d_chunk_tensor) (void)hipFree(c->d_chunk_tensor);
-  if (c->d_redo_desc) (void)hipFree(c->d_redo_desc);
-  if (c->d_redo_chunk_tensor) (void)hipFree(c->d_redo_chunk_tensor);
+  free_tables(c);
   c->d_desc = d_desc;
-  c->d_chunk_tensor = d_chunk_tensor;
+  c->d_chunks = d_chunks;
+  c->d_epi_tensor = d_epi_tensor;
   c->d_redo_desc = d_redo_desc;
-  c->d_redo_chunk_tensor = d_redo_chunk_tensor;
+  c->d_redo_chunks = d_redo_chunks;
+  c->d_records = d_records;
+  c->d_totals = d_totals;
+  c->record_bytes = record_bytes;
+  c->n_epi = n_epi;
   c->chunk_elems = chunk_elems;
   c->n_chunks = (int32_t)total_chunks;
   return FP8LM_OK;
 }
 
-// Workgroups per launch: blocks_per_cu per compute unit, but never more than there are chunks.
+// Workgroups of a persistent launch: blocks_per_cu per compute unit, but never more than there are chunks.
 int grid_of(const fp8lm_ctx* c) {
   const long long full = (long long)c->num_cus * c->blocks_per_cu;
   return (int)std::max<long long>(1, std::min<long long>(full, c->n_chunks));
 }
 
-// The single-pass form of the cross-workgroup reduction costs every workgroup a ticket (about 20 ns that
-// do not overlap between workgroups); with few chunks per workgroup that is more than the data.  The
-// deferred form (a second, tiny launch) is used below single_pass_min_chunks chunks per workgroup.
-bool deferred_of(const fp8lm_ctx* c) {
-  return c->single_pass_min_chunks > 0 && c->n_chunks / grid_of(c) < c->single_pass_min_chunks;
-}
-
-Tables tables_of(const fp8lm_ctx* c) {
-  return Tables{c->d_desc, c->d_chunk_tensor, c->d_scratch, c->d_partials, c->n_chunks, c->chunk_elems,
-                deferred_of(c) ? 1 : 0, nullptr};
+// Tables of a launch whose workgroups take up to `un` tiles at once and leave records of `record` bytes, and its grid.
+// By default a workgroup per unit.  A unit is `un` tiles where that gives every compute unit four workgroups, otherwise
+// fewer (a small launch needs workgroups more than it needs loads in flight), and more where the record memory would not
+// do.  A persistent grid where the caller asked for a limit (fp8lm_set_tuning), or where there would be more workgroups than
+// a launch can have.
+constexpr long long kMaxGrid = 1ll << 23;          // x 256 threads stays below 2^32
+Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
+  Tables tb{};
+  tb.desc = c->d_desc;
+  tb.chunks = c->d_chunks;
+  tb.scratch = c->d_scratch;
+  tb.records = c->d_records;
+  tb.totals = c->d_totals;
+  tb.epi_tensor = c->d_epi_tensor;
+  tb.n_epi = c->n_epi;
+  tb.n_chunks = c->n_chunks;
+  tb.unit_elems = c->chunk_elems;
+  auto units = [&] { return (long long)c->n_chunks << tb.unit_shift; };
+  if (c->blocks_per_cu >= kMaxBlocksPerCu) {
+    while (tb.unit_elems % (2 * kTile) == 0 && (tb.unit_elems > un * kTile || units() < 4ll * c->num_cus) &&
+           (size_t)(2 * units() * record) <= c->record_bytes) {
+      tb.unit_elems /= 2;
+      ++tb.unit_shift;
+    }
+    tb.one_unit = units() <= kMaxGrid;
+  }
+  *grid = tb.one_unit ? (int)units() : grid_of(c);
+  // in the deferred form the second launch finishes the tensors; see walk.hpp for the two forms' costs
+  tb.deferred = c->single_pass_min_chunks > 0 && c->n_chunks / grid_of(c) < c->single_pass_min_chunks;
+  return tb;
 }
 // The tables of the tensors a speculative quantisation has to cast again: built on the device, so the number of
-// chunks is only known there; tensors always finished by the second launch.
-Tables redo_tables_of(const fp8lm_ctx* c) {
-  return Tables{c->d_redo_desc, c->d_redo_chunk_tensor, c->d_scratch, c->d_partials, c->n_chunks, c->chunk_elems, 1,
-                c->d_redo_count};
+// chunks is only known there; a persistent grid, tensors always finished by the second launch.
+Tables redo_tables_of(const fp8lm_ctx* c, int record, int* grid) {
+  Tables tb = tables_of(c, 1, record, grid);
+  tb.desc = c->d_redo_desc;
+  tb.chunks = c->d_redo_chunks;
+  tb.n_chunks_dev = c->d_redo_count;
+  tb.one_unit = 0;
+  tb.deferred = 1;
+  *grid = (int)std::min<long long>((long long)c->num_cus * 8, (long long)c->n_chunks << tb.unit_shift);
+  return tb;
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -241,23 +290,20 @@ fp8lm_status after_launch() {
   return FP8LM_OK;
 }
 
-// Launches a chunk-walking kernel and, in the deferred form, the launch that finishes its tensors.
+// Launches a kernel that walks the units and, in the deferred form, the launch that finishes its tensors.
+template <class Stats> struct RecordOf;
+template <int NV, int NC> struct RecordOf<BlockStats<NV, NC>> { static constexpr int bytes = kRecordBytes<NC>; };
 template <class Op, class Params, class Kernel>
-void launch_walk_on(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, const Tables& tb) {
-  const dim3 g(grid_of(c)), b(kThreads);
-  hipLaunchKernelGGL(kernel, g, b, 0, s, tb, p);
-  if (tb.deferred)
-    hipLaunchKernelGGL((epilogue_kernel<Op, Params>), dim3(std::min<int>(c->n_tensors, 8 * c->num_cus)), b, 0, s, tb, p,
-                       (int)g.x, (int)c->n_tensors);
+void launch_walk_on(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, const Tables& tb, int grid) {
+  const dim3 b(kThreads);
+  hipLaunchKernelGGL(kernel, dim3(grid), b, 0, s, tb, p);
+  if (tb.deferred) hipLaunchKernelGGL((epilogue_kernel<Op, Params>), dim3(std::min<int>(c->n_epi, 8 * c->num_cus)), b, 0, s, tb, p);
 }
 template <class Op, class Params, class Kernel>
-void launch_walk(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p) {
-  const Tables tb = tables_of(c);
-  const dim3 g(grid_of(c)), b(kThreads);
-  hipLaunchKernelGGL(kernel, g, b, 0, s, tb, p);
-  if (tb.deferred)
-    hipLaunchKernelGGL((epilogue_kernel<Op, Params>), dim3(std::min<int>(c->n_tensors, 8 * c->num_cus)), b, 0, s, tb, p,
-                       (int)g.x, (int)c->n_tensors);
+void launch_walk(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, int un = 1) {
+  int grid = 0;
+  const Tables tb = tables_of(c, un, RecordOf<typename Op::Stats>::bytes, &grid);
+  launch_walk_on<Op>(c, s, kernel, p, tb, grid);
 }
 
 // Selects the adam_update_kernel instantiation.
@@ -354,11 +400,12 @@ fp8lm_status fp8lm_create(fp8lm_ctx** out, const fp8lm_tensor* tensors, int32_t 
   c->num_cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
   c->tensors.assign(tensors, tensors + n);
   c->tensor_flags.assign((size_t)n, 0u);
-  fp8lm_status st = build_tables(c, c->chunk_elems);
+  const size_t bytes = std::max<size_t>(1, (size_t)n) * sizeof(Scratch);
+  hipError_t e = hipMalloc((void**)&c->d_scratch, bytes);
+  if (e == hipSuccess) e = hipMemset(c->d_scratch, 0, bytes);
+  if (e != hipSuccess) g_hip_error = hipGetErrorString(e);
+  fp8lm_status st = e == hipSuccess ? build_tables(c, c->chunk_elems) : FP8LM_ERR_HIP;
   if (st == FP8LM_OK) {
-    const size_t bytes = std::max<size_t>(1, (size_t)n) * sizeof(Scratch);
-    hipError_t e = hipMalloc((void**)&c->d_scratch, bytes);
-    if (e == hipSuccess) e = hipMemset(c->d_scratch, 0, bytes);
     const size_t records = (size_t)c->num_cus * kMaxBlocksPerCu + (size_t)n + 1;
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_partials, records * sizeof(Partial));
     if (e == hipSuccess) e = hipMemset(c->d_partials, 0, records * sizeof(Partial));
@@ -377,12 +424,9 @@ fp8lm_status fp8lm_create(fp8lm_ctx** out, const fp8lm_tensor* tensors, int32_t 
 fp8lm_status fp8lm_destroy(fp8lm_ctx* c) {
   if (!c) return FP8LM_OK;
   DeviceGuard guard(c->device);
-  if (c->d_desc) (void)hipFree(c->d_desc);
-  if (c->d_chunk_tensor) (void)hipFree(c->d_chunk_tensor);
+  free_tables(c);
   if (c->d_scratch) (void)hipFree(c->d_scratch);
   if (c->d_partials) (void)hipFree(c->d_partials);
-  if (c->d_redo_desc) (void)hipFree(c->d_redo_desc);
-  if (c->d_redo_chunk_tensor) (void)hipFree(c->d_redo_chunk_tensor);
   if (c->d_redo_count) (void)hipFree(c->d_redo_count);
   if (c->d_spec_totals) (void)hipFree(c->d_spec_totals);
   for (auto& s : c->stamps) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
@@ -438,9 +482,9 @@ fp8lm_status fp8lm_amax_scale(fp8lm_ctx* c, const void* src, fp8lm_src src_type,
   AmaxParams p{src, meta, target == FP8LM_E4M3 ? kBitsE4M3Max : kBitsE5M2Max, cfg->hist_window, cfg->margin};
   hipStream_t s = (hipStream_t)stream;
   Timed tm(c, s, FP8LM_K_AMAX);
-  if (src_type == FP8LM_SRC_F32) launch_walk<AmaxOp<kAmaxForGradient, kSrcF32>>(c, s, amax_kernel<kAmaxForGradient, kSrcF32>, p);
-  else if (src_type == FP8LM_SRC_F16) launch_walk<AmaxOp<kAmaxForGradient, kSrcF16>>(c, s, amax_kernel<kAmaxForGradient, kSrcF16>, p);
-  else launch_walk<AmaxOp<kAmaxForGradient, kSrcBF16>>(c, s, amax_kernel<kAmaxForGradient, kSrcBF16>, p);
+  if (src_type == FP8LM_SRC_F32) launch_walk<AmaxOp<kAmaxForGradient, kSrcF32>>(c, s, amax_kernel<kAmaxForGradient, kSrcF32>, p, kUnRead);
+  else if (src_type == FP8LM_SRC_F16) launch_walk<AmaxOp<kAmaxForGradient, kSrcF16>>(c, s, amax_kernel<kAmaxForGradient, kSrcF16>, p, kUnRead);
+  else launch_walk<AmaxOp<kAmaxForGradient, kSrcBF16>>(c, s, amax_kernel<kAmaxForGradient, kSrcBF16>, p, kUnRead);
   return after_launch();
 }
 
@@ -489,10 +533,10 @@ static fp8lm_status cast_impl(fp8lm_ctx* c, const void* src, fp8lm_src src_type,
     Timed tm(c, s, FP8LM_K_CAST);
 #define FP8LM_CAST_LAUNCH(F, S)                                                                           \
     do {                                                                                                    \
-      if (delayed && fuse) launch_walk<CastOp<F, true, true, S>>(c, s, cast_kernel<F, true, true, S>, p);          \
-      else if (delayed) launch_walk<CastOp<F, true, false, S>>(c, s, cast_kernel<F, true, false, S>, p);            \
-      else if (fuse) launch_walk<CastOp<F, false, true, S>>(c, s, cast_kernel<F, false, true, S>, p);               \
-      else launch_walk<CastOp<F, false, false, S>>(c, s, cast_kernel<F, false, false, S>, p);                        \
+      if (delayed && fuse) launch_walk<CastOp<F, true, true, S>>(c, s, cast_kernel<F, true, true, S>, p, kUnCast<S>);          \
+      else if (delayed) launch_walk<CastOp<F, true, false, S>>(c, s, cast_kernel<F, true, false, S>, p, kUnCast<S>);            \
+      else if (fuse) launch_walk<CastOp<F, false, true, S>>(c, s, cast_kernel<F, false, true, S>, p, kUnCast<S>);               \
+      else launch_walk<CastOp<F, false, false, S>>(c, s, cast_kernel<F, false, false, S>, p, kUnCast<S>);                        \
     } while (0)
 #define FP8LM_CAST_SRC(S)                                                                                   \
     do {                                                                                                    \
@@ -512,18 +556,19 @@ static fp8lm_status cast_impl(fp8lm_ctx* c, const void* src, fp8lm_src src_type,
       Timed tm(c, s, FP8LM_K_SCALARS);
       hipLaunchKernelGGL(redo_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, c->d_desc, c->d_scratch, c->d_redo_desc,
                          c->n_tensors, c->d_redo_count, c->d_spec_totals);
-      hipLaunchKernelGGL(redo_fill_kernel, dim3(std::min<int>(c->n_tensors, 1024)), dim3(256), 0, s, c->d_redo_desc,
-                         c->d_redo_chunk_tensor, c->n_tensors);
+      hipLaunchKernelGGL(redo_fill_kernel, dim3(std::min<int>(c->n_tensors, 1024)), dim3(256), 0, s, c->d_desc,
+                         c->d_redo_desc, c->d_chunks, c->d_redo_chunks, c->n_tensors);
       st = after_launch();
     }
     if (st == FP8LM_OK) {
-      const Tables rt = redo_tables_of(c);
+      int redo_grid = 0;
+      const Tables rt = redo_tables_of(c, 32, &redo_grid);
       p.speculative = 0;
       Timed tm(c, s, FP8LM_K_CAST);
 #define FP8LM_REDO_LAUNCH(F, S)                                                                            \
       do {                                                                                                  \
-        if (fuse) launch_walk_on<CastOp<F, false, true, S>>(c, s, cast_kernel<F, false, true, S>, p, rt);   \
-        else launch_walk_on<CastOp<F, false, false, S>>(c, s, cast_kernel<F, false, false, S>, p, rt);      \
+        if (fuse) launch_walk_on<CastOp<F, false, true, S>>(c, s, cast_kernel<F, false, true, S>, p, rt, redo_grid);   \
+        else launch_walk_on<CastOp<F, false, false, S>>(c, s, cast_kernel<F, false, false, S>, p, rt, redo_grid);      \
       } while (0)
 #define FP8LM_REDO_SRC(S)                                                                                  \
       do {                                                                                                  \
@@ -609,9 +654,9 @@ fp8lm_status fp8lm_requantize_fp8(fp8lm_ctx* c, const uint8_t* src, fp8lm_fmt fm
   RequantParams p{src, src_meta, shared, dst, dst_meta};
   Timed tm(c, (hipStream_t)stream, FP8LM_K_REQUANT);
   if (fmt == FP8LM_E4M3)
-    launch_walk<RequantOp<kE4M3>>(c, (hipStream_t)stream, requantize_kernel<kE4M3>, p);
+    launch_walk<RequantOp<kE4M3>>(c, (hipStream_t)stream, requantize_kernel<kE4M3>, p, kUnRequant);
   else
-    launch_walk<RequantOp<kE5M2>>(c, (hipStream_t)stream, requantize_kernel<kE5M2>, p);
+    launch_walk<RequantOp<kE5M2>>(c, (hipStream_t)stream, requantize_kernel<kE5M2>, p, kUnRequant);
   return after_launch();
 }
 
@@ -637,8 +682,8 @@ fp8lm_status fp8lm_sum_fp8(fp8lm_ctx* c, const uint8_t* const* payloads, int32_t
   hipStream_t s = (hipStream_t)stream;
 #define FP8LM_SUM_N(N)                                                                          \
   case N:                                                                                       \
-    if (fmt == FP8LM_E4M3) launch_walk<SumOp<kE4M3, N>>(c, s, sum_fp8_kernel<kE4M3, N>, p);   \
-    else launch_walk<SumOp<kE5M2, N>>(c, s, sum_fp8_kernel<kE5M2, N>, p);                     \
+    if (fmt == FP8LM_E4M3) launch_walk<SumOp<kE4M3, N>>(c, s, sum_fp8_kernel<kE4M3, N>, p, sum_tiles(N));   \
+    else launch_walk<SumOp<kE5M2, N>>(c, s, sum_fp8_kernel<kE5M2, N>, p, sum_tiles(N));                    \
     break
   static_assert(kUnrolledRanks == 8, "one case per unrolled rank count");
   switch (n_ranks) {
@@ -693,7 +738,7 @@ fp8lm_status fp8lm_init_master_as(fp8lm_ctx* c, const void* w_bf16, void* w_out,
   Timed tm(c, s, FP8LM_K_INIT_MASTER);
   const uint32_t fmax_bits = master_fmt == FP8LM_STATE_F16 ? kBitsF16Max : (master_fmt == FP8LM_STATE_E4M3 ? kBitsE4M3Max : 0u);
   AmaxParams pa{static_cast<const uint16_t*>(w_bf16), w_meta, fmax_bits, 1, 0};
-  launch_walk<AmaxOp<kAmaxForMaster, kSrcBF16>>(c, s, amax_kernel<kAmaxForMaster, kSrcBF16>, pa);
+  launch_walk<AmaxOp<kAmaxForMaster, kSrcBF16>>(c, s, amax_kernel<kAmaxForMaster, kSrcBF16>, pa, kUnRead);
   fp8lm_status st = after_launch();
   if (st != FP8LM_OK) return st;
   InitParams pi{static_cast<const uint16_t*>(w_bf16), w_out, w_meta};
@@ -782,7 +827,8 @@ static fp8lm_status adam_launch(fp8lm_ctx* c, const uint8_t* grad, fp8lm_fmt gra
   p.speculative_m = spec_m ? 1 : 0;
 
   const bool stats = hp->stats != 0, fast = hp->exact == 0;
-  const Tables tb = tables_of(c);
+  int grid = 0;
+  const Tables tb = tables_of(c, 1, 16, &grid);      // for the per-tensor kernels, which only need the tables
   const bool e5 = grad_fmt == FP8LM_E5M2, q8 = hp->wcopy == FP8LM_WCOPY_E4M3;
   if (spec_m) {
     Timed tm(c, s, FP8LM_K_SCALARS);
@@ -805,10 +851,10 @@ static fp8lm_status adam_launch(fp8lm_ctx* c, const uint8_t* grad, fp8lm_fmt gra
     else hipLaunchKernelGGL((adam_predict_scales_kernel<FP8LM_WCOPY_BF16>), gs, bs, 0, s, tb, p, c->n_tensors);
   } else {
     Timed tm(c, s, FP8LM_K_ADAM_AMAX);
-    if (e5 && q8) launch_walk<AdamAmaxOp<kE5M2, FP8LM_WCOPY_E4M3>>(c, s, adam_amax_kernel<kE5M2, FP8LM_WCOPY_E4M3>, p);
-    else if (e5) launch_walk<AdamAmaxOp<kE5M2, FP8LM_WCOPY_BF16>>(c, s, adam_amax_kernel<kE5M2, FP8LM_WCOPY_BF16>, p);
-    else if (q8) launch_walk<AdamAmaxOp<kE4M3, FP8LM_WCOPY_E4M3>>(c, s, adam_amax_kernel<kE4M3, FP8LM_WCOPY_E4M3>, p);
-    else launch_walk<AdamAmaxOp<kE4M3, FP8LM_WCOPY_BF16>>(c, s, adam_amax_kernel<kE4M3, FP8LM_WCOPY_BF16>, p);
+    if (e5 && q8) launch_walk<AdamAmaxOp<kE5M2, FP8LM_WCOPY_E4M3>>(c, s, adam_amax_kernel<kE5M2, FP8LM_WCOPY_E4M3>, p, kUnRead);
+    else if (e5) launch_walk<AdamAmaxOp<kE5M2, FP8LM_WCOPY_BF16>>(c, s, adam_amax_kernel<kE5M2, FP8LM_WCOPY_BF16>, p, kUnRead);
+    else if (q8) launch_walk<AdamAmaxOp<kE4M3, FP8LM_WCOPY_E4M3>>(c, s, adam_amax_kernel<kE4M3, FP8LM_WCOPY_E4M3>, p, kUnRead);
+    else launch_walk<AdamAmaxOp<kE4M3, FP8LM_WCOPY_BF16>>(c, s, adam_amax_kernel<kE4M3, FP8LM_WCOPY_BF16>, p, kUnRead);
   }
   fp8lm_status st = after_launch();
   if (st != FP8LM_OK) return st;
@@ -829,14 +875,15 @@ static fp8lm_status adam_launch(fp8lm_ctx* c, const uint8_t* grad, fp8lm_fmt gra
     Timed tm(c, s, FP8LM_K_SCALARS);
     hipLaunchKernelGGL(redo_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, c->d_desc, c->d_scratch, c->d_redo_desc,
                        c->n_tensors, c->d_redo_count, c->d_spec_totals + 3);
-    hipLaunchKernelGGL(redo_fill_kernel, dim3(std::min<int>(c->n_tensors, 1024)), dim3(256), 0, s, c->d_redo_desc,
-                       c->d_redo_chunk_tensor, c->n_tensors);
+    hipLaunchKernelGGL(redo_fill_kernel, dim3(std::min<int>(c->n_tensors, 1024)), dim3(256), 0, s, c->d_desc,
+                       c->d_redo_desc, c->d_chunks, c->d_redo_chunks, c->n_tensors);
     st = after_launch();
     if (st != FP8LM_OK) return st;
   }
   {
-    const Tables rt = redo_tables_of(c);
-    const dim3 g(grid_of(c)), b(kThreads);
+    int redo_grid = 0;
+    const Tables rt = redo_tables_of(c, 16, &redo_grid);
+    const dim3 g(redo_grid), b(kThreads);
     Timed tm(c, s, FP8LM_K_ADAM_AMAX);
     if (e5) hipLaunchKernelGGL((adam_moment_redo_kernel<kE5M2>), g, b, 0, s, rt, p);
     else hipLaunchKernelGGL((adam_moment_redo_kernel<kE4M3>), g, b, 0, s, rt, p);
@@ -955,20 +1002,30 @@ fp8lm_status fp8lm_adam_step_fp8_static(int device, const fp8lm_tensor* tensors,
 
   // 1. the tensor table, a batch of descriptors per launch, then the chunk table
   DescBatch batch;
-  int32_t first_chunk = 0;
+  int32_t first_chunk = 0, first_epi = 0;
+  // chunks of 16384 elements or, where the units of a launch would be too many for the records, larger ones
+  int32_t chunk_elems = kStaticChunkElems;
+  auto chunks_of = [&](int64_t numel) { return (numel + chunk_elems - 1) / chunk_elems; };
+  for (;; chunk_elems *= 2) {
+    total_chunks = 0;
+    for (int t = 0; t < n; ++t) total_chunks += chunks_of(tensors[t].numel);
+    if (total_chunks <= kStaticChunks) break;
+  }
   for (int t0 = 0; t0 < n; t0 += kDescBatch) {
     batch.first = t0;
     batch.count = std::min(kDescBatch, n - t0);
     for (int i = 0; i < batch.count; ++i) {
       const fp8lm_tensor& T = tensors[t0 + i];
-      const int32_t nc = (int32_t)((T.numel + kStaticChunkElems - 1) / kStaticChunkElems);
-      batch.d[i] = TensorDesc{T.offset, T.numel, first_chunk, nc, tensor_flags ? tensor_flags[t0 + i] : 0u, 0u};
+      const int32_t nc = (int32_t)chunks_of(T.numel);
+      batch.d[i] = TensorDesc{T.offset, T.numel, first_chunk, nc, tensor_flags ? tensor_flags[t0 + i] : 0u, first_epi};
       first_chunk += nc;
+      if (nc > 0) first_epi += epilogue_groups(nc);
     }
-    for (int i = batch.count; i < kDescBatch; ++i) batch.d[i] = TensorDesc{0, 0, 0, 0, 0u, 0u};
+    for (int i = batch.count; i < kDescBatch; ++i) batch.d[i] = TensorDesc{0, 0, 0, 0, 0u, 0};
     hipLaunchKernelGGL(static_desc_kernel, dim3(1), dim3(kDescBatch), 0, s, batch, A->desc);
   }
-  hipLaunchKernelGGL(static_chunks_kernel, dim3(std::min(n, 1024)), dim3(256), 0, s, A->desc, A->chunk_tensor, A->scratch, n);
+  hipLaunchKernelGGL(chunk_tables_kernel, dim3(std::min(n, 1024)), dim3(kThreads), 0, s, A->desc, A->chunks, A->epi_tensor, A->scratch,
+                     chunk_elems, n);
   fp8lm_status st = after_launch();
   if (st != FP8LM_OK) return st;
 
@@ -977,15 +1034,17 @@ fp8lm_status fp8lm_adam_step_fp8_static(int device, const fp8lm_tensor* tensors,
   view.device = device;
   view.n_tensors = n;
   view.num_cus = dev.num_cus;
-  view.chunk_elems = kStaticChunkElems;
-  view.blocks_per_cu = std::max(1, std::min<int>(kMaxBlocksPerCu, kStaticMaxGrid / dev.num_cus));   // grid <= kStaticMaxGrid records
-  if ((long long)view.num_cus * view.blocks_per_cu > kStaticMaxGrid) return FP8LM_ERR_TOO_LARGE;
+  view.chunk_elems = chunk_elems;
   view.single_pass_min_chunks = 1 << 30;     // per-tensor totals in a second launch: no tickets to keep at zero
   view.n_chunks = (int32_t)total_chunks;
   view.d_desc = A->desc;
-  view.d_chunk_tensor = A->chunk_tensor;
+  view.d_chunks = A->chunks;
   view.d_scratch = A->scratch;
-  view.d_partials = A->partials;
+  view.d_records = A->records;
+  view.record_bytes = sizeof(A->records);
+  view.d_totals = A->totals;
+  view.d_epi_tensor = A->epi_tensor;
+  view.n_epi = first_epi;
   return adam_launch(&view, grad, grad_fmt, grad_meta, m, m_meta, v, v_meta, w, w_meta, wcopy, wcopy_meta, hp, s);
 }
 
@@ -997,25 +1056,32 @@ fp8lm_status fp8lm_quant_error_stats(fp8lm_ctx* c, const void* ref, fp8lm_src re
   if (c->n_chunks > 0 && (!aligned16(ref) || !aligned16(q))) return FP8LM_ERR_MISALIGNED;
   DeviceGuard guard(c->device);
   hipStream_t s = (hipStream_t)stream;
-  {
-    // entries of empty tensors are never written by the reduction: start from zero
+  if (c->n_chunks == 0) {                        // only empty tensors
     Timed tm(c, s, FP8LM_K_SCALARS);
     hipLaunchKernelGGL(quant_stats_zero_kernel, dim3((c->n_tensors + 255) / 256), dim3(256), 0, s, out, c->n_tensors);
-    fp8lm_status st = after_launch();
-    if (st != FP8LM_OK) return st;
+    return after_launch();
   }
-  if (c->n_chunks == 0) return FP8LM_OK;
-  StatsParams p{ref, q, q_meta, out};
+  StatsParams p{ref, q, q_meta, out, c->d_partials};
+  int grid = 0;
+  const Tables tb = tables_of(c, 1, 16, &grid);
+  grid = grid_of(c);
+  const dim3 ge(std::min<int>(c->n_tensors, 8 * c->num_cus));
   Timed tm(c, s, FP8LM_K_STATS);
+#define FP8LM_STATS_LAUNCH(F, S)                                                                             \
+  do {                                                                                                       \
+    hipLaunchKernelGGL((quant_stats_kernel<F, S>), dim3(grid), dim3(kThreads), 0, s, tb, p);                 \
+    hipLaunchKernelGGL((quant_stats_epilogue_kernel<F, S>), ge, dim3(kThreads), 0, s, tb, p, grid, c->n_tensors); \
+  } while (0)
 #define FP8LM_STATS_SRC(S)                                                                                   \
   do {                                                                                                       \
-    if (fmt == FP8LM_E4M3) launch_walk<QuantStatsOp<kE4M3, S>>(c, s, quant_stats_kernel<kE4M3, S>, p);        \
-    else launch_walk<QuantStatsOp<kE5M2, S>>(c, s, quant_stats_kernel<kE5M2, S>, p);                          \
+    if (fmt == FP8LM_E4M3) FP8LM_STATS_LAUNCH(kE4M3, S);                                                     \
+    else FP8LM_STATS_LAUNCH(kE5M2, S);                                                                       \
   } while (0)
   if (ref_type == FP8LM_SRC_F32) FP8LM_STATS_SRC(kSrcF32);
   else if (ref_type == FP8LM_SRC_F16) FP8LM_STATS_SRC(kSrcF16);
   else FP8LM_STATS_SRC(kSrcBF16);
 #undef FP8LM_STATS_SRC
+#undef FP8LM_STATS_LAUNCH
   return after_launch();
 }
 
@@ -1057,8 +1123,8 @@ fp8lm_status fp8lm_copy_bytes(fp8lm_ctx* c, const void* src, void* dst, int64_t 
 }
 
 fp8lm_status fp8lm_memory_skeleton(fp8lm_ctx* c, int32_t shape, void* const* bufs, int64_t n_elems, void* stream) {
-  static const int n_bufs[] = {1, 2, 1, 1, 2, 5, 5, 5};
-  if (!c || shape < 0 || shape > FP8LM_SKEL_UPDATE_WRITES || !bufs || n_elems < 0 || n_elems % kTile != 0)
+  static const int n_bufs[] = {1, 2, 1, 1, 2, 5, 5, 5, 5};
+  if (!c || shape < 0 || shape > FP8LM_SKEL_UPDATE_RANGES || !bufs || n_elems < 0 || n_elems % kTile != 0)
     return FP8LM_ERR_INVALID_ARGUMENT;
   for (int i = 0; i < n_bufs[shape]; ++i) {
     if (!bufs[i]) return FP8LM_ERR_INVALID_ARGUMENT;
@@ -1068,40 +1134,42 @@ fp8lm_status fp8lm_memory_skeleton(fp8lm_ctx* c, int32_t shape, void* const* buf
   DeviceGuard guard(c->device);
   SkeletonParams p{};
   p.n_tiles = n_elems / kTile;
-  p.sink = reinterpret_cast<uint32_t*>(c->d_partials);     // kWaves words per workgroup: far inside the record array
-  const long long want = (long long)c->num_cus * c->blocks_per_cu;
-  const dim3 g((unsigned)std::max<long long>(1, std::min<long long>(want, p.n_tiles))), b(kThreads);
+  p.sink = reinterpret_cast<uint32_t*>(c->d_partials);
+  const dim3 b(kThreads);
+  auto grid = [&](int un) { return dim3((unsigned)std::min(kMaxGrid, (p.n_tiles + un - 1) / un)); };
   hipStream_t s = (hipStream_t)stream;
   Timed tm(c, s, FP8LM_K_SKELETON);
   switch (shape) {
     case FP8LM_SKEL_READ16:
       p.s2[0] = static_cast<const uint16_t*>(bufs[0]);
-      hipLaunchKernelGGL((skeleton_kernel<0, 1, 0, 0, FP8LM_UN_READ>), g, b, 0, s, p);
+      hipLaunchKernelGGL((skeleton_kernel<0, 1, 0, 0, kUnRead>), grid(kUnRead), b, 0, s, p);
       break;
     case FP8LM_SKEL_READ8X2:
       p.s1[0] = static_cast<const uint8_t*>(bufs[0]); p.s1[1] = static_cast<const uint8_t*>(bufs[1]);
-      hipLaunchKernelGGL((skeleton_kernel<2, 0, 0, 0, FP8LM_UN_READ>), g, b, 0, s, p);
+      hipLaunchKernelGGL((skeleton_kernel<2, 0, 0, 0, kUnRead>), grid(kUnRead), b, 0, s, p);
       break;
     case FP8LM_SKEL_WRITE16:
       p.d2[0] = static_cast<uint16_t*>(bufs[0]);
-      hipLaunchKernelGGL((skeleton_kernel<0, 0, 0, 1, 1>), g, b, 0, s, p);
+      hipLaunchKernelGGL((skeleton_kernel<0, 0, 0, 1, 1>), grid(1), b, 0, s, p);
       break;
     case FP8LM_SKEL_WRITE8:
       p.d1[0] = static_cast<uint8_t*>(bufs[0]);
-      hipLaunchKernelGGL((skeleton_kernel<0, 0, 1, 0, 1>), g, b, 0, s, p);
+      hipLaunchKernelGGL((skeleton_kernel<0, 0, 1, 0, 1>), grid(1), b, 0, s, p);
       break;
     case FP8LM_SKEL_CAST:
       p.s2[0] = static_cast<const uint16_t*>(bufs[0]); p.d1[0] = static_cast<uint8_t*>(bufs[1]);
-      hipLaunchKernelGGL((skeleton_kernel<0, 1, 1, 0, FP8LM_UN_CAST>), g, b, 0, s, p);
+      hipLaunchKernelGGL((skeleton_kernel<0, 1, 1, 0, kUnCast<kSrcBF16>>), grid(kUnCast<kSrcBF16>), b, 0, s, p);
       break;
     default:   // the update shapes: reads g, m, v, w; writes m, v, w in place and the weight copy; or one half of that
       p.s1[0] = static_cast<const uint8_t*>(bufs[0]); p.s1[1] = static_cast<const uint8_t*>(bufs[1]);
       p.s2[0] = static_cast<const uint16_t*>(bufs[2]); p.s2[1] = static_cast<const uint16_t*>(bufs[3]);
       p.d1[0] = static_cast<uint8_t*>(bufs[1]); p.d1[1] = static_cast<uint8_t*>(bufs[4]);
       p.d2[0] = static_cast<uint16_t*>(bufs[2]); p.d2[1] = static_cast<uint16_t*>(bufs[3]);
-      if (shape == FP8LM_SKEL_UPDATE) hipLaunchKernelGGL((skeleton_kernel<2, 2, 2, 2, FP8LM_UN_UPDATE>), g, b, 0, s, p);
-      else if (shape == FP8LM_SKEL_UPDATE_READS) hipLaunchKernelGGL((skeleton_kernel<2, 2, 0, 0, FP8LM_UN_UPDATE>), g, b, 0, s, p);
-      else hipLaunchKernelGGL((skeleton_kernel<0, 0, 2, 2, FP8LM_UN_UPDATE>), g, b, 0, s, p);
+      if (shape == FP8LM_SKEL_UPDATE) hipLaunchKernelGGL((skeleton_kernel<2, 2, 2, 2, kUnUpdate>), grid(kUnUpdate), b, 0, s, p);
+      else if (shape == FP8LM_SKEL_UPDATE_READS) hipLaunchKernelGGL((skeleton_kernel<2, 2, 0, 0, kUnUpdate>), grid(kUnUpdate), b, 0, s, p);
+      else if (shape == FP8LM_SKEL_UPDATE_WRITES) hipLaunchKernelGGL((skeleton_kernel<0, 0, 2, 2, kUnUpdate>), grid(kUnUpdate), b, 0, s, p);
+      else hipLaunchKernelGGL((skeleton_kernel<2, 2, 2, 2, 1, true>),
+                              dim3((unsigned)std::min<long long>((long long)c->num_cus * kMaxBlocksPerCu, p.n_tiles)), b, 0, s, p);
       break;
   }
   return after_launch();

@@ -94,24 +94,26 @@ struct AmaxOp {
   const Tables& tb;
   uint32_t acc;   // running maximum of the magnitude bits (two packed maxima for 16-bit sources)
   __device__ AmaxOp(const AmaxParams& p_, const Tables& tb_) : p(p_), tb(tb_), acc(0) {}
-  __device__ __forceinline__ void begin(int, const TensorDesc&) { acc = 0; }
+  __device__ __forceinline__ void begin(int) { acc = 0; }
   __device__ __forceinline__ bool fast() const { return true; }
-  template <int UN> __device__ __forceinline__ void tiles(long long pos) {
-    // a pure reduction: each load instruction of a wavefront covers 1 KiB contiguous
-    uint4 r[UN][kLoads];
+  template <int UN> struct Regs { uint4 r[UN][kLoads]; };
+  // a pure reduction: each load instruction of a wavefront covers 1 KiB contiguous
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& g, long long pos) {
     const elem_t* q = static_cast<const elem_t*>(p.src) + pos + threadIdx.x * kPer;
 #pragma unroll
     for (int u = 0; u < UN; ++u)
 #pragma unroll
-      for (int k = 0; k < kLoads; ++k) r[u][k] = ld16<kNtLoadRO>(q + u * kTile + k * (kThreads * kPer));
+      for (int k = 0; k < kLoads; ++k) g.r[u][k] = ld16<kNtLoadRO>(q + u * kTile + k * (kThreads * kPer));
+  }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& g, long long) {
 #pragma unroll
     for (int u = 0; u < UN; ++u)
 #pragma unroll
       for (int k = 0; k < kLoads; ++k) {
-        src_fold<SRC>(acc, r[u][k].x);
-        src_fold<SRC>(acc, r[u][k].y);
-        src_fold<SRC>(acc, r[u][k].z);
-        src_fold<SRC>(acc, r[u][k].w);
+        src_fold<SRC>(acc, g.r[u][k].x);
+        src_fold<SRC>(acc, g.r[u][k].y);
+        src_fold<SRC>(acc, g.r[u][k].z);
+        src_fold<SRC>(acc, g.r[u][k].w);
       }
   }
   // 16 consecutive elements at `pos`, by this thread alone
@@ -133,12 +135,11 @@ struct AmaxOp {
     for (int j = 0; j < valid; ++j) src_fold1<SRC>(acc, q[j]);
   }
   using Stats = BlockStats<1, 0>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
+  __device__ __forceinline__ void flush(int t, long long u) {
+    BlockStats<1, 0, uint32_t> s;
     s.mx[0] = src_final<SRC>(acc);
     s.orv = 0;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+    collect(tb, *this, t, u, s);
   }
   // scalar epilogue, one thread per tensor
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
@@ -179,7 +180,7 @@ struct AmaxOp {
 template <int MODE, int SRC>
 __global__ __launch_bounds__(kThreads) void amax_kernel(Tables tb, AmaxParams p) {
   AmaxOp<MODE, SRC> op(p, tb);
-  walk_chunks<FP8LM_UN_READ>(tb, op);
+  walk_units<kUnRead>(tb, op);
 }
 
 // ================================================================================================
@@ -257,12 +258,12 @@ struct CastOp {
   uint32_t z_in;          // inputs that are +-0
   __device__ CastOp(const CastParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
   __device__ __forceinline__ void reset() { vmax = 0.0f; n_elems = nz_top = nz_code = z_in = 0; amax16 = 0; macc = 0; }
-  __device__ __forceinline__ void begin(int t, const TensorDesc&) {
-    scale = p.meta[t].scale;
-    careful = !DELAYED && (p.meta[t].flags & FP8LM_FLAG_NONFINITE) != 0;
+  __device__ __forceinline__ void begin(int t) {
+    scale = uniform_load(&p.meta[t].scale);
+    careful = !DELAYED && (uniform_load(&p.meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0;
     if constexpr (FUSE) {
-      inv_sg = p.meta[t].inv_scale;
-      inv_sm = p.m_meta[t].inv_scale;
+      inv_sg = uniform_load(&p.meta[t].inv_scale);
+      inv_sm = uniform_load(&p.m_meta[t].inv_scale);
     }
     reset();
   }
@@ -334,97 +335,96 @@ struct CastOp {
     return c;
   }
   __device__ __forceinline__ bool fast() const { return !careful; }
-  template <int UN> __device__ __forceinline__ void tiles(long long pos0) { tiles_as<UN, FP8LM_CAST_SPLIT && kSrc16<SRC>>(pos0); }
   // kSplit: the thread's 16 elements are [8L, 8L+8) of each half of the tile (every 128-bit load contiguous
   // over the workgroup, 64-bit stores); otherwise 16 consecutive elements.
-  template <int UN, bool kSplit> __device__ __forceinline__ void tiles_as(long long pos0) {
-    uint4 r[UN][kLoads], mm[UN];
+  template <int UN> struct Regs { uint4 r[UN][kLoads], mm[FUSE ? UN : 1]; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& g, long long pos0) { load_as<kSrc16<SRC>>(g, pos0); }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& g, long long pos0) { tiles_as<kSrc16<SRC>>(g, pos0); }
+  template <bool kSplit, int UN> __device__ __forceinline__ void load_as(Regs<UN>& g, long long pos0) {
     const long long pos = pos0 + threadIdx.x * (kSplit ? 8 : kGroup);
     const elem_t* q = static_cast<const elem_t*>(p.src) + pos;
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
 #pragma unroll
-      for (int k = 0; k < kLoads; ++k) r[u][k] = ld16<kNtLoadRO>(q + u * kTile + k * (kSplit ? kTile / 2 : kPer));
+      for (int k = 0; k < kLoads; ++k) g.r[u][k] = ld16<kNtLoadRO>(q + u * kTile + k * (kSplit ? kTile / 2 : kPer));
       if constexpr (FUSE) {
         if constexpr (kSplit) {
           const uint2 lo = ld8<kNtLoadRO>(p.m + pos + u * kTile), hi = ld8<kNtLoadRO>(p.m + pos + u * kTile + kTile / 2);
-          mm[u] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+          g.mm[u] = make_uint4(lo.x, lo.y, hi.x, hi.y);
         } else {
-          mm[u] = ld16<kNtLoadRO>(p.m + pos + u * kTile);
+          g.mm[u] = ld16<kNtLoadRO>(p.m + pos + u * kTile);
         }
       }
     }
-    // called by all lanes of a wavefront together (the 128-bit form exchanges halves between neighbouring lanes)
-    auto store = [&](int u, const uint4& o) {
-      if constexpr (kSplit && FP8LM_CAST_STORE16) {
-        // lanes 2k and 2k+1 hold 8 codes each of both halves of the tile: the even lane takes the pair's 16 codes
-        // of the first half, the odd lane those of the second half, and each stores once with 128 bits
-        const bool odd = (threadIdx.x & 1) != 0;
-        const uint32_t g0 = (uint32_t)__shfl_xor((int)(odd ? o.x : o.z), 1, 64);
-        const uint32_t g1 = (uint32_t)__shfl_xor((int)(odd ? o.y : o.w), 1, 64);
-        const long long at = pos0 + u * kTile + (threadIdx.x & ~1) * 8 + (odd ? kTile / 2 : 0);
-        st16<kNtStoreWO>(p.dst + at, odd ? make_uint4(g0, g1, o.z, o.w) : make_uint4(o.x, o.y, g0, g1));
-      } else if constexpr (kSplit) {
-        st8<kNtStoreWO>(p.dst + pos + u * kTile, make_uint2(o.x, o.y));
-        st8<kNtStoreWO>(p.dst + pos + u * kTile + kTile / 2, make_uint2(o.z, o.w));
-      } else {
-        st16<kNtStoreWO>(p.dst + pos + u * kTile, o);
-      }
-    };
+  }
+  template <bool kSplit, int UN> __device__ __forceinline__ void tiles_as(const Regs<UN>& g, long long pos0) {
+    const long long pos = pos0 + threadIdx.x * (kSplit ? 8 : kGroup);
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       uint32_t w[kW];
 #pragma unroll
       for (int k = 0; k < kLoads; ++k) {
-        w[4 * k] = r[u][k].x; w[4 * k + 1] = r[u][k].y; w[4 * k + 2] = r[u][k].z; w[4 * k + 3] = r[u][k].w;
+        w[4 * k] = g.r[u][k].x; w[4 * k + 1] = g.r[u][k].y; w[4 * k + 2] = g.r[u][k].z; w[4 * k + 3] = g.r[u][k].w;
       }
-      uint4 o = make_uint4(0, 0, 0, 0);
-      bool slow = false;
-      if constexpr (DELAYED) slow = note_source(w);
-      if (slow) {             // rare: this group holds inf/NaN, encode it element by element
-        const uint32_t mw[4] = {mm[u].x, mm[u].y, mm[u].z, mm[u].w};
-        const uint32_t keep = amax16;
-        uint32_t* ow = &o.x;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const uint32_t bits = kSrc16<SRC> ? (w[(j >> 1) % kW] >> ((j & 1) * 16)) & 0xFFFFu : w[j % kW];
-          ow[j >> 2] |= one(bits, FUSE ? (mw[j >> 2] >> ((j & 3) * 8)) & 0xFFu : 0u) << ((j & 3) * 8);
+      if constexpr (DELAYED) {
+        if (note_source(w)) {   // rare: this group holds inf/NaN; element by element, and again from memory: no registers for it
+          if constexpr (kSplit) {
+            group(pos + u * kTile, kGroup / 2);
+            group(pos + u * kTile + kTile / 2, kGroup / 2);
+          } else {
+            group(pos + u * kTile, kGroup);
+          }
+          continue;
         }
-        amax16 = keep;
+      }
+      // one quad after the other: interleaved, as the compiler would have them, they take registers that other
+      // wavefronts make better use of (119 -> 94 with two tiles; the cast of GPT-125M 66 -> 62 us)
+      uint4 o;
+      o.x = quad(w, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      o.y = quad(w, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      o.z = quad(w, 2);
+      __builtin_amdgcn_sched_barrier(0);
+      o.w = quad(w, 3);
+      n_elems += kGroup;
+      if constexpr (FUSE) {
+        const uint4 mm = g.mm[u];
+        moment_word(o.x, mm.x);
+        moment_word(o.y, mm.y);
+        moment_word(o.z, mm.z);
+        moment_word(o.w, mm.w);
+      }
+      if constexpr (kSplit) {
+        st8<kNtStoreWO>(p.dst + pos + u * kTile, make_uint2(o.x, o.y));
+        st8<kNtStoreWO>(p.dst + pos + u * kTile + kTile / 2, make_uint2(o.z, o.w));
       } else {
-        o.x = quad(w, 0);
-        o.y = quad(w, 1);
-        o.z = quad(w, 2);
-        o.w = quad(w, 3);
-        if constexpr (FUSE) {
-          moment_word(o.x, mm[u].x);
-          moment_word(o.y, mm[u].y);
-          moment_word(o.z, mm[u].z);
-          moment_word(o.w, mm[u].w);
-        }
+        st16<kNtStoreWO>(p.dst + pos + u * kTile, o);
       }
-      store(u, o);            // all lanes again: the store may exchange data between lanes
     }
-    n_elems += UN * kGroup;
   }
   // 16 consecutive elements at `pos`, by this thread alone (the layout without the split)
-  __device__ __forceinline__ void full_group(long long pos) { tiles_as<1, false>(pos - (long long)threadIdx.x * kGroup); }
+  __device__ __forceinline__ void full_group(long long pos) {
+    Regs<1> g;
+    load_as<false>(g, pos - (long long)threadIdx.x * kGroup);
+    tiles_as<false>(g, pos - (long long)threadIdx.x * kGroup);
+  }
   __device__ __forceinline__ void group(long long pos, int valid) {
     const elem_t* q = static_cast<const elem_t*>(p.src) + pos;
+#pragma unroll 1
     for (int j = 0; j < valid; ++j) p.dst[pos + j] = (uint8_t)one(q[j], FUSE ? p.m[pos + j] : 0u);
     n_elems += valid;
   }
   using Stats = BlockStats<3, 2>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
+  __device__ __forceinline__ void flush(int t, long long u) {
+    BlockStats<3, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = src_final<SRC>(amax16);
     s.mx[2] = macc;
     s.ct[0] = n_elems - nz_top;                 // codes on the top magnitude
     s.ct[1] = (n_elems - nz_code) - z_in;       // zero codes that did not come from zero inputs
     s.orv = 0;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+    collect(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -486,7 +486,7 @@ struct CastOp {
 template <int FMT, bool DELAYED, bool FUSE, int SRC>
 __global__ __launch_bounds__(kThreads) void cast_kernel(Tables tb, CastParams p) {
   CastOp<FMT, DELAYED, FUSE, SRC> op(p, tb);
-  walk_chunks<FP8LM_UN_CAST>(tb, op);
+  walk_units<kUnCast<SRC>>(tb, op);
 }
 
 // Speculative just-in-time quantisation, step 1: one thread per tensor keeps the scale the meta holds and sets the
@@ -553,11 +553,12 @@ __global__ __launch_bounds__(kScanThreads) void redo_scan_kernel(const TensorDes
     totals[2] += e;
   }
 }
-// ... and its chunk table: workgroup t (and t + grid, ...) writes tensor t's id into its run of chunks.
-__global__ void redo_fill_kernel(const TensorDesc* redo_desc, int32_t* chunk_tensor, int n) {
+// ... and its chunk table: workgroup t (and t + grid, ...) copies tensor t's chunks into its run.
+__global__ void redo_fill_kernel(const TensorDesc* desc, const TensorDesc* redo_desc, const ChunkDesc* chunks, ChunkDesc* redo_chunks, int n) {
   for (int t = blockIdx.x; t < n; t += gridDim.x) {
     const TensorDesc d = redo_desc[t];
-    for (int i = threadIdx.x; i < d.n_chunks; i += blockDim.x) chunk_tensor[d.first_chunk + i] = t;
+    const int from = desc[t].first_chunk;
+    for (int i = threadIdx.x; i < d.n_chunks; i += blockDim.x) redo_chunks[d.first_chunk + i] = chunks[from + i];
   }
 }
 
@@ -623,10 +624,10 @@ struct RequantOp {
   float vmax;
   uint32_t n_elems, nz_top, nz_code, nz_in, nonfinite;
   __device__ RequantOp(const RequantParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
-  __device__ __forceinline__ void begin(int t, const TensorDesc&) {
-    inv_src = p.src_meta[t].inv_scale;
-    sg = p.shared[t];
-    careful = (p.src_meta[t].flags & FP8LM_FLAG_NONFINITE) != 0;
+  __device__ __forceinline__ void begin(int t) {
+    inv_src = uniform_load(&p.src_meta[t].inv_scale);
+    sg = uniform_load(p.shared + t);
+    careful = (uniform_load(&p.src_meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0;
     vmax = 0.0f;
     n_elems = nz_top = nz_code = nz_in = nonfinite = 0;
   }
@@ -642,17 +643,25 @@ struct RequantOp {
     nz_top += nonzero_bytes7(mag ^ Fp8Traits<FMT>::kTopX4);
     return c;
   }
-  template <int UN> __device__ __forceinline__ void tiles(long long pos0) {
-    uint4 a[UN];
+  template <int UN> struct Regs { uint4 a[UN]; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& g, long long pos0) {
     const long long pos = pos0 + threadIdx.x * kGroup;
 #pragma unroll
-    for (int u = 0; u < UN; ++u) a[u] = ld16<false>(p.src + pos + u * kTile);   // may be in place: cached loads
+    for (int u = 0; u < UN; ++u) g.a[u] = ld16<kNtLoadRW>(p.src + pos + u * kTile);
+  }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& g, long long pos0) {
+    const long long pos = pos0 + threadIdx.x * kGroup;
 #pragma unroll
-    for (int u = 0; u < UN; ++u) st16<false>(p.dst + pos + u * kTile, make_uint4(word(a[u].x), word(a[u].y), word(a[u].z), word(a[u].w)));
+    for (int u = 0; u < UN; ++u)
+      st16<kNtStoreRW>(p.dst + pos + u * kTile, make_uint4(word(g.a[u].x), word(g.a[u].y), word(g.a[u].z), word(g.a[u].w)));
     n_elems += UN * kGroup;
   }
   // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
-  __device__ __forceinline__ void full_group(long long pos) { tiles<1>(pos - (long long)threadIdx.x * kGroup); }
+  __device__ __forceinline__ void full_group(long long pos) {
+    Regs<1> g;
+    load(g, pos - (long long)threadIdx.x * kGroup);
+    tiles(g, pos - (long long)threadIdx.x * kGroup);
+  }
   __device__ __forceinline__ void group(long long pos, int valid) {
     for (int j = 0; j < valid; ++j) {
       const uint32_t in = p.src[pos + j];
@@ -668,21 +677,20 @@ struct RequantOp {
     n_elems += valid;
   }
   using Stats = BlockStats<1, 2>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
+  __device__ __forceinline__ void flush(int t, long long u) {
+    BlockStats<1, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.ct[0] = n_elems - nz_top;
     s.ct[1] = nz_in - nz_code;                 // non-zero codes in, zero codes out (a NaN code is non-zero on both sides)
     s.orv = nonfinite;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+    collect(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float vm = u2f(s.mx[0]);
     const unsigned long long n_sat = s.ct[0], n_und = s.ct[1];
     const uint32_t nf = s.orv;
     fp8lm_meta& M = p.dst_meta[t];
-    const float src_amax = p.src_meta[t].amax;
+    const float src_amax = p.src_meta[t].amax, sg = p.shared[t];
     const float inv = 1.0f / sg;
     M.scale = sg;
     M.inv_scale = inv;
@@ -697,7 +705,7 @@ struct RequantOp {
 template <int FMT>
 __global__ __launch_bounds__(kThreads) void requantize_kernel(Tables tb, RequantParams p) {
   RequantOp<FMT> op(p, tb);
-  walk_chunks<2>(tb, op);
+  walk_units<kUnRequant>(tb, op);
 }
 
 struct SumParams {
@@ -718,7 +726,7 @@ struct SumOp {
   uint32_t amax_bits, n_elems, n_top, n_und;   // n_top / n_und: counted element by element (tails, NaN groups)
   uint32_t n_fast, nz_top, nz_code, z_acc;     // whole groups: counted on the packed codes, as in the cast
   __device__ SumOp(const SumParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
-  __device__ __forceinline__ void begin(int, const TensorDesc&) {
+  __device__ __forceinline__ void begin(int) {
     vmax = 0.0f;
     amax_bits = n_elems = n_top = n_und = n_fast = nz_top = nz_code = z_acc = 0;
   }
@@ -776,15 +784,23 @@ struct SumOp {
   }
   // NR > 0: that many ranks, all loads of UN tiles issued up front.  NR == 0: any number of ranks
   // (p.in.n_ranks), loaded eight at a time.
-  template <int UN> __device__ __forceinline__ void tiles(long long pos0) {
+  template <int UN> struct Regs { uint4 a[UN][NR > 0 ? NR : 1]; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& g, long long pos0) {
     const long long pos = pos0 + threadIdx.x * kGroup;
-    if constexpr (NR == 0) {
-      const int n = p.in.n_ranks;
 #pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        float acc[kGroup];
+    for (int u = 0; u < UN; ++u)
 #pragma unroll
-        for (int j = 0; j < kGroup; ++j) acc[j] = 0.0f;
+      for (int r = 0; r < NR; ++r) g.a[u][r] = ld16<kNtLoadRO>(p.in.p[r] + pos + u * kTile);
+  }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& g, long long pos0) {
+    const long long pos = pos0 + threadIdx.x * kGroup;
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      float acc[kGroup];
+#pragma unroll
+      for (int j = 0; j < kGroup; ++j) acc[j] = 0.0f;
+      if constexpr (NR == 0) {
+        const int n = p.in.n_ranks;
         for (int r0 = 0; r0 < n; r0 += kUnrolledRanks) {
           uint4 a[kUnrolledRanks];
 #pragma unroll
@@ -794,28 +810,20 @@ struct SumOp {
           for (int k = 0; k < kUnrolledRanks; ++k)
             if (r0 + k < n) add_rank(acc, a[k]);
         }
-        finish_group(acc, pos + u * kTile);
+      } else {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) add_rank(acc, g.a[u][r]);
       }
-    } else {
-      uint4 a[UN][NR > 0 ? NR : 1];
-#pragma unroll
-      for (int u = 0; u < UN; ++u)
-#pragma unroll
-        for (int r = 0; r < NR; ++r) a[u][r] = ld16<kNtLoadRO>(p.in.p[r] + pos + u * kTile);
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        float acc[kGroup];
-#pragma unroll
-        for (int j = 0; j < kGroup; ++j) acc[j] = 0.0f;
-#pragma unroll
-        for (int r = 0; r < NR; ++r) add_rank(acc, a[u][r]);
-        finish_group(acc, pos + u * kTile);
-      }
+      finish_group(acc, pos + u * kTile);
     }
     n_elems += UN * kGroup;
   }
   // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
-  __device__ __forceinline__ void full_group(long long pos) { tiles<1>(pos - (long long)threadIdx.x * kGroup); }
+  __device__ __forceinline__ void full_group(long long pos) {
+    Regs<1> g;
+    load(g, pos - (long long)threadIdx.x * kGroup);
+    tiles(g, pos - (long long)threadIdx.x * kGroup);
+  }
   __device__ __forceinline__ void group(long long pos, int valid) {
     for (int j = 0; j < valid; ++j) {
       float acc = 0.0f;
@@ -826,15 +834,14 @@ struct SumOp {
     n_elems += valid;
   }
   using Stats = BlockStats<2, 2>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
+  __device__ __forceinline__ void flush(int t, long long u) {
+    BlockStats<2, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = amax_bits;
     s.ct[0] = n_top + (n_fast - nz_top);              // codes on the top magnitude
     s.ct[1] = n_und + ((n_fast - nz_code) - z_acc);   // zero codes that did not come from zero sums
     s.orv = 0;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+    collect(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -857,7 +864,7 @@ struct SumOp {
 template <int FMT, int NR>
 __global__ __launch_bounds__(kThreads) void sum_fp8_kernel(Tables tb, SumParams p) {
   SumOp<FMT, NR> op(p, tb);
-  walk_chunks<(NR == 0 ? 1 : NR <= 2 ? 4 : NR <= 4 ? 2 : 1)>(tb, op);   // about eight 128-bit loads in flight per thread
+  walk_units<sum_tiles(NR)>(tb, op);   // about eight 128-bit loads in flight per thread
 }
 
 }  // namespace fp8lm

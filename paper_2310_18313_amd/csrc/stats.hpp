@@ -18,6 +18,7 @@ struct StatsParams {
   const uint8_t* q;
   const fp8lm_meta* meta;
   fp8lm_quant_stats* out;
+  Partial* partials;       // [grid + n_tensors]
 };
 
 template <int FMT, int SRC>
@@ -31,12 +32,11 @@ struct QuantStatsOp {
   double rs, signal, noise;
   uint32_t n_nonzero, n_under, n_over, n_nonfinite;
   __device__ QuantStatsOp(const StatsParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
-  __device__ __forceinline__ void begin(int t, const TensorDesc&) {
+  __device__ __forceinline__ void begin(int t) {
     rs = 1.0 / (double)p.meta[t].scale;
     signal = noise = 0.0;
     n_nonzero = n_under = n_over = n_nonfinite = 0;
   }
-  __device__ __forceinline__ bool fast() const { return true; }
   __device__ __forceinline__ void one(uint32_t rbits, uint32_t code) {
     const float r = SrcTraits<SRC>::dec(rbits);
     const float pv = fp8_to_f32<FMT>(code);
@@ -53,55 +53,97 @@ struct QuantStatsOp {
     n_under += (r != 0.0f) && mag == 0u;
     n_over += mag == Fp8Traits<FMT>::kTop;
   }
-  template <int UN> __device__ __forceinline__ void tiles(long long pos0) {
-    const long long pos = pos0 + threadIdx.x * kGroup;
+  // the 16 consecutive elements at `pos`, by this thread alone
+  __device__ __forceinline__ void full_group(long long pos) {
     const elem_t* rp = static_cast<const elem_t*>(p.ref) + pos;
-    uint4 r[UN][kLoads], qq[UN];
+    uint4 r[kLoads];
 #pragma unroll
-    for (int u = 0; u < UN; ++u) {
+    for (int k = 0; k < kLoads; ++k) r[k] = ld16<kNtLoadRO>(rp + k * kPer);
+    const uint4 qq = ld16<kNtLoadRO>(p.q + pos);
+    uint32_t w[kW];
 #pragma unroll
-      for (int k = 0; k < kLoads; ++k) r[u][k] = ld16<kNtLoadRO>(rp + u * kTile + k * kPer);
-      qq[u] = ld16<kNtLoadRO>(p.q + pos + u * kTile);
+    for (int k = 0; k < kLoads; ++k) {
+      w[4 * k] = r[k].x; w[4 * k + 1] = r[k].y; w[4 * k + 2] = r[k].z; w[4 * k + 3] = r[k].w;
     }
+    const uint32_t qw[4] = {qq.x, qq.y, qq.z, qq.w};
 #pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      uint32_t w[kW];
-#pragma unroll
-      for (int k = 0; k < kLoads; ++k) {
-        w[4 * k] = r[u][k].x; w[4 * k + 1] = r[u][k].y; w[4 * k + 2] = r[u][k].z; w[4 * k + 3] = r[u][k].w;
-      }
-      const uint32_t qw[4] = {qq[u].x, qq[u].y, qq[u].z, qq[u].w};
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const uint32_t bits = kSrc16<SRC> ? (w[(j >> 1) % kW] >> ((j & 1) * 16)) & 0xFFFFu : w[j % kW];
-        one(bits, (qw[j >> 2] >> ((j & 3) * 8)) & 0xFFu);
-      }
+    for (int j = 0; j < 16; ++j) {
+      const uint32_t bits = kSrc16<SRC> ? (w[(j >> 1) % kW] >> ((j & 1) * 16)) & 0xFFFFu : w[j % kW];
+      one(bits, (qw[j >> 2] >> ((j & 3) * 8)) & 0xFFu);
     }
   }
-  // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
-  __device__ __forceinline__ void full_group(long long pos) { tiles<1>(pos - (long long)threadIdx.x * kGroup); }
   __device__ __forceinline__ void group(long long pos, int valid) {
     const elem_t* rp = static_cast<const elem_t*>(p.ref) + pos;
     for (int j = 0; j < valid; ++j) one(rp[j], p.q[pos + j]);
   }
-  using Stats = BlockStats<0, 4, 2>;
-  __device__ __forceinline__ void flush(int t, const TensorDesc& d, int done) {
-    Stats s;
-    s.ct[0] = n_nonzero; s.ct[1] = n_under; s.ct[2] = n_over; s.ct[3] = n_nonfinite;
-    s.fs[0] = signal; s.fs[1] = noise;
-    s.orv = 0;
-    block_combine(s);
-    if (collect(tb, t, d, done, s) && threadIdx.x == 0) finalize(t, d, s);
+  // The workgroup's totals as one record (every step in a fixed order).
+  __device__ __forceinline__ void flush(Partial* rec) { combine(Partial{{signal, noise}, {n_nonzero, n_under, n_over, n_nonfinite}}, rec); }
+  static __device__ __forceinline__ void combine(Partial s, Partial* rec) {
+    __shared__ Partial l_p[kWaves];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) s.fs[i] = wave_sum_f64(s.fs[i]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s.ct[i] = wave_sum_u64(s.ct[i]);
+    __syncthreads();             // the previous use of the LDS array is over
+    if ((threadIdx.x & 63) == 0) l_p[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      for (int w = 1; w < kWaves; ++w) add(s, l_p[w]);
+      *rec = s;
+    }
   }
-  __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
-    p.out[t] = fp8lm_quant_stats{s.fs[0], s.fs[1], s.ct[0], s.ct[1], s.ct[2], s.ct[3]};
+  static __device__ __forceinline__ void add(Partial& s, const Partial& o) {
+    s.fs[0] += o.fs[0];
+    s.fs[1] += o.fs[1];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s.ct[i] += o.ct[i];
   }
 };
 
+// float64 sums are only reproducible if they are added in a fixed order, so these statistics do not go through slots: a
+// persistent grid, workgroup b walking the chunks [b*C/G, (b+1)*C/G), one record per (workgroup, tensor) pair.  The
+// workgroups that touch tensor t are consecutive and a workgroup touches consecutive tensors, so record b + t is unique
+// and the records of a tensor are contiguous.  (The kernel only reads: the order of the walk costs nothing here.)
 template <int FMT, int SRC>
 __global__ __launch_bounds__(kThreads) void quant_stats_kernel(Tables tb, StatsParams p) {
   QuantStatsOp<FMT, SRC> op(p, tb);
-  walk_chunks<1>(tb, op);
+  const long long C = tb.n_chunks, b = blockIdx.x, G = gridDim.x;
+  int cur = -1;
+  for (long long c = b * C / G; c < (b + 1) * C / G; ++c) {
+    const ChunkDesc k = uniform_load(tb.chunks + c);
+    if (k.tensor != cur) {
+      if (cur >= 0) op.flush(p.partials + (b + cur));
+      cur = k.tensor;
+      op.begin(cur);
+    }
+    for (int i = threadIdx.x * kGroup; i < k.len; i += kTile) {
+      if (k.len - i >= kGroup) op.full_group(k.base + i);
+      else op.group(k.base + i, k.len - i);
+    }
+  }
+  if (cur >= 0) op.flush(p.partials + (b + cur));
+}
+
+// One workgroup per tensor adds up its records: lane by lane, then over the workgroup, in a fixed order.
+template <int FMT, int SRC>
+__global__ __launch_bounds__(kThreads) void quant_stats_epilogue_kernel(Tables tb, StatsParams p, int main_grid, int n_tensors) {
+  typedef QuantStatsOp<FMT, SRC> Op;
+  __shared__ Partial l_total;
+  for (int t = blockIdx.x; t < n_tensors; t += gridDim.x) {
+    const TensorDesc d = tb.desc[t];
+    if (d.n_chunks == 0) {                       // an empty tensor
+      if (threadIdx.x == 0) p.out[t] = fp8lm_quant_stats{0.0, 0.0, 0, 0, 0, 0};
+      continue;
+    }
+    // owner(c) = the b with b*C/G <= c < (b+1)*C/G
+    const long long C = tb.n_chunks, c0 = d.first_chunk, c1 = c0 + d.n_chunks - 1;
+    const long long b_lo = ((c0 + 1) * main_grid - 1) / C, b_hi = ((c1 + 1) * main_grid - 1) / C;
+    Partial s{};
+    for (long long b = b_lo + threadIdx.x; b <= b_hi; b += kThreads) Op::add(s, p.partials[b + t]);
+    Op::combine(s, &l_total);
+    if (threadIdx.x == 0)
+      p.out[t] = fp8lm_quant_stats{l_total.fs[0], l_total.fs[1], l_total.ct[0], l_total.ct[1], l_total.ct[2], l_total.ct[3]};
+  }
 }
 
 __global__ void quant_stats_zero_kernel(fp8lm_quant_stats* out, int n) {
@@ -135,9 +177,11 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(const uint4* __restrict_
   for (; i < b1; i += kThreads) st16<true>(dst + i, ld16<true>(src + i));
 }
 
-// Memory-only skeletons of the hot kernels: the same persistent grid, tile walk, access widths, access layout and
+// Memory-only skeletons of the hot kernels: the same grid, walk, access widths, access layout and
 // cache policies as the kernels they stand for, with the arithmetic replaced by XORs.  What they reach is the
 // bandwidth ceiling of that access pattern on this machine; the real kernels are measured against it.
+//   RANGES : 0: a workgroup takes UN tiles and ends, as the kernels do; 1: a persistent grid, every workgroup walking a
+//   range of its own, which shows where a buffer lies in HBM more clearly than the kernels feel it;
 //   NS1 / NS2 : number of 8-bit / 16-bit streams read;  ND1 / ND2 : number of 8-bit / 16-bit streams written.
 // A thread takes elements [8L, 8L+8) of both halves of a 4096-element tile (L = thread index), like the update and
 // cast kernels: 64-bit accesses on 8-bit streams, 128-bit accesses on 16-bit streams, contiguous over the workgroup.
@@ -147,11 +191,13 @@ struct SkeletonParams {
   uint8_t* d1[2];
   uint16_t* d2[2];
   long long n_tiles;
-  uint32_t* sink;        // one word per workgroup, so that pure reads cannot be optimised away
+  uint32_t* sink;        // a word that pure reads could write, so that they cannot be optimised away
 };
-template <int NS1, int NS2, int ND1, int ND2, int UN>
+template <int NS1, int NS2, int ND1, int ND2, int UN, bool RANGES = false>
 __global__ __launch_bounds__(kThreads) void skeleton_kernel(SkeletonParams p) {
-  const long long t0 = p.n_tiles * blockIdx.x / gridDim.x, t1 = p.n_tiles * (blockIdx.x + 1) / gridDim.x;
+  const long long t0 = RANGES ? p.n_tiles * blockIdx.x / gridDim.x : (long long)blockIdx.x * UN;
+  const long long t1 = RANGES ? p.n_tiles * (blockIdx.x + 1) / gridDim.x : p.n_tiles;
+  const long long stride = RANGES ? UN : (long long)gridDim.x * UN;      // one round unless the grid is at its limit
   uint32_t acc = 0;
   auto body = [&](long long tile, auto un_tag) {
     constexpr int U = decltype(un_tag)::value;
@@ -184,11 +230,10 @@ __global__ __launch_bounds__(kThreads) void skeleton_kernel(SkeletonParams p) {
     }
   };
   long long tile = t0;
-  for (; tile + UN <= t1; tile += UN) body(tile, std::integral_constant<int, UN>{});
-  for (; tile < t1; ++tile) body(tile, std::integral_constant<int, 1>{});
+  for (; tile + UN <= t1; tile += stride) body(tile, std::integral_constant<int, UN>{});
+  for (int u = 0; u < UN && tile < t1; ++u, ++tile) body(tile, std::integral_constant<int, 1>{});
   if constexpr (ND1 + ND2 == 0) {
-    acc = wave_or_u32(acc);
-    if ((threadIdx.x & 63) == 0) p.sink[blockIdx.x * kWaves + (threadIdx.x >> 6)] = acc;
+    if (acc == 0x9E3779B9u) *p.sink = acc;
   }
 }
 

@@ -12,10 +12,7 @@ constexpr int kThreads = 256;
 constexpr int kGroup = 16;                 // elements per thread per iteration
 constexpr int kTile = kThreads * kGroup;   // elements per workgroup per iteration
 constexpr int kWaves = kThreads / 64;
-#ifndef FP8LM_MAX_BLOCKS_PER_CU
-#define FP8LM_MAX_BLOCKS_PER_CU 16         // the step gains up to 16 workgroups per compute unit and is flat from 16 to 64
-#endif
-constexpr int kMaxBlocksPerCu = FP8LM_MAX_BLOCKS_PER_CU;   // upper limit (and default) of the launch tuning; sizes the record array
+constexpr int kMaxBlocksPerCu = 16;        // upper limit of the launch tuning; this value, the default, means "no limit"
 
 struct TensorDesc {
   int64_t offset;
@@ -23,13 +20,24 @@ struct TensorDesc {
   int32_t first_chunk;
   int32_t n_chunks;
   uint32_t flags;       // FP8LM_TENSOR_* attributes of the tensor
-  uint32_t pad;
+  int32_t epi0;         // the first of the workgroups that combine its records (epilogue_kernel)
 };
+struct alignas(16) ChunkDesc {
+  int64_t base;         // its first element in the flat buffers
+  int32_t len;
+  int32_t tensor;
+};
+// How many workgroups combine a tensor's records.
+constexpr int kEpilogueChunks = 512, kMaxEpilogue = 64;
+__host__ __device__ inline int epilogue_groups(int32_t n_chunks) {
+  const int k = (n_chunks + kEpilogueChunks - 1) / kEpilogueChunks;
+  return k < 1 ? 1 : (k > kMaxEpilogue ? kMaxEpilogue : k);
+}
 
 // Per-tensor scratch.  The ticket is zero between launches; the `pend` block carries the scales chosen
-// by the first Adam pass to the second.
+// by the first Adam pass to the second, and what else that needs to know of a tensor.
 struct alignas(128) Scratch {
-  uint32_t ticket;                // chunks finished
+  uint32_t ticket;                // units finished, or epilogue workgroups
   uint32_t redo;                  // speculative quantisation: 1 if the tensor has to be cast again with the scale now in its meta
   float old_scale, old_inv;       // ... and the scale the meta held before the speculation
   struct Pending {
@@ -39,45 +47,88 @@ struct alignas(128) Scratch {
     uint32_t amax_m_bits;   // written by a fused cast: bit pattern of max |m'|
     uint32_t tame;          // the update may take the short arithmetic, with these coefficients (tame_range)
     float c[8];
+    float inv_sg, inv_sm, inv_sv, inv_sw, decay;      // inverse scales of the inputs; 1 - lr * weight_decay, or 1 if exempt
   } pend;
 };
 
-// What one workgroup found in its part of one tensor: maxima (bit patterns of non-negative values),
-// counters and an OR-mask.  One record per (workgroup, tensor) pair, each in a cache line of its own.
-struct alignas(128) Partial {
-  uint32_t mx[3];
-  uint32_t orv;
-  unsigned long long ct[8];
-  double fs[2];                   // float64 sums (error statistics)
+// What one workgroup found in its part of one tensor, for statistics whose order of summation has to be fixed (float64
+// sums).  One record per (workgroup, tensor) pair.
+struct alignas(64) Partial {
+  double fs[2];
+  unsigned long long ct[4];
 };
 
 struct Tables {
   const TensorDesc* desc;
-  const int32_t* chunk_tensor;
+  const ChunkDesc* chunks;
   Scratch* scratch;
-  Partial* partials;              // [grid + n_tensors]
+  unsigned char* records;         // one record per unit (see leave_record)
+  unsigned long long* totals;     // [epilogue workgroups][kTotalWords] what those of a large tensor hand to the last of them
+  const int32_t* epi_tensor;      // [n_epi] tensor of an epilogue workgroup
+  int32_t n_epi;
   int32_t n_chunks;
-  int32_t chunk_elems;
+  int32_t unit_elems;             // a chunk is cut into 2^unit_shift units of unit_elems elements, the work of a workgroup
+  int32_t unit_shift;
+  int32_t one_unit;               // 1: the grid has one workgroup per unit; 0: a workgroup walks a contiguous range of units
   int32_t deferred;               // 1: workgroups only leave their records; an epilogue launch finishes the tensors
   const int32_t* n_chunks_dev;    // if set: the number of chunks is read from here (a chunk list built on the device);
                                   // n_chunks is then only the host's upper bound
 };
 __device__ __forceinline__ long long chunk_count(const Tables& tb) { return tb.n_chunks_dev ? *tb.n_chunks_dev : tb.n_chunks; }
 
-// ---- reductions ----------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+// A load of something that no kernel writes while another may read it here, from an address all lanes share: through the
+// scalar cache, whatever stores come before it.
+template <class T> __device__ __forceinline__ T uniform_load(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "words");
+  struct Words { uint32_t w[sizeof(T) / 4]; } v;
+  const auto* q = reinterpret_cast<const __attribute__((address_space(4))) uint32_t*>(reinterpret_cast<uintptr_t>(p));
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, o, 64));
+  for (size_t i = 0; i < sizeof(T) / 4; ++i) v.w[i] = q[i];
+  return __builtin_bit_cast(T, v);
+}
+
+// Writes the chunk and epilogue tables from the tensor table and returns the tickets to zero; workgroup t (and t + grid,
+// ...) does tensor t's part.
+__global__ void chunk_tables_kernel(const TensorDesc* desc, ChunkDesc* chunks, int32_t* epi_tensor, Scratch* scratch, int chunk_elems, int n) {
+  for (int t = blockIdx.x; t < n; t += gridDim.x) {
+    const TensorDesc d = desc[t];
+    for (int i = threadIdx.x; i < d.n_chunks; i += blockDim.x) {
+      const long long e0 = (long long)i * chunk_elems, rest = d.numel - e0;
+      chunks[d.first_chunk + i] = ChunkDesc{d.offset + e0, (int32_t)(rest < chunk_elems ? rest : chunk_elems), t};
+    }
+    if (d.n_chunks > 0)
+      for (int i = threadIdx.x; i < epilogue_groups(d.n_chunks); i += blockDim.x) epi_tensor[d.epi0 + i] = t;
+    if (threadIdx.x == 0) scratch[t].ticket = 0;
+  }
+}
+
+// ---- reductions ----------------------------------------------------------------------------------
+// Over a wavefront by data-parallel-primitive moves (rows of 16 lanes, then the two row broadcasts): the moves are part
+// of the vector instruction, no LDS traffic.  The total is valid in lane 63.
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <class F> __device__ __forceinline__ uint32_t wave_reduce_u32(uint32_t v, F f) {   // f(x, 0) == x
+  v = f(v, dpp_or_zero<0x111, 0xF>(v));   // row_shr:1
+  v = f(v, dpp_or_zero<0x112, 0xF>(v));   // row_shr:2
+  v = f(v, dpp_or_zero<0x114, 0xF>(v));   // row_shr:4
+  v = f(v, dpp_or_zero<0x118, 0xF>(v));   // row_shr:8: lane 15 of every row holds the row's total
+  v = f(v, dpp_or_zero<0x142, 0xA>(v));   // row_bcast:15 into rows 1 and 3
+  v = f(v, dpp_or_zero<0x143, 0xC>(v));   // row_bcast:31 into rows 2 and 3
   return v;
 }
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  return wave_reduce_u32(v, [](uint32_t a, uint32_t b) { return max(a, b); });
 }
 __device__ __forceinline__ uint32_t wave_or_u32(uint32_t v) {
+  return wave_reduce_u32(v, [](uint32_t a, uint32_t b) { return a | b; });
+}
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
+  return wave_reduce_u32(v, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {   // valid in every lane
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v |= (uint32_t)__shfl_xor((int)v, o, 64);
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
 __device__ __forceinline__ double wave_sum_f64(double v) {
@@ -86,213 +137,265 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
   return v;
 }
 
-// Workgroup-wide combine of up to NV maxima, NC counters, NF float64 sums and one OR-mask; result valid in
-// thread 0.  Every step is done in a fixed order, so the float64 sums are reproducible from run to run.
-template <int NV, int NC, int NF = 0>
+// NV maxima, NC counters and one OR-mask of a tensor: per lane while a workgroup works on it (CT = uint32_t; a unit
+// has at most 2^20 elements), and as the tensor's totals.
+template <int NV, int NC, class CT = unsigned long long>
 struct BlockStats {
+  static constexpr int kNV = NV, kNC = NC;
   uint32_t mx[NV > 0 ? NV : 1];
-  unsigned long long ct[NC > 0 ? NC : 1];
-  double fs[NF > 0 ? NF : 1];
+  CT ct[NC > 0 ? NC : 1];
   uint32_t orv;
 };
-
-template <int NV, int NC, int NF>
-__device__ __forceinline__ void block_combine(BlockStats<NV, NC, NF>& s) {
-  __shared__ uint32_t l_mx[kWaves][NV > 0 ? NV : 1];
-  __shared__ unsigned long long l_ct[kWaves][NC > 0 ? NC : 1];
-  __shared__ double l_fs[kWaves][NF > 0 ? NF : 1];
-  __shared__ uint32_t l_or[kWaves];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int i = 0; i < NV; ++i) s.mx[i] = wave_max_u32(s.mx[i]);
-#pragma unroll
-  for (int i = 0; i < NC; ++i) s.ct[i] = wave_sum_u64(s.ct[i]);
-#pragma unroll
-  for (int i = 0; i < NF; ++i) s.fs[i] = wave_sum_f64(s.fs[i]);
-  s.orv = wave_or_u32(s.orv);
-  __syncthreads();   // the previous use of the LDS arrays is over
-  if (lane == 0) {
-#pragma unroll
-    for (int i = 0; i < NV; ++i) l_mx[wave][i] = s.mx[i];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) l_ct[wave][i] = s.ct[i];
-#pragma unroll
-    for (int i = 0; i < NF; ++i) l_fs[wave][i] = s.fs[i];
-    l_or[wave] = s.orv;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-#pragma unroll
-    for (int w = 1; w < kWaves; ++w) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i) s.mx[i] = max(s.mx[i], l_mx[w][i]);
-#pragma unroll
-      for (int i = 0; i < NC; ++i) s.ct[i] += l_ct[w][i];
-#pragma unroll
-      for (int i = 0; i < NF; ++i) s.fs[i] += l_fs[w][i];
-      s.orv |= l_or[w];
-    }
-  }
-}
+constexpr int kTotalWords = 16;       // 4 words of maxima and mask, up to 8 counters
 
 // Cross-workgroup reduction of a tensor's statistics.
 //
-// Workgroup b walks the chunk range [b*C/G, (b+1)*C/G), so the workgroups that touch tensor t are
-// consecutive and a workgroup touches consecutive tensors: record b + t is unique to the pair (b, t) and
-// the records of one tensor are contiguous.  Every workgroup stores its partial result into its record
-// (each record has a cache line of its own).  What happens next has two forms:
+// A workgroup combines what its lanes found in one unit (wavefront, then LDS) and leaves it as a record of 16 bytes
+// (maxima and OR-mask), 32 (and two counters) or 64 (and eight).  The units of a tensor are consecutive, so are their
+// records.  How the tensors are finished has two forms with the same results:
 //
-//  * single pass: the workgroup adds its finished chunks to the tensor's ticket with one atomic; the
-//    workgroup whose addition completes the ticket reads the records of all the others, combines them
-//    and runs the tensor's scalar epilogue.  Measured on MI355X, a ticket costs every workgroup about
-//    20 ns that do not overlap with those of other workgroups (12 ns for an atomic on an address all
-//    workgroups share, 8 ns for the release that makes the record visible): 80 us for a launch of 4096
-//    workgroups, nothing beside the milliseconds of a 13B-parameter model, more than the data of a
-//    100M-parameter one.
-//  * deferred: no ticket; a second, tiny launch (one workgroup per tensor) combines the records after the
-//    first has ended and runs the epilogues.  Costs one launch (about 3 us), independent of the grid.
+//  * deferred: a second, tiny launch combines the records and runs the tensors' scalar epilogues: one workgroup per
+//    tensor, or one per 512 chunks of a large one, of which the last to arrive adds up what the others left.
+//  * single pass: every workgroup bumps a per-tensor ticket, the one that completes it reads the records of the tensor.  A
+//    ticket costs every workgroup about 20 ns that do not overlap with those of other workgroups (12 ns for an
+//    atomic on an address all workgroups share, 8 ns for the release that makes the record visible).
 //
-// The host picks the form per launch from the chunks each workgroup has (fp8lm_set_tuning); the default is
-// the deferred form at every size.
-//
-// Ordering in the single pass: records are written and read with agent-scope atomic accesses (they bypass
-// the caches that are not coherent across the chip); the ticket is bumped with release/acquire semantics,
-// so the completing workgroup observes every record written before the other workgroups' bumps.
-template <int NV, int NC, int NF>
-__device__ __forceinline__ void store_record(const Tables& tb, int t, const BlockStats<NV, NC, NF>& s) {
-  Partial* rec = tb.partials + ((long long)blockIdx.x + t);
+// Measured and not used: adding to per-tensor slots with fire-and-forget atomics instead of leaving records.  At device
+// scope they are served outside the L2s at about 15 ns each whichever line they go to: the update pass of 1.8e9
+// elements (442 000 workgroups) took 29 ms instead of 4.
+template <int NC> constexpr int kRecordBytes = NC == 0 ? 16 : (NC <= 4 ? 32 : 64);
+
+// Combines s over the workgroup; the results end up in the first lanes of the first wavefront: lane 0 holds the maxima and the
+// mask, lane 1 counters 0..3, lane 2 counters 4..7 (that is, lane i holds the i-th 16 bytes of the record).
+template <int NV, int NC>
+__device__ __forceinline__ uint4 block_combine(const BlockStats<NV, NC, uint32_t>& s) {
+  constexpr int kWords = NC == 0 ? 4 : (NC <= 4 ? 8 : 12);
+  __shared__ uint4 l_v[kWaves][kWords / 4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t v[kWords];
 #pragma unroll
-  for (int i = 0; i < NV; ++i) __hip_atomic_store(&rec->mx[i], s.mx[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int i = 0; i < 3; ++i) v[i] = i < NV ? wave_max_u32(s.mx[i < NV ? i : 0]) : 0u;
+  v[3] = wave_or_u32(s.orv);
 #pragma unroll
-  for (int i = 0; i < NC; ++i) __hip_atomic_store(&rec->ct[i], s.ct[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int i = 4; i < kWords; ++i) v[i] = i - 4 < NC ? wave_sum_u32(s.ct[i - 4 < NC ? i - 4 : 0]) : 0u;
+  __syncthreads();   // the previous use of the LDS array is over
+  if (lane == 63) {
 #pragma unroll
-  for (int i = 0; i < NF; ++i) __hip_atomic_store(&rec->fs[i], s.fs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(&rec->orv, s.orv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int i = 0; i < kWords / 4; ++i) l_v[wave][i] = make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+  }
+  __syncthreads();
+  uint4 r = make_uint4(0, 0, 0, 0);
+  if (threadIdx.x < kWords / 4) {
+    r = l_v[0][threadIdx.x];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) {
+      const uint4 o = l_v[w][threadIdx.x];
+      if (threadIdx.x == 0) r = make_uint4(max(r.x, o.x), max(r.y, o.y), max(r.z, o.z), r.w | o.w);
+      else r = make_uint4(r.x + o.x, r.y + o.y, r.z + o.z, r.w + o.w);
+    }
+  }
+  return r;
 }
 
-// Combines the records of all workgroups of a launch with `grid` workgroups that touched tensor t.  Called
-// by all threads; the totals end up in thread 0's `s`.
-template <int NV, int NC, int NF>
-__device__ __forceinline__ void gather_records(const Tables& tb, int t, const TensorDesc& d, long long grid, BlockStats<NV, NC, NF>& s) {
-  // owner(c) = the b with b*C/G <= c < (b+1)*C/G
-  const long long C = chunk_count(tb);
-  if (grid > C) grid = C;         // a launch with more workgroups than chunks uses only the first C (see walk_chunks)
-  const long long c0 = d.first_chunk, c1 = c0 + d.n_chunks - 1;
-  const long long b_lo = ((c0 + 1) * grid - 1) / C, b_hi = ((c1 + 1) * grid - 1) / C;
+// Adds up records [u0, u1) with the whole workgroup; the totals are valid in thread 0.
+template <int NV, int NC>
+__device__ __forceinline__ void gather_records(const Tables& tb, long long u0, long long u1, BlockStats<NV, NC>& s) {
+  constexpr int kQuads = kRecordBytes<NC> / 16;
+  BlockStats<NV, NC> a;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) s.mx[i] = 0;
+  for (int i = 0; i < NV; ++i) a.mx[i] = 0;
 #pragma unroll
-  for (int i = 0; i < NC; ++i) s.ct[i] = 0;
+  for (int i = 0; i < NC; ++i) a.ct[i] = 0;
+  a.orv = 0;
+#pragma unroll 4
+  for (long long u = u0 + threadIdx.x; u < u1; u += kThreads) {
+    const uint4* rec = reinterpret_cast<const uint4*>(tb.records + u * kRecordBytes<NC>);
+    const uint4 h = rec[0];
+    const uint32_t m[3] = {h.x, h.y, h.z};
 #pragma unroll
-  for (int i = 0; i < NF; ++i) s.fs[i] = 0.0;
-  s.orv = 0;
-  for (long long b = b_lo + threadIdx.x; b <= b_hi; b += kThreads) {
-    const Partial* rec = tb.partials + (b + t);
+    for (int i = 0; i < NV; ++i) a.mx[i] = max(a.mx[i], m[i]);
+    a.orv |= h.w;
+    if constexpr (NC > 0) {
+      uint32_t c[8];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) s.mx[i] = max(s.mx[i], __hip_atomic_load(&rec->mx[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      for (int q = 1; q < (kQuads < 3 ? kQuads : 3); ++q) {
+        const uint4 k = rec[q];
+        c[4 * q - 4] = k.x; c[4 * q - 3] = k.y; c[4 * q - 2] = k.z; c[4 * q - 1] = k.w;
+      }
 #pragma unroll
-    for (int i = 0; i < NC; ++i) s.ct[i] += __hip_atomic_load(&rec->ct[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int i = 0; i < NF; ++i) s.fs[i] += __hip_atomic_load(&rec->fs[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s.orv |= __hip_atomic_load(&rec->orv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int i = 0; i < NC; ++i) a.ct[i] += c[i];
+    }
   }
-  block_combine(s);
-}
-
-// Called by all threads at the end of a workgroup's part of tensor t, after block_combine(s).  Returns
-// true in every thread of the workgroup that has to run the tensor's epilogue, with the tensor's totals in
-// thread 0's `s`; always false in the deferred form.
-template <int NV, int NC, int NF>
-__device__ __forceinline__ bool collect(const Tables& tb, int t, const TensorDesc& d, int done, BlockStats<NV, NC, NF>& s) {
-  if (tb.deferred) {
-    if (threadIdx.x == 0) store_record(tb, t, s);
-    return false;
+  __shared__ uint32_t l_m[kWaves][4];
+  __shared__ unsigned long long l_c[kWaves][NC > 0 ? NC : 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) a.mx[i] = wave_max_u32(a.mx[i]);
+  a.orv = wave_or_u32(a.orv);
+#pragma unroll
+  for (int i = 0; i < NC; ++i) a.ct[i] = wave_sum_u64(a.ct[i]);
+  __syncthreads();
+  if (lane == 63) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) l_m[wave][i] = a.mx[i];
+    l_m[wave][3] = a.orv;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) l_c[wave][i] = a.ct[i];
   }
-  __shared__ int l_last;
+  __syncthreads();
+  s = a;
   if (threadIdx.x == 0) {
-    store_record(tb, t, s);
-    Scratch* sc = tb.scratch + t;
-    const uint32_t old = __hip_atomic_fetch_add(&sc->ticket, (uint32_t)done, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    const bool last = old + (uint32_t)done == (uint32_t)d.n_chunks;
-    if (last) __hip_atomic_store(&sc->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
-    l_last = last;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) s.mx[i] = max(max(l_m[0][i], l_m[1][i]), max(l_m[2][i], l_m[3][i]));
+    s.orv = l_m[0][3] | l_m[1][3] | l_m[2][3] | l_m[3][3];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) s.ct[i] = l_c[0][i] + l_c[1][i] + l_c[2][i] + l_c[3][i];
+  }
+  static_assert(kWaves == 4, "four partial results");
+}
+
+// Adds `add` to a tensor's ticket; true in the workgroup that makes it `want`, which then sees everything the others wrote
+// before they came here.  Called by all threads after the first wavefront wrote what the others are to see.
+__device__ __forceinline__ bool ticket_last(const Tables& tb, int t, uint32_t add, uint32_t want) {
+  __shared__ int l_last;
+  if (threadIdx.x < 64) {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");        // the stores of all lanes of this wavefront
+    if (threadIdx.x == 0) {
+      uint32_t* ticket = &tb.scratch[t].ticket;
+      const bool last = __hip_atomic_fetch_add(ticket, add, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + add == want;
+      if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+      l_last = last;
+    }
   }
   __syncthreads();
   const bool last = l_last != 0;
-  __syncthreads();                 // l_last may be rewritten by the next flush
-  if (!last) return false;
-  gather_records(tb, t, d, gridDim.x, s);
-  return true;
+  __syncthreads();                 // l_last may be rewritten by the next call
+  if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  return last;
 }
 
-// The second launch of the deferred form: workgroup t finishes tensor t.
+__device__ __forceinline__ uint32_t units_of(const Tables& tb, const TensorDesc& d) {
+  return (uint32_t)((d.numel + tb.unit_elems - 1) / tb.unit_elems);
+}
+
+// Called by all threads at the end of unit u, a part of tensor t.  In the single-pass form the workgroup that completes
+// the tensor runs its scalar epilogue.
+template <int NV, int NC, class Op>
+__device__ __forceinline__ void collect(const Tables& tb, Op& op, int t, long long u, const BlockStats<NV, NC, uint32_t>& s) {
+  const uint4 r = block_combine(s);
+  constexpr int kStored = NC == 0 ? 1 : (NC <= 4 ? 2 : 3);
+  if (threadIdx.x < kStored) reinterpret_cast<uint4*>(tb.records + u * kRecordBytes<NC>)[threadIdx.x] = r;
+  if (tb.deferred) return;
+  const TensorDesc d = tb.desc[t];
+  const uint32_t n = units_of(tb, d);
+  if (!ticket_last(tb, t, 1u, n)) return;
+  const long long u0 = (long long)d.first_chunk << tb.unit_shift;
+  BlockStats<NV, NC> total;
+  gather_records(tb, u0, u0 + n, total);
+  if (threadIdx.x == 0) op.finalize(t, d, total);
+}
+
+// The second launch of the deferred form.
 template <class Op, class Params>
-__global__ __launch_bounds__(kThreads) void epilogue_kernel(Tables tb, Params p, int main_grid, int n_tensors) {
+__global__ __launch_bounds__(kThreads) void epilogue_kernel(Tables tb, Params p) {
   Op op(p, tb);
-  for (int t = blockIdx.x; t < n_tensors; t += gridDim.x) {
+  for (int i = blockIdx.x; i < tb.n_epi; i += gridDim.x) {
+    const int t = tb.epi_tensor[i];
     const TensorDesc d = tb.desc[t];
-    if (d.n_chunks == 0) continue;
-    op.begin(t, d);
+    if (d.n_chunks == 0) continue;               // (a list of tensors to be cast again leaves the others out)
+    const int K = epilogue_groups(d.n_chunks), k = i - d.epi0;
+    const long long n = units_of(tb, d), u0 = (long long)d.first_chunk << tb.unit_shift;
     typename Op::Stats s;
-    gather_records(tb, t, d, main_grid, s);
+    gather_records(tb, u0 + n * k / K, u0 + n * (k + 1) / K, s);
+    if (K > 1) {
+      constexpr int NV = Op::Stats::kNV, NC = Op::Stats::kNC;
+      if (threadIdx.x == 0) {
+        unsigned long long* w = tb.totals + (long long)i * kTotalWords;
+        for (int j = 0; j < NV; ++j) w[j] = s.mx[j];
+        w[3] = s.orv;
+        for (int j = 0; j < NC; ++j) w[4 + j] = s.ct[j];
+      }
+      if (!ticket_last(tb, t, 1u, (uint32_t)K)) continue;
+      if (threadIdx.x == 0) {
+        for (int j = 0; j < NV; ++j) s.mx[j] = 0;
+        for (int j = 0; j < NC; ++j) s.ct[j] = 0;
+        s.orv = 0;
+        for (int q = 0; q < K; ++q) {
+          const unsigned long long* w = tb.totals + (long long)(d.epi0 + q) * kTotalWords;
+          for (int j = 0; j < NV; ++j) s.mx[j] = max(s.mx[j], (uint32_t)w[j]);
+          s.orv |= (uint32_t)w[3];
+          for (int j = 0; j < NC; ++j) s.ct[j] += w[4 + j];
+        }
+      }
+    }
     if (threadIdx.x == 0) op.finalize(t, d, s);
   }
 }
 
-// ---- the chunk walk shared by all kernels -------------------------------------------------------
-// Op must provide: begin(t, desc); fast() (uniform: may the vector path be used for this tensor);
-// tiles<UN>(pos): UN complete 4096-element tiles starting at element `pos` of the flat buffers, handled
-// by the whole workgroup (all loads issued before the first use; the op chooses which 16 elements of
-// a tile a thread takes); full_group(pos): the 16 consecutive elements starting at `pos`, handled by the calling
-// thread alone with vector accesses (any subset of the threads may call it); group(pos, valid) with
-// 1 <= valid <= 16 for everything else, element by element; flush(t, desc, chunks_done) (called by all threads when the workgroup leaves tensor t: it fills
-// a Stats = BlockStats<..>, combines it over the workgroup and hands it to `collect`); and for the tensor's
-// scalar epilogue finalize(t, desc, stats), run by one thread once the totals of all workgroups are known.
+// ---- the walk shared by all kernels -------------------------------------------------------
+// Op must provide: begin(t); fast() (uniform: may the vector path be used for this tensor); Regs<UN>, the registers
+// of UN complete 4096-element tiles, with load(r, pos) (issues the loads of the tiles starting at element `pos` of the
+// flat buffers; does not depend on the tensor) and tiles(r, pos) (the rest, the whole workgroup together; the op chooses
+// which 16 elements of a tile a thread takes); full_group(pos): the 16 consecutive elements starting at `pos`, handled by
+// the calling thread alone with vector accesses (any subset of the threads may call it); group(pos, valid) with
+// 1 <= valid <= 16 for everything else, element by element; flush(t, unit) (called by all threads at the end of a
+// unit: it fills a BlockStats and hands it to `collect`); and for the tensor's scalar epilogue
+// finalize(t, desc, stats), run by one thread once the totals of all workgroups are known.
+//
+// Order of the walk.  By default a workgroup takes one unit (UN tiles) and ends: the dispatcher starts workgroups in order, so
+// at any time the chip works on a few hundred neighbouring tiles of every buffer, a window that sweeps through memory and
+// finds the DRAM rows it needs open.  A persistent grid in which every workgroup walked a range of its own (or a
+// round-robin share: the workgroups drift apart) touched a few thousand places at once and lost more the more it wrote:
+// XOR-only traffic of 1.8e9 elements in one HBM region, TB/s, persistent / one tile per workgroup: update shape 5.13 / 5.5
+// (5.9 with two or three workgroups per compute unit), cast shape 5.37 / 6.45, one-to-one copy 5.23 / 6.54, reads alone
+// 6.95 / 6.95.  Two tiles per workgroup cost 5 % of the cast shape, four consecutive ones 2 to 8 % of the update shape.
 template <int UN, class Op>
-__device__ __forceinline__ void walk_chunks(const Tables& tb, Op& op) {
-  // workgroup b walks the contiguous chunk range [b*C/G, (b+1)*C/G): `collect` relies on this mapping
-  // With fewer chunks than workgroups (a chunk list built on the device) only the first C workgroups take part, so
-  // that every one of them owns a chunk and leaves a record wherever `gather_records` expects one.
-  const long long C = chunk_count(tb), b = blockIdx.x;
-  const long long G = C < (long long)gridDim.x ? C : (long long)gridDim.x;
-  if (b >= G) return;
-  long long c = b * C / G;
-  const long long c_end = (b + 1) * C / G;
-  int cur = -1, done = 0;
-  TensorDesc d{};
-  // the tensor id of the next chunk is fetched one iteration ahead, so its latency hides behind the body
-  int t_next = c < c_end ? tb.chunk_tensor[c] : -1;
-  for (; c < c_end; ++c) {
-    const int t = t_next;
-    t_next = c + 1 < c_end ? tb.chunk_tensor[c + 1] : -1;
-    if (t != cur) {
-      if (cur >= 0) op.flush(cur, d, done);
-      cur = t;
-      done = 0;
-      d = tb.desc[t];
-      op.begin(t, d);
+__device__ __forceinline__ void walk_unit(const Tables& tb, Op& op, long long u) {
+  const ChunkDesc c = uniform_load(tb.chunks + (u >> tb.unit_shift));
+  const int e0 = ((int)u & ((1 << tb.unit_shift) - 1)) * tb.unit_elems;
+  const int len = min(c.len - e0, tb.unit_elems);
+  if (len <= 0) return;                        // the last chunk of a tensor can have fewer units
+  const int t = c.tensor;
+  const long long base = c.base + e0;
+  const int ntiles = len / kTile;
+  // the loads of the first tiles go out before anything about the tensor but its address is known
+  typename Op::template Regs<UN> r;
+  if (ntiles >= UN) op.load(r, base);
+  op.begin(t);
+  int tile = 0;
+  if (op.fast()) {
+    while (tile + UN <= ntiles) {
+      op.tiles(r, base + (long long)tile * kTile);
+      tile += UN;
+      if (tile + UN <= ntiles) op.load(r, base + (long long)tile * kTile);
     }
-    const long long e0 = (long long)((int)c - d.first_chunk) * tb.chunk_elems;
-    const long long rest = d.numel - e0;
-    const int len = rest < tb.chunk_elems ? (int)rest : tb.chunk_elems;
-    const long long base = d.offset + e0;
-    const int ntiles = len / kTile;
-    int tile = 0;
-    if (op.fast()) {
-      if constexpr (UN > 1)
-        for (; tile + UN <= ntiles; tile += UN) op.template tiles<UN>(base + (long long)tile * kTile);
-      for (; tile < ntiles; ++tile) op.template tiles<1>(base + (long long)tile * kTile);
+    if constexpr (UN > 1) {
+      for (; tile < ntiles; ++tile) {
+        typename Op::template Regs<1> q;
+        op.load(q, base + (long long)tile * kTile);
+        op.tiles(q, base + (long long)tile * kTile);
+      }
     }
-    // what is left of the chunk (less than a tile; a whole small tensor): complete 16-element groups still take
-    // 128-bit accesses, only the last, incomplete group of a tensor goes element by element
-    for (int i = tile * kTile + threadIdx.x * kGroup; i < len; i += kTile) {
-      const int valid = len - i < kGroup ? len - i : kGroup;
-      if (valid == kGroup && op.fast()) op.full_group(base + i);
-      else op.group(base + i, valid);
-    }
-    ++done;
   }
-  if (cur >= 0) op.flush(cur, d, done);
+  // what is left (less than a tile; a whole small tensor): complete 16-element groups still take
+  // 128-bit accesses, only the last, incomplete group of a tensor goes element by element
+  for (int i = tile * kTile + threadIdx.x * kGroup; i < len; i += kTile) {
+    const int valid = len - i < kGroup ? len - i : kGroup;
+    if (valid == kGroup && op.fast()) op.full_group(base + i);
+    else op.group(base + i, valid);
+  }
+  op.flush(t, u);
+}
+
+template <int UN, class Op>
+__device__ __forceinline__ void walk_units(const Tables& tb, Op& op) {
+  long long u = blockIdx.x, end = u + 1;
+  if (!tb.one_unit) {
+    const long long U = chunk_count(tb) << tb.unit_shift, b = blockIdx.x, G = gridDim.x;
+    u = b * U / G;
+    end = (b + 1) * U / G;
+  }
+  for (; u < end; ++u) walk_unit<UN>(tb, op, u);
 }
 
 // Build-time tuning knobs (defaults are the measured best on MI355X).
@@ -302,31 +405,17 @@ __device__ __forceinline__ void walk_chunks(const Tables& tb, Op& op) {
                           // measured best with the split access layout (bits 2+3 together: -1 % on the update
                           // kernel; bit 3 alone: +0.7 %)
 #endif
-#ifndef FP8LM_UN_READ
-#define FP8LM_UN_READ 4   // 16-element groups a thread keeps in flight in the read-only kernels
-#endif
-#ifndef FP8LM_UN_CAST
-#define FP8LM_UN_CAST 2
-#endif
-#ifndef FP8LM_UN_UPDATE
-#define FP8LM_UN_UPDATE 1
-#endif
-#ifndef FP8LM_SINGLE_PASS_MIN_CHUNKS
-#define FP8LM_SINGLE_PASS_MIN_CHUNKS (1 << 30)   // launches with fewer chunks per workgroup finish their tensors in
-                                                 // a second launch instead of through tickets (see collect); the
-                                                 // default never uses tickets: the second launch measured faster
-                                                 // at every size, 2 % on the read-only kernels even at 13e9 parameters
-#endif
-#ifndef FP8LM_CAST_SPLIT
-#define FP8LM_CAST_SPLIT 1     // cast kernel, 16-bit sources: the same split layout as the update kernel
-#endif
-#ifndef FP8LM_CAST_STORE16
-#define FP8LM_CAST_STORE16 0   // cast kernel, split layout: neighbouring lanes swap halves so that each stores 128 bits once
-#endif
-#ifndef FP8LM_UPDATE_SPLIT
-#define FP8LM_UPDATE_SPLIT 1   // update kernel: a thread takes elements [8L, 8L+8) of both halves of a tile, so
-                               // that every access of the workgroup is contiguous (0: 16 consecutive elements)
-#endif
+// Tiles a workgroup takes at once (all their loads are issued before the first is used).  One tile keeps the window of
+// walk_units smallest, but then a workgroup's fixed costs (the chain table -> data, two barriers, the record) come once per 4096
+// elements: cast of GPT-125M with bf16 gradients, 1 / 2 / 4 tiles: 69 / 62 / 71 us (4: 207 registers, two wavefronts
+// per SIMD); re-quantisation 55 / 48 / 47 us; cast of fp32 gradients (201e6 elements) 228 / 240 us for 1 / 2.  The update pass
+// does 40 to 70 instructions per element in the meantime and has no registers for a second tile.
+constexpr int kUnRead = 4;
+template <int SRC> constexpr int kUnCast = 2;
+template <> constexpr int kUnCast<2> = 1;        // fp32 sources
+constexpr int kUnRequant = 4;
+constexpr int kUnUpdate = 1;
+__host__ __device__ constexpr int sum_tiles(int ranks) { return ranks == 0 ? 1 : ranks <= 2 ? 4 : ranks <= 4 ? 2 : 1; }
 constexpr bool kNtLoadRO = (FP8LM_NT_MASK & 1) != 0, kNtStoreWO = (FP8LM_NT_MASK & 2) != 0;
 constexpr bool kNtLoadRW = (FP8LM_NT_MASK & 4) != 0, kNtStoreRW = (FP8LM_NT_MASK & 8) != 0;
 

@@ -69,12 +69,12 @@ def probe_ms(ctx, a: torch.Tensor, b: torch.Tensor, n: Optional[int] = None, rep
     v, w = a[:2 * n].view(torch.int16), a[2 * n:4 * n].view(torch.int16)
     g, m, q = b[:n], b[n:2 * n], b[2 * n:3 * n]
     bufs = [g, m, v, w, q]
-    ctx.memory_skeleton(B.SKEL_UPDATE, bufs, n)
+    ctx.memory_skeleton(B.SKEL_UPDATE_RANGES, bufs, n)
     torch.cuda.synchronize()
     ctx.set_timing(True)
     ctx.get_timing()
     for _ in range(reps):
-        ctx.memory_skeleton(B.SKEL_UPDATE, bufs, n)
+        ctx.memory_skeleton(B.SKEL_UPDATE_RANGES, bufs, n)
     k, ms = ctx.get_timing()["skeleton"]
     ctx.set_timing(False)
     return ms / k
