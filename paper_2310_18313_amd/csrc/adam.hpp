@@ -82,13 +82,13 @@ struct InitCastOp {
     }
   }
   using Stats = BlockStats<1, 2>;
-  __device__ __forceinline__ void flush(int t, long long u) {
+  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<1, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.ct[0] = n_sat;
     s.ct[1] = n_und;
     s.orv = 0;
-    collect(tb, *this, t, u, s);
+    collect<FINISH>(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -269,7 +269,6 @@ __global__ void adam_speculate_scales_kernel(Tables tb, AdamParams p, int n) {
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n || tb.desc[t].numel == 0) return;
   Scratch& S = tb.scratch[t];
-  S.redo = 0;
   S.old_scale = p.m_meta[t].scale;
   S.old_inv = p.m_meta[t].inv_scale;
   adam_choose_scales<WCOPY>(p, S.pend, t, tb.desc[t].flags, p.m_meta[t].amax);
@@ -332,11 +331,11 @@ struct AdamAmaxOp {
     for (int j = 0; j < valid; ++j) elem(fp8_to_f32<GFMT>(p.grad[pos + j]), fp8_to_f32<kE4M3>(p.m[pos + j]));
   }
   using Stats = BlockStats<1, 0>;
-  __device__ __forceinline__ void flush(int t, long long u) {
+  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<1, 0, uint32_t> s;
     s.mx[0] = acc;
     s.orv = 0;
-    collect(tb, *this, t, u, s);
+    collect<FINISH>(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const uint32_t abits = s.mx[0];
@@ -597,7 +596,7 @@ struct AdamUpdateOp {
   }
 
   using Stats = BlockStats<3, STATS ? 8 : 0>;
-  __device__ __forceinline__ void flush(int t, long long u) {
+  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<3, STATS ? 8 : 0, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = f2u(wmax);
@@ -608,15 +607,15 @@ struct AdamUpdateOp {
       for (int i = 0; i < 8; ++i) s.ct[i] = cnt[i] + (first_lane ? wcnt[i] : 0u);
     }
     s.orv = nf;
-    collect(tb, *this, t, u, s);
+    collect<FINISH>(tb, *this, t, u, s);
   }
-  __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
+  __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     unsigned long long c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     if constexpr (STATS) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) c[i] = s.ct[i];
     }
-    finish(t, u2f(s.mx[0]), u2f(s.mx[1]), u2f(s.mx[2]), s.orv, c);
+    finish(t, d, u2f(s.mx[0]), u2f(s.mx[1]), u2f(s.mx[2]), s.orv, c);
   }
 
   // Fills one output meta.  amax_deq is the stored value of the largest element: rounding is monotone,
@@ -644,7 +643,7 @@ struct AdamUpdateOp {
     M.n_underflow = STATS ? n_und : 0;
   }
 
-  __device__ void finish(int t, float A_v, float A_w, float A_mc, uint32_t nfb, const unsigned long long* c) {
+  __device__ void finish(int t, const TensorDesc& d, float A_v, float A_w, float A_mc, uint32_t nfb, const unsigned long long* c) {
     Scratch::Pending& P = tb.scratch[t].pend;
     const float A_m = A_mc;    // measured by this pass on both paths (equals what pass A saw)
     uint32_t m_nf = nfb & 3u;
@@ -656,7 +655,7 @@ struct AdamUpdateOp {
       float sm = 0.0f, ism = 0.0f;
       uint32_t fm = 0;
       refresh_scale(kBitsE4M3Max, m_nf ? __builtin_inff() : A_m, 0, tb.scratch[t].old_scale, tb.scratch[t].old_inv, sm, ism, fm);
-      tb.scratch[t].redo = sm != P.sm ? 1u : 0u;
+      mark_redo(tb, t, d, sm != P.sm);
       P.sm = sm;
       P.ism = ism;
       P.fm = fm;
@@ -686,7 +685,7 @@ __global__ __launch_bounds__(kThreads) void adam_update_kernel(Tables tb, AdamPa
 }
 
 // ---- repair of a failed first-moment speculation ---------------------------------------------------
-// Walks the chunk list of the marked tensors: m' = fma(beta1, m_in / s_m, (1-beta1) * g / s_g) once more, stored to
+// Walks the marked tensors: m' = fma(beta1, m_in / s_m, (1-beta1) * g / s_g) once more, stored to
 // m with the exact scale that the update pass's epilogue left in the scratch.
 template <int GFMT>
 struct AdamMomentRedoOp {
@@ -696,10 +695,10 @@ struct AdamMomentRedoOp {
   bool careful;
   __device__ AdamMomentRedoOp(const AdamParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
   __device__ __forceinline__ void begin(int t) {
-    inv_sg = p.grad_meta[t].inv_scale;
-    inv_sm = tb.scratch[t].old_inv;                 // the scale m_in is stored with (m_meta already holds the new one)
-    sm = tb.scratch[t].pend.sm;
-    careful = tb.scratch[t].pend.careful != 0;
+    inv_sg = uniform_load(&p.grad_meta[t].inv_scale);
+    inv_sm = uniform_load(&tb.scratch[t].old_inv);  // the scale m_in is stored with (m_meta already holds the new one)
+    sm = uniform_load(&tb.scratch[t].pend.sm);
+    careful = uniform_load(&tb.scratch[t].pend.careful) != 0;
   }
   __device__ __forceinline__ float moment(float dg, float dm) const {
     return __builtin_fmaf(p.b1, dm * inv_sm, p.omb1 * (dg * inv_sg));
@@ -732,15 +731,16 @@ struct AdamMomentRedoOp {
       p.m[i] = (uint8_t)encode1_fp8_careful<kE4M3>(moment(fp8_to_f32<GFMT>(p.grad[i]), fp8_to_f32<kE4M3>(p.m_in[i])) * sm);
     }
   }
+  static constexpr bool kFinishes = false;     // nothing to reduce: the metadata is complete
   using Stats = BlockStats<1, 0>;
-  __device__ __forceinline__ void flush(int, long long) {}      // nothing to reduce: the metadata is complete
+  template <bool FINISH> __device__ __forceinline__ void flush(int, long long) {}
   __device__ void finalize(int, const TensorDesc&, const Stats&) {}
 };
 
 template <int GFMT>
 __global__ __launch_bounds__(kThreads) void adam_moment_redo_kernel(Tables tb, AdamParams p) {
   AdamMomentRedoOp<GFMT> op(p, tb);
-  walk_units<1>(tb, op);
+  walk_marked<kUnUpdate>(tb, op);
 }
 
 // ---- pass B for the other storage formats of the precision-decoupling study ----------------------
@@ -855,13 +855,13 @@ struct AdamUpdateVarOp {
     M.n_underflow = 0;
   }
   using Stats = BlockStats<3, 0>;
-  __device__ __forceinline__ void flush(int t, long long u) {
+  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<3, 0, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = f2u(wmax);
     s.mx[2] = f2u(mmax);
     s.orv = nf;
-    collect(tb, *this, t, u, s);
+    collect<FINISH>(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float A_v = u2f(s.mx[0]), A_w = u2f(s.mx[1]), A_m = u2f(s.mx[2]);

@@ -54,7 +54,7 @@ struct StaticArena {
   Scratch scratch[FP8LM_STATIC_MAX_TENSORS];              // 512 KiB
   unsigned char records[kStaticRecords];                  // 4 MiB
   unsigned long long totals[(size_t)kStaticEpilogue * kTotalWords];   // 528 KiB
-  int32_t epi_tensor[kStaticEpilogue];                    // 16.5 KiB
+  EpilogueDesc epi[kStaticEpilogue];                      // 198 KiB
   ChunkDesc chunks[kStaticChunks];                        // 1 MiB
 };
 
@@ -81,6 +81,8 @@ using namespace fp8lm;
 
 static thread_local std::string g_hip_error;
 
+constexpr int32_t kLibraryChooses = 1 << 30;      // default of single_pass_min_chunks
+
 struct fp8lm_ctx {
   int device = 0;
   int n_tensors = 0;
@@ -89,7 +91,7 @@ struct fp8lm_ctx {
   std::vector<uint32_t> tensor_flags;   // FP8LM_TENSOR_* per tensor
   int32_t chunk_elems = 16384;
   int32_t blocks_per_cu = kMaxBlocksPerCu;
-  int32_t single_pass_min_chunks = 1 << 30;
+  int32_t single_pass_min_chunks = kLibraryChooses;
   int32_t n_chunks = 0;
   TensorDesc* d_desc = nullptr;
   ChunkDesc* d_chunks = nullptr;
@@ -97,14 +99,14 @@ struct fp8lm_ctx {
   unsigned char* d_records = nullptr;   // one record per unit
   size_t record_bytes = 0;
   unsigned long long* d_totals = nullptr;
-  int32_t* d_epi_tensor = nullptr;
+  EpilogueDesc* d_epi = nullptr;
   int32_t n_epi = 0;
   Partial* d_partials = nullptr;    // [num_cus * kMaxBlocksPerCu + n_tensors], error statistics
-  // speculative quantisation: tensor and chunk tables of the tensors that have to be cast again, their chunk
-  // count, and running totals (calls, tensors cast twice, elements cast twice)
-  TensorDesc* d_redo_desc = nullptr;
-  ChunkDesc* d_redo_chunks = nullptr;
-  int32_t* d_redo_count = nullptr;
+  // speculation: number of the last call and, on the device, of the last one that marked a tensor; running totals (calls,
+  // tensors done again, elements done again) for the gradient and for the first moment
+  uint32_t spec_call = 0;
+  uint32_t* d_marked_call = nullptr;
+  int spec_kind = 0;                    // what the call speculates about: 0 gradient scales, 1 first-moment scales
   unsigned long long* d_spec_totals = nullptr;
   // what the last fused cast measured for (checked by the Adam step that wants to use it)
   struct Fused { bool valid; const uint8_t* grad; const uint8_t* m; const fp8lm_meta* m_meta; float b1; int fmt; };
@@ -139,9 +141,19 @@ struct DeviceGuard {
 };
 
 void free_tables(fp8lm_ctx* c) {
-  for (void* p : {(void*)c->d_desc, (void*)c->d_chunks, (void*)c->d_epi_tensor, (void*)c->d_redo_desc,
-                  (void*)c->d_redo_chunks, (void*)c->d_records, (void*)c->d_totals})
+  for (void* p : {(void*)c->d_desc, (void*)c->d_chunks, (void*)c->d_epi, (void*)c->d_records, (void*)c->d_totals})
     if (p) (void)hipFree(p);
+}
+
+// Elements per chunk of a context (or a call without one) that has not been given a tuning: 16384, which keeps the chunk
+// table small, unless the tensors are so small that most of the units such chunks are cut into would be empty.
+template <class NumelOf> int32_t default_chunk(int n, NumelOf numel_of) {
+  long long chunks = 0, tiles = 0;
+  for (int t = 0; t < n; ++t) {
+    chunks += (numel_of(t) + 4 * kTile - 1) / (4 * kTile);
+    tiles += (numel_of(t) + kTile - 1) / kTile;
+  }
+  return 4 * chunks > tiles + tiles / 4 ? kTile : 4 * kTile;
 }
 
 // Builds the tensor and chunk tables for chunks of chunk_elems elements and installs them.  On failure the
@@ -163,18 +175,14 @@ fp8lm_status build_tables(fp8lm_ctx* c, int32_t chunk_elems) {
   // everything in one list, so that a failure gives back what had been allocated
   struct Piece { void** at; size_t bytes; const void* from; };
   TensorDesc* d_desc = nullptr;
-  TensorDesc* d_redo_desc = nullptr;
   ChunkDesc* d_chunks = nullptr;
-  ChunkDesc* d_redo_chunks = nullptr;
-  int32_t* d_epi_tensor = nullptr;
+  EpilogueDesc* d_epi = nullptr;
   unsigned char* d_records = nullptr;
   unsigned long long* d_totals = nullptr;
   const Piece pieces[] = {
       {(void**)&d_desc, desc.size() * sizeof(TensorDesc), desc.data()},
       {(void**)&d_chunks, (size_t)total_chunks * sizeof(ChunkDesc), nullptr},
-      {(void**)&d_epi_tensor, (size_t)n_epi * sizeof(int32_t), nullptr},
-      {(void**)&d_redo_desc, desc.size() * sizeof(TensorDesc), nullptr},
-      {(void**)&d_redo_chunks, (size_t)total_chunks * sizeof(ChunkDesc), nullptr},
+      {(void**)&d_epi, (size_t)n_epi * sizeof(EpilogueDesc), nullptr},
       {(void**)&d_records, record_bytes, nullptr},
       {(void**)&d_totals, (size_t)n_epi * kTotalWords * sizeof(unsigned long long), nullptr},
   };
@@ -185,7 +193,7 @@ fp8lm_status build_tables(fp8lm_ctx* c, int32_t chunk_elems) {
   }
   if (e == hipSuccess && total_chunks > 0) {     // the per-chunk tables are written on the device
     hipLaunchKernelGGL(chunk_tables_kernel, dim3(std::min(c->n_tensors, 1024)), dim3(kThreads), 0, nullptr, d_desc, d_chunks,
-                       d_epi_tensor, c->d_scratch, chunk_elems, c->n_tensors);
+                       d_epi, c->d_scratch, chunk_elems, c->n_tensors);
     e = hipGetLastError();
     if (e == hipSuccess) e = hipDeviceSynchronize();
   }
@@ -198,9 +206,7 @@ fp8lm_status build_tables(fp8lm_ctx* c, int32_t chunk_elems) {
   free_tables(c);
   c->d_desc = d_desc;
   c->d_chunks = d_chunks;
-  c->d_epi_tensor = d_epi_tensor;
-  c->d_redo_desc = d_redo_desc;
-  c->d_redo_chunks = d_redo_chunks;
+  c->d_epi = d_epi;
   c->d_records = d_records;
   c->d_totals = d_totals;
   c->record_bytes = record_bytes;
@@ -229,7 +235,11 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   tb.scratch = c->d_scratch;
   tb.records = c->d_records;
   tb.totals = c->d_totals;
-  tb.epi_tensor = c->d_epi_tensor;
+  tb.epi = c->d_epi;
+  tb.n_tensors = c->n_tensors;
+  tb.call = c->spec_call;
+  tb.marked_call = c->d_marked_call;
+  tb.spec_totals = c->d_spec_totals ? c->d_spec_totals + 3 * c->spec_kind : nullptr;
   tb.n_epi = c->n_epi;
   tb.n_chunks = c->n_chunks;
   tb.unit_elems = c->chunk_elems;
@@ -243,20 +253,20 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
     tb.one_unit = units() <= kMaxGrid;
   }
   *grid = tb.one_unit ? (int)units() : grid_of(c);
-  // in the deferred form the second launch finishes the tensors; see walk.hpp for the two forms' costs
-  tb.deferred = c->single_pass_min_chunks > 0 && c->n_chunks / grid_of(c) < c->single_pass_min_chunks;
+  // In the deferred form a second launch finishes the tensors; see walk.hpp for the two forms' costs.  Unless told otherwise
+  // tickets are for launches of at most 64 units: a step of 2^18 parameters (64 units) takes 26.7 us with and 35.9 without
+  // them, one of 50 tensors with 66 000 elements in all 31.2 and 44.2; at 256 units 37.4 and 36.2, at 1024 141 and 36.
+  constexpr int kTicketUnits = 64;
+  tb.deferred = c->single_pass_min_chunks == kLibraryChooses
+                    ? units() > kTicketUnits
+                    : c->single_pass_min_chunks > 0 && c->n_chunks / grid_of(c) < c->single_pass_min_chunks;
   return tb;
 }
-// The tables of the tensors a speculative quantisation has to cast again: built on the device, so the number of
-// chunks is only known there; a persistent grid, tensors always finished by the second launch.
-Tables redo_tables_of(const fp8lm_ctx* c, int record, int* grid) {
-  Tables tb = tables_of(c, 1, record, grid);
-  tb.desc = c->d_redo_desc;
-  tb.chunks = c->d_redo_chunks;
-  tb.n_chunks_dev = c->d_redo_count;
-  tb.one_unit = 0;
-  tb.deferred = 1;
-  *grid = (int)std::min<long long>((long long)c->num_cus * 8, (long long)c->n_chunks << tb.unit_shift);
+// The tables and the grid of the second round of a speculation (walk_marked); `un` and `record` as for the first.
+Tables marked_tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
+  Tables tb = tables_of(c, un, record, grid);
+  tb.deferred = ((long long)c->n_chunks << tb.unit_shift) > 256;
+  *grid = (int)std::min<long long>(4ll * c->num_cus, (long long)c->n_chunks << tb.unit_shift);
   return tb;
 }
 
@@ -298,6 +308,13 @@ void launch_walk_on(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p,
   const dim3 b(kThreads);
   hipLaunchKernelGGL(kernel, dim3(grid), b, 0, s, tb, p);
   if (tb.deferred) hipLaunchKernelGGL((epilogue_kernel<Op, Params>), dim3(std::min<int>(c->n_epi, 8 * c->num_cus)), b, 0, s, tb, p);
+}
+// The same for the second round of a speculation.
+template <class Op, class Params, class Kernel>
+void launch_marked(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, const Tables& tb, int grid) {
+  const dim3 b(kThreads);
+  hipLaunchKernelGGL(kernel, dim3(grid), b, 0, s, tb, p);
+  if (tb.deferred) hipLaunchKernelGGL((epilogue_kernel<Op, Params, true>), dim3(std::min<int>(c->n_epi, 8 * c->num_cus)), b, 0, s, tb, p);
 }
 template <class Op, class Params, class Kernel>
 void launch_walk(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, int un = 1) {
@@ -404,13 +421,14 @@ fp8lm_status fp8lm_create(fp8lm_ctx** out, const fp8lm_tensor* tensors, int32_t 
   hipError_t e = hipMalloc((void**)&c->d_scratch, bytes);
   if (e == hipSuccess) e = hipMemset(c->d_scratch, 0, bytes);
   if (e != hipSuccess) g_hip_error = hipGetErrorString(e);
+  c->chunk_elems = default_chunk(n, [&](int t) { return tensors[t].numel; });
   fp8lm_status st = e == hipSuccess ? build_tables(c, c->chunk_elems) : FP8LM_ERR_HIP;
   if (st == FP8LM_OK) {
     const size_t records = (size_t)c->num_cus * kMaxBlocksPerCu + (size_t)n + 1;
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_partials, records * sizeof(Partial));
     if (e == hipSuccess) e = hipMemset(c->d_partials, 0, records * sizeof(Partial));
-    if (e == hipSuccess) e = hipMalloc((void**)&c->d_redo_count, sizeof(int32_t));
-    if (e == hipSuccess) e = hipMemset(c->d_redo_count, 0, sizeof(int32_t));
+    if (e == hipSuccess) e = hipMalloc((void**)&c->d_marked_call, sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMemset(c->d_marked_call, 0, sizeof(uint32_t));
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_spec_totals, 6 * sizeof(unsigned long long));     // gradient, first moment
     if (e == hipSuccess) e = hipMemset(c->d_spec_totals, 0, 6 * sizeof(unsigned long long));
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -427,7 +445,7 @@ fp8lm_status fp8lm_destroy(fp8lm_ctx* c) {
   free_tables(c);
   if (c->d_scratch) (void)hipFree(c->d_scratch);
   if (c->d_partials) (void)hipFree(c->d_partials);
-  if (c->d_redo_count) (void)hipFree(c->d_redo_count);
+  if (c->d_marked_call) (void)hipFree(c->d_marked_call);
   if (c->d_spec_totals) (void)hipFree(c->d_spec_totals);
   for (auto& s : c->stamps) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
   for (auto& e : c->free_events) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
@@ -504,17 +522,9 @@ static fp8lm_status cast_impl(fp8lm_ctx* c, const void* src, fp8lm_src src_type,
   DeviceGuard guard(c->device);
   hipStream_t s = (hipStream_t)stream;
   const uint32_t fmax_bits = fmt == FP8LM_E4M3 ? kBitsE4M3Max : kBitsE5M2Max;
-  if (delayed) {
-    Timed tm(c, s, FP8LM_K_SCALARS);
-    const dim3 gs((c->n_tensors + 255) / 256), bs(256);
-    if (mode == kCastSpeculative)
-      hipLaunchKernelGGL(speculate_scale_kernel, gs, bs, 0, s, c->d_desc, meta, c->d_scratch, c->n_tensors, fmax_bits,
-                         cfg->hist_window, cfg->margin);
-    else
-      hipLaunchKernelGGL(delayed_scale_kernel, gs, bs, 0, s, c->d_desc, meta, c->n_tensors, fmax_bits, cfg->hist_window,
-                         cfg->margin);
-    fp8lm_status st = after_launch();
-    if (st != FP8LM_OK) return st;
+  if (mode == kCastSpeculative) {
+    ++c->spec_call;
+    c->spec_kind = 0;
   }
   CastParams p{};
   p.speculative = mode == kCastSpeculative ? 1 : 0;
@@ -551,24 +561,16 @@ static fp8lm_status cast_impl(fp8lm_ctx* c, const void* src, fp8lm_src src_type,
   }
   fp8lm_status st = after_launch();
   if (st == FP8LM_OK && mode == kCastSpeculative) {
-    // the tensors whose scale turned out different: their chunk list, then the plain cast over that list
+    // the tensors whose scale turned out different, with the plain cast
     {
-      Timed tm(c, s, FP8LM_K_SCALARS);
-      hipLaunchKernelGGL(redo_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, c->d_desc, c->d_scratch, c->d_redo_desc,
-                         c->n_tensors, c->d_redo_count, c->d_spec_totals);
-      hipLaunchKernelGGL(redo_fill_kernel, dim3(std::min<int>(c->n_tensors, 1024)), dim3(256), 0, s, c->d_desc,
-                         c->d_redo_desc, c->d_chunks, c->d_redo_chunks, c->n_tensors);
-      st = after_launch();
-    }
-    if (st == FP8LM_OK) {
-      int redo_grid = 0;
-      const Tables rt = redo_tables_of(c, 32, &redo_grid);
+      int grid = 0;
+      const Tables rt = marked_tables_of(c, src_type == FP8LM_SRC_F32 ? kUnCast<kSrcF32> : kUnCast<kSrcBF16>, 32, &grid);
       p.speculative = 0;
       Timed tm(c, s, FP8LM_K_CAST);
 #define FP8LM_REDO_LAUNCH(F, S)                                                                            \
       do {                                                                                                  \
-        if (fuse) launch_walk_on<CastOp<F, false, true, S>>(c, s, cast_kernel<F, false, true, S>, p, rt, redo_grid);   \
-        else launch_walk_on<CastOp<F, false, false, S>>(c, s, cast_kernel<F, false, false, S>, p, rt, redo_grid);      \
+        if (fuse) launch_marked<CastOp<F, false, true, S>>(c, s, cast_marked_kernel<F, true, S>, p, rt, grid);    \
+        else launch_marked<CastOp<F, false, false, S>>(c, s, cast_marked_kernel<F, false, S>, p, rt, grid);       \
       } while (0)
 #define FP8LM_REDO_SRC(S)                                                                                  \
       do {                                                                                                  \
@@ -827,6 +829,10 @@ static fp8lm_status adam_launch(fp8lm_ctx* c, const uint8_t* grad, fp8lm_fmt gra
   p.speculative_m = spec_m ? 1 : 0;
 
   const bool stats = hp->stats != 0, fast = hp->exact == 0;
+  if (spec_m) {
+    ++c->spec_call;
+    c->spec_kind = 1;
+  }
   int grid = 0;
   const Tables tb = tables_of(c, 1, 16, &grid);      // for the per-tensor kernels, which only need the tables
   const bool e5 = grad_fmt == FP8LM_E5M2, q8 = hp->wcopy == FP8LM_WCOPY_E4M3;
@@ -870,20 +876,11 @@ static fp8lm_status adam_launch(fp8lm_ctx* c, const uint8_t* grad, fp8lm_fmt gra
   }
   st = after_launch();
   if (st != FP8LM_OK || !spec_m) return st;
-  // tensors whose first-moment scale turned out different: their chunk list, then the moment once more
+  // tensors whose first-moment scale turned out different: the moment once more
   {
-    Timed tm(c, s, FP8LM_K_SCALARS);
-    hipLaunchKernelGGL(redo_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, c->d_desc, c->d_scratch, c->d_redo_desc,
-                       c->n_tensors, c->d_redo_count, c->d_spec_totals + 3);
-    hipLaunchKernelGGL(redo_fill_kernel, dim3(std::min<int>(c->n_tensors, 1024)), dim3(256), 0, s, c->d_desc,
-                       c->d_redo_desc, c->d_chunks, c->d_redo_chunks, c->n_tensors);
-    st = after_launch();
-    if (st != FP8LM_OK) return st;
-  }
-  {
-    int redo_grid = 0;
-    const Tables rt = redo_tables_of(c, 16, &redo_grid);
-    const dim3 g(redo_grid), b(kThreads);
+    int grid = 0;
+    const Tables rt = marked_tables_of(c, kUnUpdate, 16, &grid);
+    const dim3 g(grid), b(kThreads);
     Timed tm(c, s, FP8LM_K_ADAM_AMAX);
     if (e5) hipLaunchKernelGGL((adam_moment_redo_kernel<kE5M2>), g, b, 0, s, rt, p);
     else hipLaunchKernelGGL((adam_moment_redo_kernel<kE4M3>), g, b, 0, s, rt, p);
@@ -1003,8 +1000,8 @@ fp8lm_status fp8lm_adam_step_fp8_static(int device, const fp8lm_tensor* tensors,
   // 1. the tensor table, a batch of descriptors per launch, then the chunk table
   DescBatch batch;
   int32_t first_chunk = 0, first_epi = 0;
-  // chunks of 16384 elements or, where the units of a launch would be too many for the records, larger ones
-  int32_t chunk_elems = kStaticChunkElems;
+  // the usual chunks or, where the units of a launch would be too many for the records, larger ones
+  int32_t chunk_elems = default_chunk(n, [&](int t) { return tensors[t].numel; });
   auto chunks_of = [&](int64_t numel) { return (numel + chunk_elems - 1) / chunk_elems; };
   for (;; chunk_elems *= 2) {
     total_chunks = 0;
@@ -1024,7 +1021,7 @@ fp8lm_status fp8lm_adam_step_fp8_static(int device, const fp8lm_tensor* tensors,
     for (int i = batch.count; i < kDescBatch; ++i) batch.d[i] = TensorDesc{0, 0, 0, 0, 0u, 0};
     hipLaunchKernelGGL(static_desc_kernel, dim3(1), dim3(kDescBatch), 0, s, batch, A->desc);
   }
-  hipLaunchKernelGGL(chunk_tables_kernel, dim3(std::min(n, 1024)), dim3(kThreads), 0, s, A->desc, A->chunks, A->epi_tensor, A->scratch,
+  hipLaunchKernelGGL(chunk_tables_kernel, dim3(std::min(n, 1024)), dim3(kThreads), 0, s, A->desc, A->chunks, A->epi, A->scratch,
                      chunk_elems, n);
   fp8lm_status st = after_launch();
   if (st != FP8LM_OK) return st;
@@ -1035,7 +1032,6 @@ fp8lm_status fp8lm_adam_step_fp8_static(int device, const fp8lm_tensor* tensors,
   view.n_tensors = n;
   view.num_cus = dev.num_cus;
   view.chunk_elems = chunk_elems;
-  view.single_pass_min_chunks = 1 << 30;     // per-tensor totals in a second launch: no tickets to keep at zero
   view.n_chunks = (int32_t)total_chunks;
   view.d_desc = A->desc;
   view.d_chunks = A->chunks;
@@ -1043,7 +1039,7 @@ fp8lm_status fp8lm_adam_step_fp8_static(int device, const fp8lm_tensor* tensors,
   view.d_records = A->records;
   view.record_bytes = sizeof(A->records);
   view.d_totals = A->totals;
-  view.d_epi_tensor = A->epi_tensor;
+  view.d_epi = A->epi;
   view.n_epi = first_epi;
   return adam_launch(&view, grad, grad_fmt, grad_meta, m, m_meta, v, v_meta, w, w_meta, wcopy, wcopy_meta, hp, s);
 }

@@ -62,9 +62,20 @@ struct AmaxParams {
   int32_t margin;
 };
 
-// Scale of a gradient tensor from the amax history as it stands: the largest of the last H entries,
-// times 2^(mu_exp - margin).  Returns the flags (amax zero / clamped) and leaves the scale alone
-// when the history is all zero.
+// Exponent of a gradient tensor's scale from the amax history as it stands (the rule of scale_from_history), or kKeepScale
+// if the history is all zero: for a whole workgroup that is about to cast with it, without writing anything.  Integer arithmetic on values all lanes share, so it runs on the scalar unit (amax values are not negative, their bit
+// patterns are ordered like they are).
+constexpr int kKeepScale = 1000;
+__device__ __forceinline__ int predicted_exponent(const fp8lm_meta* M, uint32_t fmax_bits, int hist_window, int margin) {
+  const int H = hist_window < 1 ? 1 : (hist_window > FP8LM_HIST ? FP8LM_HIST : hist_window);
+  int bits = 0;
+  for (int h = 0; h < H; ++h) bits = max(bits, (int)uniform_load(reinterpret_cast<const uint32_t*>(&M->amax_hist[h])));
+  if (bits == 0) return kKeepScale;
+  const int k = pow2_exp(fmax_bits, u2f((uint32_t)bits)) + uniform_load(&M->mu_exp) - margin;
+  return k < -126 ? -126 : (k > 126 ? 126 : k);
+}
+// Sets the scale from the amax history as it stands: the largest of the last H entries, times 2^(mu_exp - margin).
+// Returns the flags (amax zero / clamped) and leaves the scale alone when the history is all zero.
 __device__ __forceinline__ uint32_t scale_from_history(fp8lm_meta& M, uint32_t fmax_bits, int hist_window, int margin) {
   const int H = hist_window < 1 ? 1 : (hist_window > FP8LM_HIST ? FP8LM_HIST : hist_window);
   float Aeff = 0.0f;
@@ -135,11 +146,11 @@ struct AmaxOp {
     for (int j = 0; j < valid; ++j) src_fold1<SRC>(acc, q[j]);
   }
   using Stats = BlockStats<1, 0>;
-  __device__ __forceinline__ void flush(int t, long long u) {
+  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<1, 0, uint32_t> s;
     s.mx[0] = src_final<SRC>(acc);
     s.orv = 0;
-    collect(tb, *this, t, u, s);
+    collect<FINISH>(tb, *this, t, u, s);
   }
   // scalar epilogue, one thread per tensor
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
@@ -260,9 +271,14 @@ struct CastOp {
   __device__ __forceinline__ void reset() { vmax = 0.0f; n_elems = nz_top = nz_code = z_in = 0; amax16 = 0; macc = 0; }
   __device__ __forceinline__ void begin(int t) {
     scale = uniform_load(&p.meta[t].scale);
+    int e = kKeepScale;
+    if constexpr (DELAYED) {
+      e = predicted_exponent(p.meta + t, p.fmax_bits, p.hist_window, p.margin);
+      if (e != kKeepScale) scale = pow2f(e);
+    }
     careful = !DELAYED && (uniform_load(&p.meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0;
     if constexpr (FUSE) {
-      inv_sg = uniform_load(&p.meta[t].inv_scale);
+      inv_sg = e != kKeepScale ? pow2f(-e) : uniform_load(&p.meta[t].inv_scale);
       inv_sm = uniform_load(&p.m_meta[t].inv_scale);
     }
     reset();
@@ -415,8 +431,9 @@ struct CastOp {
     for (int j = 0; j < valid; ++j) p.dst[pos + j] = (uint8_t)one(q[j], FUSE ? p.m[pos + j] : 0u);
     n_elems += valid;
   }
+  static constexpr bool kFinishes = true;      // walk_marked
   using Stats = BlockStats<3, 2>;
-  __device__ __forceinline__ void flush(int t, long long u) {
+  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<3, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = src_final<SRC>(amax16);
@@ -424,7 +441,7 @@ struct CastOp {
     s.ct[0] = n_elems - nz_top;                 // codes on the top magnitude
     s.ct[1] = (n_elems - nz_code) - z_in;       // zero codes that did not come from zero inputs
     s.orv = 0;
-    collect(tb, *this, t, u, s);
+    collect<FINISH>(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -433,10 +450,13 @@ struct CastOp {
     const unsigned long long n_sat = s.ct[0], n_und = s.ct[1];
     if constexpr (DELAYED) {
       if (p.speculative) {
-        if (speculation_verdict(t, abits)) finish(t, d, vm, n_sat, n_und);
+        const bool held = speculation_verdict(t, abits);
+        mark_redo(tb, t, d, !held);
+        if (held) finish(t, d, vm, n_sat, n_und);
         return;
       }
       fp8lm_meta& M = p.meta[t];
+      M.flags = scale_from_history(M, p.fmax_bits, p.hist_window, p.margin);     // the scale the pass has used
       if (abits >= SrcTraits<SRC>::kNonfinite) {
         M.amax = __builtin_inff();
         M.flags |= FP8LM_FLAG_NONFINITE;
@@ -451,13 +471,11 @@ struct CastOp {
   // history predicted and measured the true amax on the way.  Now the metadata is brought to exactly what the amax
   // pass of the two-pass form would have left (scale from the true amax, history pushed, flags); if that scale is
   // the one the cast used, the codes already written are the just-in-time result and the caller finishes the cast's
-  // bookkeeping; otherwise the tensor is marked to be cast again.  Returns true if the speculation held.
+  // bookkeeping; otherwise the tensor has to be cast again.  Returns true if the speculation held.
   __device__ bool speculation_verdict(int t, uint32_t abits) {
     fp8lm_meta& M = p.meta[t];
-    Scratch& S = tb.scratch[t];
-    const float used = M.scale;
-    M.scale = S.old_scale;
-    M.inv_scale = S.old_inv;
+    const int e = predicted_exponent(p.meta + t, p.fmax_bits, p.hist_window, p.margin);
+    const float used = e != kKeepScale ? pow2f(e) : M.scale;
     bool held;
     if (abits >= SrcTraits<SRC>::kNonfinite) {
       M.amax = __builtin_inff();
@@ -470,7 +488,6 @@ struct CastOp {
       M.flags = scale_from_history(M, p.fmax_bits, p.hist_window, p.margin);
       held = M.scale == used;
     }
-    S.redo = held ? 0u : 1u;
     return held;
   }
   __device__ void finish(int t, const TensorDesc& d, float vm, unsigned long long n_sat, unsigned long long n_und) {
@@ -489,85 +506,11 @@ __global__ __launch_bounds__(kThreads) void cast_kernel(Tables tb, CastParams p)
   walk_units<kUnCast<SRC>>(tb, op);
 }
 
-// Speculative just-in-time quantisation, step 1: one thread per tensor keeps the scale the meta holds and sets the
-// scale its amax history predicts (the rule of delayed scaling; with an all-zero history the scale stays).
-__global__ void speculate_scale_kernel(const TensorDesc* desc, fp8lm_meta* meta, Scratch* scratch, int n, uint32_t fmax_bits,
-                                       int hist_window, int margin) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n || desc[t].numel == 0) return;
-  scratch[t].old_scale = meta[t].scale;
-  scratch[t].old_inv = meta[t].inv_scale;
-  scratch[t].redo = 0;
-  meta[t].flags = scale_from_history(meta[t], fmax_bits, hist_window, margin);
-}
-
-// Step 3: the chunk list of the tensors whose speculation failed.  One workgroup scans the tensors in order and
-// gives each marked tensor its run of chunks (first_chunk = chunks of the marked tensors before it); the others
-// get none.  Also adds to the running totals that fp8lm_get_speculation_stats reports.
-constexpr int kScanThreads = 1024;
-__global__ __launch_bounds__(kScanThreads) void redo_scan_kernel(const TensorDesc* desc, const Scratch* scratch, TensorDesc* redo_desc,
-                                                                 int n, int32_t* n_chunks_out, unsigned long long* totals) {
-  __shared__ int l_scan[kScanThreads];
-  __shared__ int l_base;
-  if (threadIdx.x == 0) l_base = 0;
-  __syncthreads();
-  unsigned long long redone_elems = 0, redone_tensors = 0;
-  for (int t0 = 0; t0 < n; t0 += kScanThreads) {
-    const int t = t0 + threadIdx.x;
-    TensorDesc d{};
-    int c = 0;
-    if (t < n) {
-      d = desc[t];
-      if (d.numel > 0 && scratch[t].redo) { c = d.n_chunks; redone_elems += (unsigned long long)d.numel; redone_tensors += 1; }
-    }
-    l_scan[threadIdx.x] = c;
-    __syncthreads();
-    for (int o = 1; o < kScanThreads; o <<= 1) {             // inclusive scan over the block
-      const int add = threadIdx.x >= o ? l_scan[threadIdx.x - o] : 0;
-      __syncthreads();
-      l_scan[threadIdx.x] += add;
-      __syncthreads();
-    }
-    const int base = l_base;
-    if (t < n) {
-      d.first_chunk = base + l_scan[threadIdx.x] - c;
-      d.n_chunks = c;
-      redo_desc[t] = d;
-    }
-    __syncthreads();
-    if (threadIdx.x == kScanThreads - 1) l_base = base + l_scan[threadIdx.x];
-    __syncthreads();
-  }
-  // totals: calls, tensors cast twice, elements cast twice (exact sums, one workgroup)
-  __shared__ unsigned long long l_e[kScanThreads / 64], l_t[kScanThreads / 64];
-  redone_elems = wave_sum_u64(redone_elems);
-  redone_tensors = wave_sum_u64(redone_tensors);
-  if ((threadIdx.x & 63) == 0) { l_e[threadIdx.x >> 6] = redone_elems; l_t[threadIdx.x >> 6] = redone_tensors; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long e = 0, k = 0;
-    for (int w = 0; w < kScanThreads / 64; ++w) { e += l_e[w]; k += l_t[w]; }
-    *n_chunks_out = l_base;
-    totals[0] += 1;
-    totals[1] += k;
-    totals[2] += e;
-  }
-}
-// ... and its chunk table: workgroup t (and t + grid, ...) copies tensor t's chunks into its run.
-__global__ void redo_fill_kernel(const TensorDesc* desc, const TensorDesc* redo_desc, const ChunkDesc* chunks, ChunkDesc* redo_chunks, int n) {
-  for (int t = blockIdx.x; t < n; t += gridDim.x) {
-    const TensorDesc d = redo_desc[t];
-    const int from = desc[t].first_chunk;
-    for (int i = threadIdx.x; i < d.n_chunks; i += blockDim.x) redo_chunks[d.first_chunk + i] = chunks[from + i];
-  }
-}
-
-// Delayed scaling, step 1: one thread per tensor fixes the scale from the history before the cast.
-__global__ void delayed_scale_kernel(const TensorDesc* desc, fp8lm_meta* meta, int n, uint32_t fmax_bits,
-                                     int hist_window, int margin) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n || desc[t].numel == 0) return;
-  meta[t].flags = scale_from_history(meta[t], fmax_bits, hist_window, margin);
+// The second round of a speculative quantisation: the marked tensors, with the scale that is now in their metadata.
+template <int FMT, bool FUSE, int SRC>
+__global__ __launch_bounds__(kThreads) void cast_marked_kernel(Tables tb, CastParams p) {
+  CastOp<FMT, false, FUSE, SRC> op(p, tb);
+  walk_marked<kUnCast<SRC>>(tb, op);
 }
 
 // ================================================================================================
@@ -677,13 +620,13 @@ struct RequantOp {
     n_elems += valid;
   }
   using Stats = BlockStats<1, 2>;
-  __device__ __forceinline__ void flush(int t, long long u) {
+  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<1, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.ct[0] = n_elems - nz_top;
     s.ct[1] = nz_in - nz_code;                 // non-zero codes in, zero codes out (a NaN code is non-zero on both sides)
     s.orv = nonfinite;
-    collect(tb, *this, t, u, s);
+    collect<FINISH>(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -834,14 +777,14 @@ struct SumOp {
     n_elems += valid;
   }
   using Stats = BlockStats<2, 2>;
-  __device__ __forceinline__ void flush(int t, long long u) {
+  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<2, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = amax_bits;
     s.ct[0] = n_top + (n_fast - nz_top);              // codes on the top magnitude
     s.ct[1] = n_und + ((n_fast - nz_code) - z_acc);   // zero codes that did not come from zero sums
     s.orv = 0;
-    collect(tb, *this, t, u, s);
+    collect<FINISH>(tb, *this, t, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const float vm = u2f(s.mx[0]);

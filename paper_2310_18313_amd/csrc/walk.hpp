@@ -27,6 +27,12 @@ struct alignas(16) ChunkDesc {
   int32_t len;
   int32_t tensor;
 };
+// A workgroup of the launch that combines records: its tensor, and which of the tensor's workgroups it is.
+struct alignas(16) EpilogueDesc {
+  TensorDesc d;
+  int32_t tensor, k;
+  int32_t pad[2];
+};
 // How many workgroups combine a tensor's records.
 constexpr int kEpilogueChunks = 512, kMaxEpilogue = 64;
 __host__ __device__ inline int epilogue_groups(int32_t n_chunks) {
@@ -38,8 +44,8 @@ __host__ __device__ inline int epilogue_groups(int32_t n_chunks) {
 // by the first Adam pass to the second, and what else that needs to know of a tensor.
 struct alignas(128) Scratch {
   uint32_t ticket;                // units finished, or epilogue workgroups
-  uint32_t redo;                  // speculative quantisation: 1 if the tensor has to be cast again with the scale now in its meta
-  float old_scale, old_inv;       // ... and the scale the meta held before the speculation
+  uint32_t redo;                  // a speculation that failed: the tensor's units, which have to be done again; otherwise 0
+  float old_scale, old_inv;       // the scale the first moment's meta held before its speculation
   struct Pending {
     float sm, ism, sv, isv, sw, isw, sq, isq;
     uint32_t fm, fv, fw, fq;      // flags gathered while choosing the scales
@@ -64,17 +70,20 @@ struct Tables {
   Scratch* scratch;
   unsigned char* records;         // one record per unit (see leave_record)
   unsigned long long* totals;     // [epilogue workgroups][kTotalWords] what those of a large tensor hand to the last of them
-  const int32_t* epi_tensor;      // [n_epi] tensor of an epilogue workgroup
+  const EpilogueDesc* epi;        // [n_epi]
   int32_t n_epi;
   int32_t n_chunks;
   int32_t unit_elems;             // a chunk is cut into 2^unit_shift units of unit_elems elements, the work of a workgroup
   int32_t unit_shift;
   int32_t one_unit;               // 1: the grid has one workgroup per unit; 0: a workgroup walks a contiguous range of units
   int32_t deferred;               // 1: workgroups only leave their records; an epilogue launch finishes the tensors
-  const int32_t* n_chunks_dev;    // if set: the number of chunks is read from here (a chunk list built on the device);
-                                  // n_chunks is then only the host's upper bound
+  int32_t n_tensors;
+  // speculation: the number of this call, where the last call that marked a tensor leaves its number, running totals (calls,
+  // tensors done again, elements done again)
+  uint32_t call;
+  uint32_t* marked_call;
+  unsigned long long* spec_totals;
 };
-__device__ __forceinline__ long long chunk_count(const Tables& tb) { return tb.n_chunks_dev ? *tb.n_chunks_dev : tb.n_chunks; }
 
 // A load of something that no kernel writes while another may read it here, from an address all lanes share: through the
 // scalar cache, whatever stores come before it.
@@ -89,7 +98,7 @@ template <class T> __device__ __forceinline__ T uniform_load(const T* p) {
 
 // Writes the chunk and epilogue tables from the tensor table and returns the tickets to zero; workgroup t (and t + grid,
 // ...) does tensor t's part.
-__global__ void chunk_tables_kernel(const TensorDesc* desc, ChunkDesc* chunks, int32_t* epi_tensor, Scratch* scratch, int chunk_elems, int n) {
+__global__ void chunk_tables_kernel(const TensorDesc* desc, ChunkDesc* chunks, EpilogueDesc* epi, Scratch* scratch, int chunk_elems, int n) {
   for (int t = blockIdx.x; t < n; t += gridDim.x) {
     const TensorDesc d = desc[t];
     for (int i = threadIdx.x; i < d.n_chunks; i += blockDim.x) {
@@ -97,7 +106,7 @@ __global__ void chunk_tables_kernel(const TensorDesc* desc, ChunkDesc* chunks, i
       chunks[d.first_chunk + i] = ChunkDesc{d.offset + e0, (int32_t)(rest < chunk_elems ? rest : chunk_elems), t};
     }
     if (d.n_chunks > 0)
-      for (int i = threadIdx.x; i < epilogue_groups(d.n_chunks); i += blockDim.x) epi_tensor[d.epi0 + i] = t;
+      for (int i = threadIdx.x; i < epilogue_groups(d.n_chunks); i += blockDim.x) epi[d.epi0 + i] = EpilogueDesc{d, t, i, {0, 0}};
     if (threadIdx.x == 0) scratch[t].ticket = 0;
   }
 }
@@ -126,6 +135,7 @@ __device__ __forceinline__ uint32_t wave_or_u32(uint32_t v) {
 __device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
   return wave_reduce_u32(v, [](uint32_t a, uint32_t b) { return a + b; });
 }
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {   // valid in every lane
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -280,12 +290,12 @@ __device__ __forceinline__ uint32_t units_of(const Tables& tb, const TensorDesc&
 
 // Called by all threads at the end of unit u, a part of tensor t.  In the single-pass form the workgroup that completes
 // the tensor runs its scalar epilogue.
-template <int NV, int NC, class Op>
+template <bool FINISH, int NV, int NC, class Op>
 __device__ __forceinline__ void collect(const Tables& tb, Op& op, int t, long long u, const BlockStats<NV, NC, uint32_t>& s) {
   const uint4 r = block_combine(s);
   constexpr int kStored = NC == 0 ? 1 : (NC <= 4 ? 2 : 3);
   if (threadIdx.x < kStored) reinterpret_cast<uint4*>(tb.records + u * kRecordBytes<NC>)[threadIdx.x] = r;
-  if (tb.deferred) return;
+  if (!FINISH || tb.deferred) return;          // FINISH = false: walk_marked bumps the ticket once for all its units
   const TensorDesc d = tb.desc[t];
   const uint32_t n = units_of(tb, d);
   if (!ticket_last(tb, t, 1u, n)) return;
@@ -295,18 +305,19 @@ __device__ __forceinline__ void collect(const Tables& tb, Op& op, int t, long lo
   if (threadIdx.x == 0) op.finalize(t, d, total);
 }
 
-// The second launch of the deferred form.
-template <class Op, class Params>
+// The second launch of the deferred form.  MARKED: of the second round of a speculation (walk_marked), for the tensors it did.
+template <class Op, class Params, bool MARKED = false>
 __global__ __launch_bounds__(kThreads) void epilogue_kernel(Tables tb, Params p) {
+  if (MARKED && uniform_load(tb.marked_call) != tb.call) return;
   Op op(p, tb);
   for (int i = blockIdx.x; i < tb.n_epi; i += gridDim.x) {
-    const int t = tb.epi_tensor[i];
-    const TensorDesc d = tb.desc[t];
-    if (d.n_chunks == 0) continue;               // (a list of tensors to be cast again leaves the others out)
-    const int K = epilogue_groups(d.n_chunks), k = i - d.epi0;
+    const EpilogueDesc e = tb.epi[i];
+    const TensorDesc& d = e.d;
+    const int t = e.tensor, K = epilogue_groups(d.n_chunks);
+    if (MARKED && tb.scratch[t].redo == 0) continue;
     const long long n = units_of(tb, d), u0 = (long long)d.first_chunk << tb.unit_shift;
     typename Op::Stats s;
-    gather_records(tb, u0 + n * k / K, u0 + n * (k + 1) / K, s);
+    gather_records(tb, u0 + n * e.k / K, u0 + n * (e.k + 1) / K, s);
     if (K > 1) {
       constexpr int NV = Op::Stats::kNV, NC = Op::Stats::kNC;
       if (threadIdx.x == 0) {
@@ -316,16 +327,15 @@ __global__ __launch_bounds__(kThreads) void epilogue_kernel(Tables tb, Params p)
         for (int j = 0; j < NC; ++j) w[4 + j] = s.ct[j];
       }
       if (!ticket_last(tb, t, 1u, (uint32_t)K)) continue;
-      if (threadIdx.x == 0) {
-        for (int j = 0; j < NV; ++j) s.mx[j] = 0;
-        for (int j = 0; j < NC; ++j) s.ct[j] = 0;
-        s.orv = 0;
-        for (int q = 0; q < K; ++q) {
-          const unsigned long long* w = tb.totals + (long long)(d.epi0 + q) * kTotalWords;
-          for (int j = 0; j < NV; ++j) s.mx[j] = max(s.mx[j], (uint32_t)w[j]);
-          s.orv |= (uint32_t)w[3];
-          for (int j = 0; j < NC; ++j) s.ct[j] += w[4 + j];
-        }
+      if (threadIdx.x < 64) {                    // a lane per workgroup
+        static_assert(kMaxEpilogue <= 64, "one wavefront");
+        const bool have = threadIdx.x < K;
+        const unsigned long long* w = tb.totals + (long long)(d.epi0 + (have ? threadIdx.x : 0)) * kTotalWords;
+#pragma unroll
+        for (int j = 0; j < NV; ++j) s.mx[j] = last_lane(wave_max_u32(have ? (uint32_t)w[j] : 0u));
+        s.orv = last_lane(wave_or_u32(have ? (uint32_t)w[3] : 0u));
+#pragma unroll
+        for (int j = 0; j < NC; ++j) s.ct[j] = wave_sum_u64(have ? w[4 + j] : 0ull);
       }
     }
     if (threadIdx.x == 0) op.finalize(t, d, s);
@@ -349,7 +359,7 @@ __global__ __launch_bounds__(kThreads) void epilogue_kernel(Tables tb, Params p)
 // XOR-only traffic of 1.8e9 elements in one HBM region, TB/s, persistent / one tile per workgroup: update shape 5.13 / 5.5
 // (5.9 with two or three workgroups per compute unit), cast shape 5.37 / 6.45, one-to-one copy 5.23 / 6.54, reads alone
 // 6.95 / 6.95.  Two tiles per workgroup cost 5 % of the cast shape, four consecutive ones 2 to 8 % of the update shape.
-template <int UN, class Op>
+template <int UN, bool FINISH = true, class Op>
 __device__ __forceinline__ void walk_unit(const Tables& tb, Op& op, long long u) {
   const ChunkDesc c = uniform_load(tb.chunks + (u >> tb.unit_shift));
   const int e0 = ((int)u & ((1 << tb.unit_shift) - 1)) * tb.unit_elems;
@@ -377,25 +387,108 @@ __device__ __forceinline__ void walk_unit(const Tables& tb, Op& op, long long u)
       }
     }
   }
-  // what is left (less than a tile; a whole small tensor): complete 16-element groups still take
-  // 128-bit accesses, only the last, incomplete group of a tensor goes element by element
-  for (int i = tile * kTile + threadIdx.x * kGroup; i < len; i += kTile) {
-    const int valid = len - i < kGroup ? len - i : kGroup;
-    if (valid == kGroup && op.fast()) op.full_group(base + i);
-    else op.group(base + i, valid);
+  // what is left (less than a tile; a whole small tensor): complete 16-element groups still take 128-bit accesses
+  const int whole = len & ~(kGroup - 1);
+  for (int i = tile * kTile + threadIdx.x * kGroup; i < whole; i += kTile) {
+    if (op.fast()) op.full_group(base + i);
+    else op.group(base + i, kGroup);
   }
-  op.flush(t, u);
+  // the last, incomplete group of a tensor goes element by element, a thread each: one thread alone with up to 15 in-place
+  // elements waits for every load in turn (the update of 600 ragged tensors: 38 us, 14 us this way)
+  const int last = whole + kThreads - 1 - (int)threadIdx.x;
+  if (last < len) op.group(base + last, 1);
+  op.template flush<FINISH>(t, u);
 }
 
 template <int UN, class Op>
 __device__ __forceinline__ void walk_units(const Tables& tb, Op& op) {
   long long u = blockIdx.x, end = u + 1;
   if (!tb.one_unit) {
-    const long long U = chunk_count(tb) << tb.unit_shift, b = blockIdx.x, G = gridDim.x;
+    const long long U = (long long)tb.n_chunks << tb.unit_shift, b = blockIdx.x, G = gridDim.x;
     u = b * U / G;
     end = (b + 1) * U / G;
   }
   for (; u < end; ++u) walk_unit<UN>(tb, op, u);
+}
+
+// ---- the second round of a speculation ------------------------------------------------------------------
+// The scalar epilogue of a speculative pass marks the tensors whose speculation failed (mark_redo); this walk does their
+// units once more.  Mostly nothing is marked: then a workgroup reads
+// one word and ends.  Otherwise every workgroup adds up the marked units of all tensors and takes a contiguous share
+// of them, so that one marked tensor keeps the whole chip busy as well as many do.  (Two small kernels that built a list
+// before it cost 10 us per call whether or not there was anything to do.)  The tensors are finished by tickets or by a launch of
+// their own, as after any other pass: tickets of 1024 workgroups are 60 us, so they are for the smallest launches.
+__device__ __forceinline__ void mark_redo(const Tables& tb, int t, const TensorDesc& d, bool redo) {
+  tb.scratch[t].redo = redo ? units_of(tb, d) : 0u;
+  if (!redo) return;
+  __hip_atomic_store(tb.marked_call, tb.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  (void)__hip_atomic_fetch_add(&tb.spec_totals[1], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  (void)__hip_atomic_fetch_add(&tb.spec_totals[2], (unsigned long long)d.numel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <int UN, class Op>
+__device__ __forceinline__ void walk_marked(const Tables& tb, Op& op) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) tb.spec_totals[0] += 1;
+  if (uniform_load(tb.marked_call) != tb.call) return;
+  __shared__ uint32_t l_sum[kWaves], l_count[kWaves];
+  __shared__ struct { uint32_t at; int32_t t; } l_share[kThreads];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t mine = 0;                             // (all units of a launch fit 32 bits)
+  for (int t = threadIdx.x; t < tb.n_tensors; t += kThreads) mine += tb.scratch[t].redo;
+  mine = wave_sum_u32(mine);
+  if (lane == 63) l_sum[wave] = mine;
+  __syncthreads();
+  const long long total = (long long)l_sum[0] + l_sum[1] + l_sum[2] + l_sum[3];
+  const long long lo = total * blockIdx.x / gridDim.x, hi = total * (blockIdx.x + 1) / gridDim.x;
+  if (lo == hi) return;
+  long long base = 0;                            // marked units of the tensors before this block of them
+  for (int t0 = 0; t0 < tb.n_tensors && base < hi; t0 += kThreads) {
+    // a thread per tensor: where its marked units lie among all, and whether this workgroup's share reaches into them
+    const int ti = t0 + threadIdx.x;
+    const uint32_t n = ti < tb.n_tensors ? tb.scratch[ti].redo : 0u;
+    uint32_t upto = n;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t x = (uint32_t)__shfl_up((int)upto, o, 64);
+      if (lane >= o) upto += x;
+    }
+    __syncthreads();                             // the previous use of the LDS arrays is over
+    if (lane == 63) l_sum[wave] = upto;
+    __syncthreads();
+    long long at = base + upto - n;
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) at += l_sum[w];
+      base += l_sum[w];
+    }
+    const bool share = n && at < hi && at + n > lo;
+    const unsigned long long ballot = __ballot(share);
+    if (lane == 0) l_count[wave] = (uint32_t)__popcll(ballot);
+    __syncthreads();
+    int count = 0, place = __popcll(ballot & ((1ull << lane) - 1));
+    for (int w = 0; w < kWaves; ++w) {
+      if (w < wave) place += (int)l_count[w];
+      count += (int)l_count[w];
+    }
+    if (share) {
+      l_share[place].at = (uint32_t)at;
+      l_share[place].t = ti;
+    }
+    __syncthreads();
+    for (int i = 0; i < count; ++i) {
+      const int t = __builtin_amdgcn_readfirstlane(l_share[i].t);
+      const long long first = (uint32_t)__builtin_amdgcn_readfirstlane((int)l_share[i].at);
+      const TensorDesc d = uniform_load(tb.desc + t);
+      const long long units = units_of(tb, d), u0 = (long long)d.first_chunk << tb.unit_shift;
+      const long long k0 = max(lo - first, 0ll), k1 = min(hi - first, units);
+      for (long long k = k0; k < k1; ++k) walk_unit<UN, false>(tb, op, u0 + k);
+      if constexpr (Op::kFinishes) {
+        if (!tb.deferred && ticket_last(tb, t, (uint32_t)(k1 - k0), (uint32_t)units)) {
+          typename Op::Stats s;
+          gather_records(tb, u0, u0 + units, s);
+          if (threadIdx.x == 0) op.finalize(t, d, s);
+        }
+      }
+    }
+  }
 }
 
 // Build-time tuning knobs (defaults are the measured best on MI355X).
