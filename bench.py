@@ -369,7 +369,7 @@ def main() -> int:
             step_no[0] += 1
             hp = B.adam_hparams(wl.lr, step_no[0], exact=args.exact, stats=args.stats, m_scale_mode=mode_of[path])
             st.step(grads[step_no[0] % len(grads)], hp, delayed=(path == "single" and step_no[0] > 1),
-                    speculative=path.startswith("spec"), pair_m=(path == "spec-m2"))
+                    speculative=path.startswith("spec"), pair_m=(path == "spec-m2"), own_moment_pass=True)
 
     def timed(path, n):
         """(seconds, per-kernel timing, bytes per parameter and step actually moved, speculation totals of the region)."""
@@ -468,7 +468,7 @@ def main() -> int:
         side.wait_stream(torch.cuda.current_stream())
         torch.cuda.synchronize()
         with torch.cuda.graph(graph, stream=side):
-            st.step(grad, hp, delayed=delayed, speculative=args.path.startswith("spec"))
+            st.step(grad, hp, delayed=delayed, speculative=args.path.startswith("spec"), own_moment_pass=True)
         for _ in range(args.warmup):
             graph.replay()
         torch.cuda.synchronize()

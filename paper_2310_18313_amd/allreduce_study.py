@@ -62,8 +62,8 @@ class Fp8AllReduce:
         c = self.ctx
         self._plant_mu()
         for r, g in enumerate(grads):
-            c.amax_scale(g, self.fmt, self.meta[r], self.cfg)
-            c.cast_fp8(g, self.payload[r], self.fmt, self.meta[r], self.cfg)
+            # amax, scale and cast; a gradient whose scale does not change is read once
+            c.quantize_fp8(g, self.payload[r], self.fmt, self.meta[r], self.cfg)
         self.shared = c.shared_scale(self.meta)
         for r in range(self.n):
             c.requantize_fp8(self.payload[r], self.fmt, self.meta[r], self.shared, self.shared_payload[r],

@@ -134,14 +134,20 @@ class OptimizerState:
                                self.w, self.w_meta, self.wq, self.q_meta, hp)
 
     def step(self, grad: torch.Tensor, hp: B.AdamHparams, delayed: bool = False, speculative: bool = False,
-             pair_m: bool = False) -> None:
+             pair_m: bool = False, own_moment_pass: bool = False) -> None:
         """One pass of the whole hot path: amax + scale, FP8 cast, FP8 Adam, from a bf16, fp16 or fp32
         gradient buffer.  With `delayed` the
         gradient is quantised in a single pass with the scale of the preceding steps.  With
         hp.m_scale_mode == MSCALE_FROM_CAST the cast also does the Adam step's first pass.  With `speculative` the
         just-in-time quantisation goes through quantize_fp8 (same results; tensors whose scale does not change are
         read once).  With `pair_m` (state created with second_m) the Adam step goes through adam_step_fp8_m2 (same
-        results; no read-only pass; the first moment moves to the other buffer of the pair)."""
+        results; no read-only pass; the first moment moves to the other buffer of the pair).
+        Nothing comes between the cast and the Adam step here, so with hp.m_scale_mode == MSCALE_EXACT_PASS the cast
+        measures the new first moment too (1 byte per parameter read instead of the 2 of a pass of its own, the same
+        results); `own_moment_pass` leaves it to the Adam step."""
+        if hp.m_scale_mode == B.MSCALE_EXACT_PASS and not pair_m and not own_moment_pass:
+            hp = B.AdamHparams.from_buffer_copy(hp)
+            hp.m_scale_mode = B.MSCALE_FROM_CAST
         fused = hp.m_scale_mode == B.MSCALE_FROM_CAST
         if pair_m:
             assert self.m_other is not None and not fused and not delayed
