@@ -282,11 +282,14 @@ struct AdamAmaxOp {
   const AdamParams& p;
   const Tables& tb;
   float inv_sg, inv_sm;
+  float cm, cg;           // the scales folded into the coefficients, if that changes no rounding
+  bool fold;
   uint32_t acc;
   __device__ AdamAmaxOp(const AdamParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
   __device__ __forceinline__ void begin(int t) {
     inv_sg = uniform_load(&p.grad_meta[t].inv_scale);
     inv_sm = uniform_load(&p.m_meta[t].inv_scale);
+    fold = fold_moment_scales(p.b1, p.omb1, inv_sg, inv_sm, cg, cm);
     acc = 0;
   }
   __device__ __forceinline__ void elem(float dg, float dm) {
@@ -295,6 +298,10 @@ struct AdamAmaxOp {
     acc = max(acc, f2u(m1) & 0x7FFFFFFFu);
   }
   __device__ __forceinline__ void word(uint32_t gw, uint32_t mw) {
+    if (fold) {
+      acc = max(acc, folded_moment_max<GFMT>(gw, mw, cg, cm));
+      return;
+    }
     const float2_t g01 = fp8x2_to_f32<GFMT, false>(gw), g23 = fp8x2_to_f32<GFMT, true>(gw);
     const float2_t m01 = fp8x2_to_f32<kE4M3, false>(mw), m23 = fp8x2_to_f32<kE4M3, true>(mw);
     elem(g01.x, m01.x);

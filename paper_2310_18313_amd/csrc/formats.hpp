@@ -26,11 +26,15 @@ template <> struct Fp8Traits<kE4M3> {
   static constexpr float kMax = 448.0f;          // largest finite value
   static constexpr uint32_t kTop = 0x7E;         // its code
   static constexpr uint32_t kTopX4 = 0x7E7E7E7Eu;
+  static constexpr float kFirstTop = 432.0f;     // smallest magnitude that is stored as the top code (a tie, to even)
+  static constexpr float kLastZero = 0x1p-10f;   // largest magnitude that is stored as zero (half of the smallest code, a tie)
 };
 template <> struct Fp8Traits<kE5M2> {
   static constexpr float kMax = 57344.0f;
   static constexpr uint32_t kTop = 0x7B;
   static constexpr uint32_t kTopX4 = 0x7B7B7B7Bu;
+  static constexpr float kFirstTop = 53248.00390625f;   // just above the tie with 49152, which goes to even, that is down
+  static constexpr float kLastZero = 0x1p-17f;
 };
 
 // ---- FP8 decode: two codes of a 32-bit word -> two floats ---------------------------------------

@@ -44,7 +44,19 @@ template <int SRC> __device__ __forceinline__ void src_fold(uint32_t& acc, uint3
   else
     acc = max(acc, word & 0x7FFFFFFFu);
 }
-// the same for a single element given by its bit pattern
+// ... and into a running minimum
+template <int SRC> __device__ __forceinline__ void src_fold_min(uint32_t& acc, uint32_t word) {
+  if constexpr (kSrc16<SRC>)
+    acc = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(ushort2_t, acc),
+                                                                 __builtin_bit_cast(ushort2_t, word & 0x7FFF7FFFu)));
+  else
+    acc = min(acc, word & 0x7FFFFFFFu);
+}
+template <int SRC> __device__ __forceinline__ uint32_t src_final_min(uint32_t acc) {
+  if constexpr (kSrc16<SRC>) return min(acc & 0xFFFFu, acc >> 16);
+  else return acc;
+}
+// the same (maximum) for a single element given by its bit pattern
 template <int SRC> __device__ __forceinline__ void src_fold1(uint32_t& acc, uint32_t bits) {
   if constexpr (kSrc16<SRC>) acc = (acc & 0xFFFF0000u) | max(acc & 0xFFFFu, bits & 0x7FFFu);
   else acc = max(acc, bits & 0x7FFFFFFFu);
@@ -226,6 +238,24 @@ __device__ __forceinline__ void autoscale_update(fp8lm_meta& M, unsigned long lo
   M.mu_exp = -1 + (ramp > 2 ? 2 : ramp);
 }
 
+// max |m'| of one element's new first moment is taken on m' = fma(beta1, m / s_m, (1-beta1) * (g / s_g)).  Scales are
+// powers of two, so they can go into the coefficients without changing a rounding, unless something gets subnormal or
+// overflows on the way: false then (or if a scale is no power of two, as that of an FP8 sum can be).
+__device__ __forceinline__ bool fold_moment_scales(float b1, float omb1, float isg, float ism, float& cg, float& cm) {
+  const uint32_t g = f2u(isg), m = f2u(ism);
+  cg = omb1 * isg;
+  cm = b1 * ism;
+  return ((g | m) & 0x807FFFFFu) == 0 && (g >> 23) - 47u <= 160u && (m >> 23) - 47u <= 160u &&     // 2^-80 .. 2^80
+         (b1 == 0.0f || b1 >= 0x1p-20f);
+}
+// the largest bit pattern of four |m'|, inf and NaN above all others
+template <int FMT> __device__ __forceinline__ uint32_t folded_moment_max(uint32_t gw, uint32_t mw, float cg, float cm) {
+  const float2_t g01 = fp8x2_to_f32<FMT, false>(gw), g23 = fp8x2_to_f32<FMT, true>(gw);
+  const float2_t m01 = fp8x2_to_f32<kE4M3, false>(mw), m23 = fp8x2_to_f32<kE4M3, true>(mw);
+  auto bits = [&](float dg, float dm) { return f2u(__builtin_fmaf(cm, dm, cg * dg)) & 0x7FFFFFFFu; };
+  return max(max(bits(g01.x, m01.x), bits(g01.y, m01.y)), max(bits(g23.x, m23.x), bits(g23.y, m23.y)));
+}
+
 struct CastParams {
   const void* src;
   uint8_t* dst;
@@ -260,10 +290,13 @@ struct CastOp {
   float scale;
   bool careful;
   float inv_sg, inv_sm;   // FUSE
+  float cm, cg;           // FUSE: beta1 / s_m and (1 - beta1) / s_g, if folding the scales changes no rounding
+  bool fold;
   uint32_t macc;          // FUSE: running max of the |m'| bit patterns
   uint32_t amax16;        // DELAYED: running maximum of the source's magnitude bits (packed pair for 16-bit types)
   float vmax;             // max |clamped scaled value|
-  uint32_t n_elems;       // elements seen (full groups * 16 + tails) since the last flush
+  // counted elements: tails and the groups that have a code on the top or at zero at all
+  uint32_t n_elems;
   uint32_t nz_top;        // codes whose magnitude differs from the top code
   uint32_t nz_code;       // codes with non-zero magnitude
   uint32_t z_in;          // inputs that are +-0
@@ -280,6 +313,7 @@ struct CastOp {
     if constexpr (FUSE) {
       inv_sg = e != kKeepScale ? pow2f(-e) : uniform_load(&p.meta[t].inv_scale);
       inv_sm = uniform_load(&p.m_meta[t].inv_scale);
+      fold = fold_moment_scales(p.b1, p.omb1, inv_sg, inv_sm, cg, cm);
     }
     reset();
   }
@@ -290,6 +324,10 @@ struct CastOp {
     macc = max(macc, f2u(m1) & 0x7FFFFFFFu);
   }
   __device__ __forceinline__ void moment_word(uint32_t gw, uint32_t mw) {
+    if (fold) {
+      macc = max(macc, folded_moment_max<FMT>(gw, mw, cg, cm));
+      return;
+    }
     const float2_t g01 = fp8x2_to_f32<FMT, false>(gw), g23 = fp8x2_to_f32<FMT, true>(gw);
     const float2_t m01 = fp8x2_to_f32<kE4M3, false>(mw), m23 = fp8x2_to_f32<kE4M3, true>(mw);
     moment(g01.x, m01.x);
@@ -297,40 +335,37 @@ struct CastOp {
     moment(g23.x, m23.x);
     moment(g23.y, m23.y);
   }
-  // DELAYED: folds one group's source bits into the running amax; true if the group holds inf or NaN
-  __device__ __forceinline__ bool note_source(const uint32_t (&w)[kW]) {
-    uint32_t gm = 0;
-#pragma unroll
-    for (int j = 0; j < kW; ++j) src_fold<SRC>(gm, w[j]);
-    if constexpr (kSrc16<SRC>)
-      amax16 = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2_t, amax16),
-                                                                      __builtin_bit_cast(ushort2_t, gm)));
-    else
-      amax16 = max(amax16, gm);
-    return src_final<SRC>(gm) >= SrcTraits<SRC>::kNonfinite;
-  }
   // four consecutive elements of a group (quad q = 0..3) widened to fp32
-  __device__ __forceinline__ uint32_t quad(const uint32_t (&w)[kW], int q) {
-    float f0, f1, f2, f3;
+  __device__ __forceinline__ float4 widen(const uint32_t (&w)[kW], int q) const {
     if constexpr (SRC == kSrcBF16) {
-      f0 = bf16lo_to_f32(w[2 * q]); f1 = bf16hi_to_f32(w[2 * q]);
-      f2 = bf16lo_to_f32(w[2 * q + 1]); f3 = bf16hi_to_f32(w[2 * q + 1]);
+      return make_float4(bf16lo_to_f32(w[2 * q]), bf16hi_to_f32(w[2 * q]), bf16lo_to_f32(w[2 * q + 1]), bf16hi_to_f32(w[2 * q + 1]));
     } else if constexpr (SRC == kSrcF16) {
       const float2_t lo = f16x2_to_f32(w[2 * q]), hi = f16x2_to_f32(w[2 * q + 1]);
-      f0 = lo.x; f1 = lo.y; f2 = hi.x; f3 = hi.y;
+      return make_float4(lo.x, lo.y, hi.x, hi.y);
     } else {
-      f0 = u2f(w[4 * q]); f1 = u2f(w[4 * q + 1]); f2 = u2f(w[4 * q + 2]); f3 = u2f(w[4 * q + 3]);
+      return make_float4(u2f(w[4 * q]), u2f(w[4 * q + 1]), u2f(w[4 * q + 2]), u2f(w[4 * q + 3]));
     }
-    const float y0 = clamp_fp8<FMT>(f0 * scale), y1 = clamp_fp8<FMT>(f1 * scale);
-    const float y2 = clamp_fp8<FMT>(f2 * scale), y3 = clamp_fp8<FMT>(f3 * scale);
-    vmax = fmaxf(fmaxf(vmax, fmaxf(fabsf(y0), fabsf(y1))), fmaxf(fabsf(y2), fabsf(y3)));
-    z_in += (f0 == 0.0f) + (f1 == 0.0f) + (f2 == 0.0f) + (f3 == 0.0f);
-    uint32_t c = f32x2_to_fp8<FMT, false>(y0, y1, 0u);
-    c = f32x2_to_fp8<FMT, true>(y2, y3, c);
-    const uint32_t mag = c & 0x7F7F7F7Fu;
-    nz_code += nonzero_bytes7(mag);
-    nz_top += nonzero_bytes7(mag ^ Fp8Traits<FMT>::kTopX4);
-    return c;
+  }
+  template <bool CLAMP> __device__ __forceinline__ uint32_t quad(const uint32_t (&w)[kW], int q) {
+    const float4 f = widen(w, q);
+    float y0 = f.x * scale, y1 = f.y * scale, y2 = f.z * scale, y3 = f.w * scale;
+    if constexpr (CLAMP) {
+      y0 = clamp_fp8<FMT>(y0); y1 = clamp_fp8<FMT>(y1); y2 = clamp_fp8<FMT>(y2); y3 = clamp_fp8<FMT>(y3);
+    }
+    return f32x2_to_fp8<FMT, true>(y2, y3, f32x2_to_fp8<FMT, false>(y0, y1, 0u));
+  }
+  // the counters of one group's codes
+  __device__ __forceinline__ void count(const uint32_t (&w)[kW], const uint4& o) {
+    const uint32_t c[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t mag = c[q] & 0x7F7F7F7Fu;
+      nz_code += nonzero_bytes7(mag);
+      nz_top += nonzero_bytes7(mag ^ Fp8Traits<FMT>::kTopX4);
+      const float4 f = widen(w, q);
+      z_in += (f.x == 0.0f) + (f.y == 0.0f) + (f.z == 0.0f) + (f.w == 0.0f);
+    }
+    n_elems += kGroup;
   }
   __device__ __forceinline__ uint32_t one(uint32_t bits, uint32_t mcode) {
     const float f = SrcTraits<SRC>::dec(bits);
@@ -382,8 +417,21 @@ struct CastOp {
       for (int k = 0; k < kLoads; ++k) {
         w[4 * k] = g.r[u][k].x; w[4 * k + 1] = g.r[u][k].y; w[4 * k + 2] = g.r[u][k].z; w[4 * k + 3] = g.r[u][k].w;
       }
+      // The largest and the smallest magnitude of the group, by integer maxima of the source's bits (packed pairs for 16-bit
+      // types): scaling is monotone, so they tell whether any element saturates, lands on the top code or underflows.
+      // Mostly none does, and the elements are only scaled and converted: 5.5 instructions each instead of 10, which is
+      // what kept the pass off the memory's pace.
+      uint32_t gmax = 0, gmin = 0xFFFFFFFFu;
+#pragma unroll
+      for (int j = 0; j < kW; ++j) {
+        src_fold<SRC>(gmax, w[j]);
+        src_fold_min<SRC>(gmin, w[j]);
+      }
+      const uint32_t top = src_final<SRC>(gmax);
       if constexpr (DELAYED) {
-        if (note_source(w)) {   // rare: this group holds inf/NaN; element by element, and again from memory: no registers for it
+        src_fold1<SRC>(amax16, top);
+        if (top >= SrcTraits<SRC>::kNonfinite) {
+          // rare: this group holds inf/NaN; element by element, and again from memory: no registers for it
           if constexpr (kSplit) {
             group(pos + u * kTile, kGroup / 2);
             group(pos + u * kTile + kTile / 2, kGroup / 2);
@@ -393,17 +441,23 @@ struct CastOp {
           continue;
         }
       }
-      // one quad after the other: interleaved, as the compiler would have them, they take registers that other
-      // wavefronts make better use of (119 -> 94 with two tiles; the cast of GPT-125M 66 -> 62 us)
+      const float ymax = SrcTraits<SRC>::dec(top) * scale, ymin = SrcTraits<SRC>::dec(src_final_min<SRC>(gmin)) * scale;
       uint4 o;
-      o.x = quad(w, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      o.y = quad(w, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      o.z = quad(w, 2);
-      __builtin_amdgcn_sched_barrier(0);
-      o.w = quad(w, 3);
-      n_elems += kGroup;
+      if (!(ymax <= Fp8Traits<FMT>::kMax)) {
+        o = make_uint4(quad<true>(w, 0), quad<true>(w, 1), quad<true>(w, 2), quad<true>(w, 3));
+      } else {
+        // one quad after the other: interleaved, as the compiler would have them, they take registers that other
+        // wavefronts make better use of
+        o.x = quad<false>(w, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        o.y = quad<false>(w, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        o.z = quad<false>(w, 2);
+        __builtin_amdgcn_sched_barrier(0);
+        o.w = quad<false>(w, 3);
+      }
+      vmax = fmaxf(vmax, fminf(ymax, Fp8Traits<FMT>::kMax));
+      if (ymax >= Fp8Traits<FMT>::kFirstTop || ymin <= Fp8Traits<FMT>::kLastZero) count(w, o);
       if constexpr (FUSE) {
         const uint4 mm = g.mm[u];
         moment_word(o.x, mm.x);
