@@ -386,30 +386,37 @@ struct CastOp {
     return c;
   }
   __device__ __forceinline__ bool fast() const { return !careful; }
-  // kSplit: the thread's 16 elements are [8L, 8L+8) of each half of the tile (every 128-bit load contiguous
-  // over the workgroup, 64-bit stores); otherwise 16 consecutive elements.
+  // kSplit: the thread's 16 elements are kRuns runs, [8L, 8L+8) of each half of the tile for 16-bit sources, [4L, 4L+4)
+  // of each quarter for fp32: every 128-bit load is contiguous over the workgroup, the stores have 64 or 32 bits.
+  // Otherwise 16 consecutive elements.  (fp32 sources with 16 consecutive elements per thread, 201e6 of them: 228 us.)
+  static constexpr int kRuns = kLoads, kRun = kGroup / kRuns;
   template <int UN> struct Regs { uint4 r[UN][kLoads], mm[FUSE ? UN : 1]; };
-  template <int UN> __device__ __forceinline__ void load(Regs<UN>& g, long long pos0) { load_as<kSrc16<SRC>>(g, pos0); }
-  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& g, long long pos0) { tiles_as<kSrc16<SRC>>(g, pos0); }
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& g, long long pos0) { load_as<true>(g, pos0); }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& g, long long pos0) { tiles_as<true>(g, pos0); }
   template <bool kSplit, int UN> __device__ __forceinline__ void load_as(Regs<UN>& g, long long pos0) {
-    const long long pos = pos0 + threadIdx.x * (kSplit ? 8 : kGroup);
+    constexpr int kStep = kTile / kRuns;
+    const long long pos = pos0 + threadIdx.x * (kSplit ? kRun : kGroup);
     const elem_t* q = static_cast<const elem_t*>(p.src) + pos;
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
 #pragma unroll
-      for (int k = 0; k < kLoads; ++k) g.r[u][k] = ld16<kNtLoadRO>(q + u * kTile + k * (kSplit ? kTile / 2 : kPer));
+      for (int k = 0; k < kLoads; ++k) g.r[u][k] = ld16<kNtLoadRO>(q + u * kTile + k * (kSplit ? kStep : kPer));
       if constexpr (FUSE) {
-        if constexpr (kSplit) {
-          const uint2 lo = ld8<kNtLoadRO>(p.m + pos + u * kTile), hi = ld8<kNtLoadRO>(p.m + pos + u * kTile + kTile / 2);
+        const uint8_t* m = p.m + pos + u * kTile;
+        if constexpr (kSplit && kRuns == 2) {
+          const uint2 lo = ld8<kNtLoadRO>(m), hi = ld8<kNtLoadRO>(m + kStep);
           g.mm[u] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        } else if constexpr (kSplit) {
+          g.mm[u] = make_uint4(ld4<kNtLoadRO>(m), ld4<kNtLoadRO>(m + kStep), ld4<kNtLoadRO>(m + 2 * kStep), ld4<kNtLoadRO>(m + 3 * kStep));
         } else {
-          g.mm[u] = ld16<kNtLoadRO>(p.m + pos + u * kTile);
+          g.mm[u] = ld16<kNtLoadRO>(m);
         }
       }
     }
   }
   template <bool kSplit, int UN> __device__ __forceinline__ void tiles_as(const Regs<UN>& g, long long pos0) {
-    const long long pos = pos0 + threadIdx.x * (kSplit ? 8 : kGroup);
+    constexpr int kStep = kTile / kRuns;
+    const long long pos = pos0 + threadIdx.x * (kSplit ? kRun : kGroup);
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       uint32_t w[kW];
@@ -433,8 +440,7 @@ struct CastOp {
         if (top >= SrcTraits<SRC>::kNonfinite) {
           // rare: this group holds inf/NaN; element by element, and again from memory: no registers for it
           if constexpr (kSplit) {
-            group(pos + u * kTile, kGroup / 2);
-            group(pos + u * kTile + kTile / 2, kGroup / 2);
+            for (int k = 0; k < kRuns; ++k) group(pos + u * kTile + k * kStep, kRun);
           } else {
             group(pos + u * kTile, kGroup);
           }
@@ -465,11 +471,17 @@ struct CastOp {
         moment_word(o.z, mm.z);
         moment_word(o.w, mm.w);
       }
-      if constexpr (kSplit) {
-        st8<kNtStoreWO>(p.dst + pos + u * kTile, make_uint2(o.x, o.y));
-        st8<kNtStoreWO>(p.dst + pos + u * kTile + kTile / 2, make_uint2(o.z, o.w));
+      uint8_t* dst = p.dst + pos + u * kTile;
+      if constexpr (kSplit && kRuns == 2) {
+        st8<kNtStoreWO>(dst, make_uint2(o.x, o.y));
+        st8<kNtStoreWO>(dst + kStep, make_uint2(o.z, o.w));
+      } else if constexpr (kSplit) {
+        st4<kNtStoreWO>(dst, o.x);
+        st4<kNtStoreWO>(dst + kStep, o.y);
+        st4<kNtStoreWO>(dst + 2 * kStep, o.z);
+        st4<kNtStoreWO>(dst + 3 * kStep, o.w);
       } else {
-        st16<kNtStoreWO>(p.dst + pos + u * kTile, o);
+        st16<kNtStoreWO>(dst, o);
       }
     }
   }

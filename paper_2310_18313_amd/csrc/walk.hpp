@@ -530,6 +530,15 @@ template <bool NT = false> __device__ __forceinline__ void st16(void* p, uint4 v
   }
 }
 
+template <bool NT = false> __device__ __forceinline__ uint32_t ld4(const void* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(static_cast<const uint32_t*>(p));
+  else return *static_cast<const uint32_t*>(p);
+}
+template <bool NT = false> __device__ __forceinline__ void st4(void* p, uint32_t v) {
+  if constexpr (NT) __builtin_nontemporal_store(v, static_cast<uint32_t*>(p));
+  else *static_cast<uint32_t*>(p) = v;
+}
+
 typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 template <bool NT = false> __device__ __forceinline__ uint2 ld8(const void* p) {
   if constexpr (NT) {
