@@ -37,6 +37,12 @@ struct QuantStatsOp {
     signal = noise = 0.0;
     n_nonzero = n_under = n_over = n_nonfinite = 0;
   }
+  __device__ __forceinline__ void add_error(float r, float pv) {
+    const double rd = (double)r;
+    const double e = __builtin_fma(-(double)pv, rs, rd);
+    signal = __builtin_fma(rd, rd, signal);
+    noise = __builtin_fma(e, e, noise);
+  }
   __device__ __forceinline__ void one(uint32_t rbits, uint32_t code) {
     const float r = SrcTraits<SRC>::dec(rbits);
     const float pv = fp8_to_f32<FMT>(code);
@@ -44,33 +50,84 @@ struct QuantStatsOp {
       ++n_nonfinite;
       return;
     }
-    const double rd = (double)r;
-    const double e = rd - (double)pv * rs;
-    signal += rd * rd;
-    noise += e * e;
+    add_error(r, pv);
     const uint32_t mag = code & 0x7Fu;
     n_nonzero += (r != 0.0f);
     n_under += (r != 0.0f) && mag == 0u;
     n_over += mag == Fp8Traits<FMT>::kTop;
   }
-  // the 16 consecutive elements at `pos`, by this thread alone
-  __device__ __forceinline__ void full_group(long long pos) {
+  // 16 elements, kRuns runs of consecutive ones: a whole tile's groups take 16 bytes of the reference at a time, contiguous over the
+  // workgroup.  What bounds this is the vector unit: two conversions and three float64 fused multiply-adds per element
+  // are what it cannot do without, so everything else is asked of the group as a whole first, by integer maxima and
+  // minima of the reference's bits and tests of four codes at a time: mostly nothing is zero, on the top code or not finite.
+  // (Element by element, 25 instructions: 157 us for 125e6 elements with an fp32 reference.)
+  static constexpr int kRuns = kLoads, kRun = kGroup / kRuns;
+  struct Regs { uint4 r[kLoads]; uint32_t q[4]; };
+  template <bool kSplit> __device__ __forceinline__ void load(Regs& g, long long pos0) const {
+    constexpr int kStep = kSplit ? kTile / kRuns : kRun;
+    const long long pos = pos0 + threadIdx.x * (kSplit ? kRun : kGroup);
     const elem_t* rp = static_cast<const elem_t*>(p.ref) + pos;
-    uint4 r[kLoads];
 #pragma unroll
-    for (int k = 0; k < kLoads; ++k) r[k] = ld16<kNtLoadRO>(rp + k * kPer);
-    const uint4 qq = ld16<kNtLoadRO>(p.q + pos);
+    for (int k = 0; k < kLoads; ++k) g.r[k] = ld16<kNtLoadRO>(rp + k * kStep);
+#pragma unroll
+    for (int k = 0; k < kRuns; ++k) {
+      if constexpr (kRun == 8) {
+        const uint2 c = ld8<kNtLoadRO>(p.q + pos + k * kStep);
+        g.q[2 * k] = c.x;
+        g.q[2 * k + 1] = c.y;
+      } else {
+        g.q[k] = ld4<kNtLoadRO>(p.q + pos + k * kStep);
+      }
+    }
+  }
+  __device__ __forceinline__ void accumulate(const Regs& g) {
     uint32_t w[kW];
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
-      w[4 * k] = r[k].x; w[4 * k + 1] = r[k].y; w[4 * k + 2] = r[k].z; w[4 * k + 3] = r[k].w;
+      w[4 * k] = g.r[k].x; w[4 * k + 1] = g.r[k].y; w[4 * k + 2] = g.r[k].z; w[4 * k + 3] = g.r[k].w;
     }
-    const uint32_t qw[4] = {qq.x, qq.y, qq.z, qq.w};
+    uint32_t gmax = 0, gmin = 0xFFFFFFFFu, all_nz = 0x80808080u, any = 0;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const uint32_t bits = kSrc16<SRC> ? (w[(j >> 1) % kW] >> ((j & 1) * 16)) & 0xFFFFu : w[j % kW];
-      one(bits, (qw[j >> 2] >> ((j & 3) * 8)) & 0xFFu);
+    for (int j = 0; j < kW; ++j) {
+      src_fold<SRC>(gmax, w[j]);
+      src_fold_min<SRC>(gmin, w[j]);
     }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t mag = g.q[k] & 0x7F7F7F7Fu;
+      all_nz &= mag + 0x7F7F7F7Fu;                                         // bit 7 of a byte: its magnitude is not zero
+      any |= mag + (0x80808080u - Fp8Traits<FMT>::kTopX4);                 // ... it is the top code or beyond it
+    }
+    if (src_final<SRC>(gmax) >= SrcTraits<SRC>::kNonfinite || src_final_min<SRC>(gmin) == 0 || all_nz != 0x80808080u || (any & 0x80808080u)) {
+#pragma unroll 1
+      for (int j = 0; j < 16; ++j) {
+        uint32_t bits = 0, code = 0;                                       // (no dynamic index into registers)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          if (i != j) continue;
+          bits = kSrc16<SRC> ? (w[(i >> 1) % kW] >> ((i & 1) * 16)) & 0xFFFFu : w[i % kW];
+          code = (g.q[i >> 2] >> ((i & 3) * 8)) & 0xFFu;
+        }
+        one(bits, code);
+      }
+      return;
+    }
+    n_nonzero += kGroup;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float2_t lo = fp8x2_to_f32<FMT, false>(g.q[k]), hi = fp8x2_to_f32<FMT, true>(g.q[k]);
+      const float pv[4] = {lo.x, lo.y, hi.x, hi.y};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int j = 4 * k + i;
+        add_error(SrcTraits<SRC>::dec(kSrc16<SRC> ? (w[(j >> 1) % kW] >> ((j & 1) * 16)) & 0xFFFFu : w[j % kW]), pv[i]);
+      }
+    }
+  }
+  template <bool kSplit> __device__ __forceinline__ void group16(long long pos0) {
+    Regs g;
+    load<kSplit>(g, pos0);
+    accumulate(g);
   }
   __device__ __forceinline__ void group(long long pos, int valid) {
     const elem_t* rp = static_cast<const elem_t*>(p.ref) + pos;
@@ -116,10 +173,12 @@ __global__ __launch_bounds__(kThreads) void quant_stats_kernel(Tables tb, StatsP
       cur = k.tensor;
       op.begin(cur);
     }
-    for (int i = threadIdx.x * kGroup; i < k.len; i += kTile) {
-      if (k.len - i >= kGroup) op.full_group(k.base + i);
-      else op.group(k.base + i, k.len - i);
-    }
+    int tile = 0;
+    for (; tile + kTile <= k.len; tile += kTile) op.template group16<true>(k.base + tile);
+    const int whole = k.len & ~(kGroup - 1), i = tile + threadIdx.x * kGroup;
+    if (i < whole) op.template group16<false>(k.base + tile);
+    const int last = whole + kThreads - 1 - (int)threadIdx.x;              // the incomplete group, a thread per element
+    if (last < k.len) op.group(k.base + last, 1);
   }
   if (cur >= 0) op.flush(p.partials + (b + cur));
 }
