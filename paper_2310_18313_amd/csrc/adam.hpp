@@ -61,7 +61,7 @@ struct InitCastOp {
       note(y[2 * k], (w[k] & 0x7FFFu) != 0);
       note(y[2 * k + 1], (w[k] & 0x7FFF0000u) != 0);
     }
-    st_store16<MASTER>(p.dst, pos, y);
+    st_store<false, MASTER, kGroup>(p.dst, pos, y);
   }
   // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
   __device__ __forceinline__ void full_group(long long pos) {
@@ -171,7 +171,8 @@ __device__ inline bool tame_range(const AdamParams& p, float isg, float ism, flo
   const int eg = ex(isg), em = ex(ism), ev = ex(isv), ew = ex(isw), e1 = ex(p.omb1), e2 = ex(p.omb2);
   const int r1 = ex(p.rbc1), r2 = ex(p.rbc2);                                  // both factors are >= 1
   if (eg > 24 || em < -60 || em > 31 || ev < -90 || ev > 60 || ew < -40 || ew > 60) return false;
-  // payloads: |g| in [2^-16, 2^16), |m| in [2^-9, 2^9), v and |w| in [2^-24, 2^16), or zero
+  // payloads: |g| in [2^-16, 2^16), |m| in [2^-9, 2^9), v and |w| in [2^-24, 2^16), or zero (of a master weight without a
+  // scale nothing is needed: its coefficient is the decay itself)
   if (e1 + eg - 16 < -100 || e2 + 2 * eg - 32 < -120) return false;
   const int vhi = max(16 + ev, e2 + 1 + 2 * (eg + 16)) + 1 + r2 + 1;           // v' / bc2 < 2^vhi
   const int vlo = min(p.b2 == 0.0f ? 1000 : ex(p.b2) - 24 + ev, e2 + 2 * eg - 32) + r2;
@@ -761,7 +762,8 @@ struct AdamUpdateVarOp {
   const AdamParams& p;
   const Tables& tb;
   float inv_sg, inv_sm, inv_sv, inv_sw, sm, sv, sw, sq, decay;
-  bool careful;
+  bool careful, tame;
+  float c[8];                             // coefficients of the tame range
   float vmax, wmax, mmax;
   uint32_t nf;
   __device__ AdamUpdateVarOp(const AdamParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
@@ -771,6 +773,9 @@ struct AdamUpdateVarOp {
     inv_sg = P.inv_sg; inv_sm = P.inv_sm; inv_sv = P.inv_sv; inv_sw = P.inv_sw;
     sm = P.sm; sv = P.sv; sw = P.sw; sq = P.sq;
     careful = P.careful != 0;
+    tame = P.tame != 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) c[i] = P.c[i];
     vmax = wmax = mmax = 0.0f;
     nf = 0;
   }
@@ -783,52 +788,73 @@ struct AdamUpdateVarOp {
     const float upd = (m1 * p.rbc1) / den;
     w1 = __builtin_fmaf(-p.lr, upd, w0 * decay);
   }
-  template <int UN> struct Regs { uint4 gq, mq; float dv[kGroup], dw[kGroup]; };
-  template <int UN> __device__ __forceinline__ void load(Regs<UN>& r, long long tile0) {
-    static_assert(UN == 1, "one group at a time");
-    const long long pos = tile0 + threadIdx.x * kGroup;
-    r.gq = ld16<kNtLoadRO>(p.grad + pos);
-    r.mq = ld16<false>(p.m + pos);
-    st_load16<VFMT>(p.v, pos, r.dv);
-    st_load16<MASTER>(p.w, pos, r.dw);
+  // A whole tile: a thread takes kRun consecutive elements of each of the tile's 16 / kRun parts, so that the widest stream's
+  // 128-bit accesses are contiguous over the workgroup: 8 of each half, or 4 of each quarter with an fp32 master weight.
+  // (16 consecutive elements per thread: 373 us for 125e6 parameters with fp32 master weights, lanes 64 bytes apart and
+  // the compiler's sqrt and division.)
+  static constexpr int kRun = MASTER == kStF32 ? 4 : 8;
+  template <int N> struct Part {
+    StRaw<kStE4M3, N> g, m;
+    StRaw<VFMT, N> v;
+    StRaw<MASTER, N> w;
+  };
+  template <int N> __device__ __forceinline__ void load_part(Part<N>& r, long long a) const {
+    st_load<kNtLoadRO>(p.grad, a, r.g);
+    st_load<kNtLoadRW>(p.m, a, r.m);
+    st_load<kNtLoadRW>(p.v, a, r.v);
+    st_load<kNtLoadRW>(p.w, a, r.w);
   }
-  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& r, long long tile0) {
-    const long long pos = tile0 + threadIdx.x * kGroup;
-    const uint4 gq = r.gq, mq = r.mq;
-    float dv[kGroup], dw[kGroup], dg[kGroup], dm[kGroup];
+  template <bool TAME, int N> __device__ __forceinline__ void update_part(const Part<N>& r, long long a) {
+    float dg[N], dm[N], dv[N], dw[N], tq[N];
 #pragma unroll
-    for (int j = 0; j < kGroup; ++j) { dv[j] = r.dv[j]; dw[j] = r.dw[j]; }
-    const uint32_t gw[4] = {gq.x, gq.y, gq.z, gq.w}, mw[4] = {mq.x, mq.y, mq.z, mq.w};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float2_t g01 = fp8x2_to_f32<GFMT, false>(gw[k]), g23 = fp8x2_to_f32<GFMT, true>(gw[k]);
-      const float2_t m01 = fp8x2_to_f32<kE4M3, false>(mw[k]), m23 = fp8x2_to_f32<kE4M3, true>(mw[k]);
+    for (int k = 0; k < N / 4; ++k) {
+      const float2_t g01 = fp8x2_to_f32<GFMT, false>(r.g.w[k]), g23 = fp8x2_to_f32<GFMT, true>(r.g.w[k]);
       dg[4 * k] = g01.x; dg[4 * k + 1] = g01.y; dg[4 * k + 2] = g23.x; dg[4 * k + 3] = g23.y;
-      dm[4 * k] = m01.x; dm[4 * k + 1] = m01.y; dm[4 * k + 2] = m23.x; dm[4 * k + 3] = m23.y;
     }
-    float tm[kGroup], tq[kGroup];
+    st_decode(r.m, dm);
+    st_decode(r.v, dv);
+    st_decode(r.w, dw);
 #pragma unroll
-    for (int j = 0; j < kGroup; ++j) {
+    for (int j = 0; j < N; ++j) {
       float m1, v1, w1;
-      update(dg[j], dm[j], dv[j], dw[j], m1, v1, w1);
+      if constexpr (TAME) tame_update(dg[j], dm[j], dv[j], dw[j], c, p.lr, m1, v1, w1);
+      else update(dg[j], dm[j], dv[j], dw[j], m1, v1, w1);
       vmax = fmaxf(vmax, v1);
       wmax = fmaxf(wmax, fabsf(w1));
       mmax = fmaxf(mmax, fabsf(m1));
-      tm[j] = m1 * sm;
+      dm[j] = m1 * sm;
       dv[j] = v1 * sv;
       dw[j] = w1 * sw;
       tq[j] = w1 * sq;
     }
-    st_store16<kStE4M3>(p.m, pos, tm);
-    st_store16<VFMT>(p.v, pos, dv);
-    st_store16<MASTER>(p.w, pos, dw);
-    st_store16<kStE4M3>(p.wcopy, pos, tq);
+    st_store<kNtStoreRW, kStE4M3, N>(p.m, a, dm);
+    st_store<kNtStoreRW, VFMT, N>(p.v, a, dv);
+    st_store<kNtStoreRW, MASTER, N>(p.w, a, dw);
+    st_store<kNtStoreWO, kStE4M3, N>(p.wcopy, a, tq);
   }
-  // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
+  static constexpr int kParts = kGroup / kRun;
+  template <int UN> struct Regs { Part<kRun> part[kParts]; };
+  template <int UN> __device__ __forceinline__ void load(Regs<UN>& r, long long tile0) const {
+    static_assert(UN == 1, "one tile at a time");
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) load_part(r.part[k], tile0 + k * (kTile / kParts) + threadIdx.x * kRun);
+  }
+  template <bool TAME, int UN> __device__ __forceinline__ void update_tile(const Regs<UN>& r, long long tile0) {
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) update_part<TAME>(r.part[k], tile0 + k * (kTile / kParts) + threadIdx.x * kRun);
+  }
+  template <int UN> __device__ __forceinline__ void tiles(const Regs<UN>& r, long long tile0) {
+    if (tame) update_tile<true>(r, tile0);
+    else update_tile<false>(r, tile0);
+  }
+  // 16 consecutive elements at `pos`, by this thread alone
   __device__ __forceinline__ void full_group(long long pos) {
-    Regs<1> g;
-    load(g, pos - (long long)threadIdx.x * kGroup);
-    tiles(g, pos - (long long)threadIdx.x * kGroup);
+#pragma unroll
+    for (int k = 0; k < kParts; ++k) {
+      Part<kRun> r;
+      load_part(r, pos + k * kRun);
+      update_part<false>(r, pos + k * kRun);
+    }
   }
   __device__ __forceinline__ void group(long long pos, int valid) {
     for (int j = 0; j < valid; ++j) {

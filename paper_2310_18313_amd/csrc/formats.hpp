@@ -144,55 +144,64 @@ template <> struct StTraits<kStF32> {
   static __device__ __forceinline__ uint32_t enc_careful(float x) { return x != x ? 0x7FC00000u : f2u(x); }
 };
 
-// 16 consecutive elements: 128-bit accesses, decoded to / encoded from fp32 payloads
-template <int K> __device__ __forceinline__ void st_load16(const void* buf, long long pos, float* out) {
-  const typename StTraits<K>::elem_t* q = static_cast<const typename StTraits<K>::elem_t*>(buf) + pos;
-  if constexpr (K == kStE4M3) {
-    const uint4 a = *reinterpret_cast<const uint4*>(q);
-    const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+// N consecutive elements (4, 8 or 16) as raw words, with the widest accesses that takes, and their fp32 payloads.
+template <int K, int N> struct StRaw {
+  static constexpr int kBytes = N * (int)sizeof(typename StTraits<K>::elem_t), kWords = kBytes / 4;
+  uint32_t w[kWords];
+};
+typedef uint32_t st_u4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t st_u2_t __attribute__((ext_vector_type(2)));
+template <bool NT, int K, int N> __device__ __forceinline__ void st_load(const void* buf, long long pos, StRaw<K, N>& r) {
+  const char* q = reinterpret_cast<const char*>(static_cast<const typename StTraits<K>::elem_t*>(buf) + pos);
+  auto ld = [](auto* p) { if constexpr (NT) return __builtin_nontemporal_load(p); else return *p; };
+  if constexpr (StRaw<K, N>::kBytes >= 16) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float2_t lo = fp8x2_to_f32<kE4M3, false>(w[k]), hi = fp8x2_to_f32<kE4M3, true>(w[k]);
-      out[4 * k] = lo.x; out[4 * k + 1] = lo.y; out[4 * k + 2] = hi.x; out[4 * k + 3] = hi.y;
+    for (int i = 0; i < StRaw<K, N>::kWords / 4; ++i) {
+      const st_u4_t a = ld(reinterpret_cast<const st_u4_t*>(q) + i);
+      r.w[4 * i] = a.x; r.w[4 * i + 1] = a.y; r.w[4 * i + 2] = a.z; r.w[4 * i + 3] = a.w;
     }
-  } else if constexpr (K == kStF32) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const uint4 a = *reinterpret_cast<const uint4*>(q + 4 * k);
-      out[4 * k] = u2f(a.x); out[4 * k + 1] = u2f(a.y); out[4 * k + 2] = u2f(a.z); out[4 * k + 3] = u2f(a.w);
-    }
+  } else if constexpr (StRaw<K, N>::kBytes == 8) {
+    const st_u2_t a = ld(reinterpret_cast<const st_u2_t*>(q));
+    r.w[0] = a.x; r.w[1] = a.y;
   } else {
-    const uint4 a = *reinterpret_cast<const uint4*>(q), b = *reinterpret_cast<const uint4*>(q + 8);
-    const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    r.w[0] = ld(reinterpret_cast<const uint32_t*>(q));
+  }
+}
+template <int K, int N> __device__ __forceinline__ void st_decode(const StRaw<K, N>& r, float* out) {
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if constexpr (K == kStF16) {
-        const float2_t f = f16x2_to_f32(w[k]);
-        out[2 * k] = f.x; out[2 * k + 1] = f.y;
-      } else {
-        out[2 * k] = bf16lo_to_f32(w[k]); out[2 * k + 1] = bf16hi_to_f32(w[k]);
-      }
+  for (int k = 0; k < StRaw<K, N>::kWords; ++k) {
+    if constexpr (K == kStE4M3) {
+      const float2_t lo = fp8x2_to_f32<kE4M3, false>(r.w[k]), hi = fp8x2_to_f32<kE4M3, true>(r.w[k]);
+      out[4 * k] = lo.x; out[4 * k + 1] = lo.y; out[4 * k + 2] = hi.x; out[4 * k + 3] = hi.y;
+    } else if constexpr (K == kStF32) {
+      out[k] = u2f(r.w[k]);
+    } else if constexpr (K == kStF16) {
+      const float2_t x = f16x2_to_f32(r.w[k]);
+      out[2 * k] = x.x; out[2 * k + 1] = x.y;
+    } else {
+      out[2 * k] = bf16lo_to_f32(r.w[k]); out[2 * k + 1] = bf16hi_to_f32(r.w[k]);
     }
   }
 }
-template <int K> __device__ __forceinline__ void st_store16(void* buf, long long pos, const float* x) {
-  typename StTraits<K>::elem_t* q = static_cast<typename StTraits<K>::elem_t*>(buf) + pos;
-  if constexpr (K == kStE4M3) {
-    *reinterpret_cast<uint4*>(q) = make_uint4(encode4_fp8<kE4M3>(x[0], x[1], x[2], x[3]), encode4_fp8<kE4M3>(x[4], x[5], x[6], x[7]),
-                                              encode4_fp8<kE4M3>(x[8], x[9], x[10], x[11]), encode4_fp8<kE4M3>(x[12], x[13], x[14], x[15]));
-  } else if constexpr (K == kStF32) {
+template <bool NT, int K, int N> __device__ __forceinline__ void st_store(void* buf, long long pos, const float* x) {
+  char* q = reinterpret_cast<char*>(static_cast<typename StTraits<K>::elem_t*>(buf) + pos);
+  auto st = [](auto v, auto* p) { if constexpr (NT) __builtin_nontemporal_store(v, p); else *p = v; };
+  uint32_t w[StRaw<K, N>::kWords];
 #pragma unroll
-    for (int k = 0; k < 4; ++k)
-      *reinterpret_cast<uint4*>(q + 4 * k) = make_uint4(f2u(x[4 * k]), f2u(x[4 * k + 1]), f2u(x[4 * k + 2]), f2u(x[4 * k + 3]));
+  for (int k = 0; k < StRaw<K, N>::kWords; ++k) {
+    if constexpr (K == kStE4M3) w[k] = encode4_fp8<kE4M3>(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
+    else if constexpr (K == kStF32) w[k] = f2u(x[k]);
+    else if constexpr (K == kStF16) w[k] = encode2_f16(x[2 * k], x[2 * k + 1]);
+    else w[k] = encode1_bf16(x[2 * k]) | (encode1_bf16(x[2 * k + 1]) << 16);
+  }
+  if constexpr (StRaw<K, N>::kBytes >= 16) {
+#pragma unroll
+    for (int i = 0; i < StRaw<K, N>::kWords / 4; ++i)
+      st(st_u4_t{w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]}, reinterpret_cast<st_u4_t*>(q) + i);
+  } else if constexpr (StRaw<K, N>::kBytes == 8) {
+    st(st_u2_t{w[0], w[1]}, reinterpret_cast<st_u2_t*>(q));
   } else {
-    uint32_t w[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if constexpr (K == kStF16) w[k] = encode2_f16(x[2 * k], x[2 * k + 1]);
-      else w[k] = encode1_bf16(x[2 * k]) | (encode1_bf16(x[2 * k + 1]) << 16);
-    }
-    *reinterpret_cast<uint4*>(q) = make_uint4(w[0], w[1], w[2], w[3]);
-    *reinterpret_cast<uint4*>(q + 8) = make_uint4(w[4], w[5], w[6], w[7]);
+    st(w[0], reinterpret_cast<uint32_t*>(q));
   }
 }
 template <int K> __device__ __forceinline__ float st_load1(const void* buf, long long i) {
