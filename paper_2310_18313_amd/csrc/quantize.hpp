@@ -630,6 +630,8 @@ struct RequantOp {
   const Tables& tb;
   float inv_src, sg;
   bool careful;
+  bool same;              // the shared scale is the source's: the codes stay as they are
+  uint32_t cmax;          // ... and the largest magnitude among them (two packed maxima)
   float vmax;
   uint32_t n_elems, nz_top, nz_code, nz_in, nonfinite;
   __device__ RequantOp(const RequantParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
@@ -637,20 +639,49 @@ struct RequantOp {
     inv_src = uniform_load(&p.src_meta[t].inv_scale);
     sg = uniform_load(p.shared + t);
     careful = (uniform_load(&p.src_meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0;
+    same = ((f2u(inv_src) | f2u(sg)) & 0x807FFFFFu) == 0 && inv_src * sg == 1.0f;      // powers of two
+    cmax = 0;
     vmax = 0.0f;
     n_elems = nz_top = nz_code = nz_in = nonfinite = 0;
   }
   __device__ __forceinline__ bool fast() const { return !careful; }
+  // Four codes.  The counters only of groups where they can change: `count`.
   __device__ __forceinline__ uint32_t word(uint32_t w) {
     const float2_t a = fp8x2_to_f32<FMT, false>(w), b = fp8x2_to_f32<FMT, true>(w);
     const float y0 = (a.x * inv_src) * sg, y1 = (a.y * inv_src) * sg, y2 = (b.x * inv_src) * sg, y3 = (b.y * inv_src) * sg;
     vmax = fmaxf(fmaxf(vmax, fmaxf(fabsf(y0), fabsf(y1))), fmaxf(fabsf(y2), fabsf(y3)));
-    const uint32_t c = encode4_fp8<FMT>(y0, y1, y2, y3);
+    return encode4_fp8<FMT>(y0, y1, y2, y3);
+  }
+  __device__ __forceinline__ void count(uint32_t w, uint32_t c) {
     const uint32_t mag = c & 0x7F7F7F7Fu;
     nz_in += nonzero_bytes7(w & 0x7F7F7F7Fu);
     nz_code += nonzero_bytes7(mag);
     nz_top += nonzero_bytes7(mag ^ Fp8Traits<FMT>::kTopX4);
-    return c;
+  }
+  // 16 codes.  Ranks whose amax lies in the same binade share their scale already: then there is nothing to convert (the
+  // tensors with NaN codes, which would get their canonical form, take the careful path).  No code on the top and none
+  // zero: nothing to count.  (Converting and counting everything, 8 instructions per code: 51 us for 125e6 codes.)
+  __device__ __forceinline__ uint4 codes16(const uint4& in) {
+    uint4 o = in;
+    if (!same) o = make_uint4(word(in.x), word(in.y), word(in.z), word(in.w));
+    const uint32_t w[4] = {in.x, in.y, in.z, in.w}, c[4] = {o.x, o.y, o.z, o.w};
+    uint32_t all_nz = 0x80808080u, any = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t mag = c[k] & 0x7F7F7F7Fu;
+      all_nz &= mag + 0x7F7F7F7Fu;                                         // bit 7 of a byte: its magnitude is not zero
+      any |= mag + (0x80808080u - Fp8Traits<FMT>::kTopX4);                 // ... it is the top code
+      if (same) {
+        src_fold<kSrcBF16>(cmax, mag & 0x007F007Fu);
+        src_fold<kSrcBF16>(cmax, (mag >> 8) & 0x007F007Fu);
+      }
+    }
+    if (all_nz != 0x80808080u || (any & 0x80808080u)) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) count(w[k], c[k]);
+      n_elems += kGroup;
+    }
+    return o;
   }
   template <int UN> struct Regs { uint4 a[UN]; };
   template <int UN> __device__ __forceinline__ void load(Regs<UN>& g, long long pos0) {
@@ -662,8 +693,7 @@ struct RequantOp {
     const long long pos = pos0 + threadIdx.x * kGroup;
 #pragma unroll
     for (int u = 0; u < UN; ++u)
-      st16<kNtStoreRW>(p.dst + pos + u * kTile, make_uint4(word(g.a[u].x), word(g.a[u].y), word(g.a[u].z), word(g.a[u].w)));
-    n_elems += UN * kGroup;
+      st16<kNtStoreRW>(p.dst + pos + u * kTile, codes16(g.a[u]));
   }
   // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
   __device__ __forceinline__ void full_group(long long pos) {
@@ -688,7 +718,7 @@ struct RequantOp {
   using Stats = BlockStats<1, 2>;
   template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
     BlockStats<1, 2, uint32_t> s;
-    s.mx[0] = f2u(vmax);
+    s.mx[0] = f2u(fmaxf(vmax, fp8_to_f32<FMT>(src_final<kSrcBF16>(cmax))));
     s.ct[0] = n_elems - nz_top;
     s.ct[1] = nz_in - nz_code;                 // non-zero codes in, zero codes out (a NaN code is non-zero on both sides)
     s.orv = nonfinite;
