@@ -410,7 +410,7 @@ fp8lm_status fp8lm_get_moment_speculation_stats(fp8lm_ctx* ctx, uint64_t* calls 
  * forbid allocation.  Same arithmetic, same kernels, same results, bit for bit; what a context keeps in
  * hipMalloc'd memory (tensor and chunk tables, the per-tensor scales that the first pass hands to the second,
  * the per-workgroup reduction records) lives in a fixed array inside the library's device image instead (about
- * 6.2 MiB, held by every GPU the library runs on until the process ends).  Every call rebuilds the tables in
+ * 6.4 MiB, held by every GPU the library runs on until the process ends).  Every call rebuilds the tables in
  * that array from `tensors` with small kernels on `stream` (arguments travel as kernel arguments: no copy from
  * host memory), then runs the two passes.  The call itself calls no allocator of any kind.
  *   device       : GPU that owns all buffers; tensors, tensor_flags: host arrays of n entries, read during the
