@@ -638,7 +638,9 @@ struct RequantOp {
   __device__ __forceinline__ void begin(int t) {
     inv_src = uniform_load(&p.src_meta[t].inv_scale);
     sg = uniform_load(p.shared + t);
-    careful = (uniform_load(&p.src_meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0;
+    // codes that stand for more than fp32 holds (amax of the last binade) come out as the top code, element by element
+    careful = (uniform_load(&p.src_meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0 ||
+              !(inv_src * Fp8Traits<FMT>::kMax <= 3.4028234663852886e38f);
     same = ((f2u(inv_src) | f2u(sg)) & 0x807FFFFFu) == 0 && inv_src * sg == 1.0f;      // powers of two
     cmax = 0;
     vmax = 0.0f;

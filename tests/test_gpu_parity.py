@@ -509,6 +509,36 @@ def test_shared_scale_requantize_and_sum(fmt):
 
 
 @pytest.mark.parametrize("fmt", [B.E5M2, B.E4M3])
+def test_requantize_where_codes_stand_for_more_than_fp32_holds(fmt):
+    """Scales around the one whose largest code times 1/s' leaves fp32 (gradients of the last binade): the value is infinite
+    on the way, so the code becomes the top code, also where the shared scale is the rank's own and codes are otherwise
+    copied.  Whole tiles, whole groups and single elements."""
+    n, exps = 3 * 4096 + 37, [-113, -112, -111, -120, -119, 0]
+    lay = synth.Layout([f"s{i}" for i in range(len(exps))], [n] * len(exps))
+    nt, tens, ctx, cfg = lay.n_tensors, O.tensors_array(lay.tensors()), B.Context(lay.tensors()), B.autoscale_cfg()
+    rng = np.random.default_rng(8)
+    q = rng.integers(0, (0x7B if fmt == B.E5M2 else 0x7E) + 1, lay.total).astype(np.uint8) | (rng.integers(0, 2, lay.total).astype(np.uint8) << 7)
+    d_q = torch.from_numpy(q).to(DEV)
+    meta = B.meta_to_numpy(ctx.new_meta(cfg), nt)
+    meta["scale"], meta["inv_scale"], meta["amax"] = np.ldexp(1.0, exps), np.ldexp(1.0, [-e for e in exps]), 3.0e38
+    d_meta = B.meta_from_numpy(meta, DEV)
+    for shift in (0, -1):
+        shared = np.ldexp(meta["scale"], shift).astype(np.float32)
+        dst, out = torch.zeros(lay.total, dtype=torch.uint8, device=DEV), ctx.new_meta(cfg)
+        say(f"requantize at the end of fp32: fmt={fmt} shared = own * 2^{shift}")
+        ctx.requantize_fp8(d_q, fmt, d_meta, torch.from_numpy(shared).to(DEV), dst, out)
+        torch.cuda.synchronize()
+        ref, ref_meta = np.zeros(lay.total, np.uint8), O.new_meta(nt, P.oracle_cfg(cfg))
+        O.requantize_fp8(q, fmt, meta, shared, tens, ref, ref_meta)
+        got = B.meta_to_numpy(out, nt)
+        for t, (off, k) in enumerate(lay.tensors()):
+            assert np.array_equal(dst[off:off + k].cpu().numpy(), ref[off:off + k]), (shift, t)
+            bad = P.meta_equal(got[t], ref_meta[t], ["scale", "inv_scale", "amax", "amax_deq", "flags", "n_sat", "n_underflow"])
+            assert not bad, (shift, t, bad, got[t], ref_meta[t])
+        assert (ref_meta["flags"][[0, 3] if fmt == B.E5M2 else [3]] & B.FLAG_NONFINITE).all()
+
+
+@pytest.mark.parametrize("fmt", [B.E5M2, B.E4M3])
 @pytest.mark.parametrize("n_ranks", [9, 13, 128])
 def test_sum_of_many_ranks(fmt, n_ranks):
     """More ranks than have a kernel of their own (the paper's communication study uses 128): shared scale and
