@@ -75,15 +75,17 @@ struct AmaxParams {
 };
 
 // Exponent of a gradient tensor's scale from the amax history as it stands (the rule of scale_from_history), or kKeepScale
-// if the history is all zero: for a whole workgroup that is about to cast with it, without writing anything.  Integer arithmetic on values all lanes share, so it runs on the scalar unit (amax values are not negative, their bit
-// patterns are ordered like they are).
+// if the history is all zero, without writing anything.  UNIFORM: for a whole workgroup that is about to cast with it; integer
+// arithmetic on values all lanes share, so it runs on the scalar unit (amax values are not negative, their bit patterns are
+// ordered like they are).  The scalar epilogue, which goes on to write the history, reads it with ordinary loads.
 constexpr int kKeepScale = 1000;
-__device__ __forceinline__ int predicted_exponent(const fp8lm_meta* M, uint32_t fmax_bits, int hist_window, int margin) {
+template <bool UNIFORM> __device__ __forceinline__ int predicted_exponent(const fp8lm_meta* M, uint32_t fmax_bits, int hist_window, int margin) {
+  auto load = [](const auto* q) { if constexpr (UNIFORM) return uniform_load(q); else return *q; };
   const int H = hist_window < 1 ? 1 : (hist_window > FP8LM_HIST ? FP8LM_HIST : hist_window);
   int bits = 0;
-  for (int h = 0; h < H; ++h) bits = max(bits, (int)uniform_load(reinterpret_cast<const uint32_t*>(&M->amax_hist[h])));
+  for (int h = 0; h < H; ++h) bits = max(bits, (int)f2u(load(&M->amax_hist[h])));
   if (bits == 0) return kKeepScale;
-  const int k = pow2_exp(fmax_bits, u2f((uint32_t)bits)) + uniform_load(&M->mu_exp) - margin;
+  const int k = pow2_exp(fmax_bits, u2f((uint32_t)bits)) + load(&M->mu_exp) - margin;
   return k < -126 ? -126 : (k > 126 ? 126 : k);
 }
 // Sets the scale from the amax history as it stands: the largest of the last H entries, times 2^(mu_exp - margin).
@@ -306,7 +308,7 @@ struct CastOp {
     scale = uniform_load(&p.meta[t].scale);
     int e = kKeepScale;
     if constexpr (DELAYED) {
-      e = predicted_exponent(p.meta + t, p.fmax_bits, p.hist_window, p.margin);
+      e = predicted_exponent<true>(p.meta + t, p.fmax_bits, p.hist_window, p.margin);
       if (e != kKeepScale) scale = pow2f(e);
     }
     careful = !DELAYED && (uniform_load(&p.meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0;
@@ -540,7 +542,7 @@ struct CastOp {
   // bookkeeping; otherwise the tensor has to be cast again.  Returns true if the speculation held.
   __device__ bool speculation_verdict(int t, uint32_t abits) {
     fp8lm_meta& M = p.meta[t];
-    const int e = predicted_exponent(p.meta + t, p.fmax_bits, p.hist_window, p.margin);
+    const int e = predicted_exponent<false>(p.meta + t, p.fmax_bits, p.hist_window, p.margin);
     const float used = e != kKeepScale ? pow2f(e) : M.scale;
     bool held;
     if (abits >= SrcTraits<SRC>::kNonfinite) {

@@ -85,8 +85,9 @@ struct Tables {
   unsigned long long* spec_totals;
 };
 
-// A load of something that no kernel writes while another may read it here, from an address all lanes share: through the
-// scalar cache, whatever stores come before it.
+// A load from an address all lanes share, through the scalar cache and whatever stores come before it: the compiler takes
+// what it reads as constant.  So only for what the launch does not write, or writes only once every workgroup that could
+// read it has done so: a tensor's metadata before its units, never in its scalar epilogue (finalize).
 template <class T> __device__ __forceinline__ T uniform_load(const T* p) {
   static_assert(sizeof(T) % 4 == 0, "words");
   struct Words { uint32_t w[sizeof(T) / 4]; } v;
