@@ -76,14 +76,17 @@ struct AmaxParams {
 
 // Exponent of a gradient tensor's scale from the amax history as it stands (the rule of scale_from_history), or kKeepScale
 // if the history is all zero, without writing anything.  UNIFORM: for a whole workgroup that is about to cast with it; integer
-// arithmetic on values all lanes share, so it runs on the scalar unit (amax values are not negative, their bit patterns are
-// ordered like they are).  The scalar epilogue, which goes on to write the history, reads it with ordinary loads.
+// arithmetic on values all lanes share, so it runs on the scalar unit (bit patterns of values that are not negative are ordered
+// like they are; of a negative one the pattern is negative too).  The scalar epilogue, which goes on to write the history, reads it with ordinary loads.
 constexpr int kKeepScale = 1000;
 template <bool UNIFORM> __device__ __forceinline__ int predicted_exponent(const fp8lm_meta* M, uint32_t fmax_bits, int hist_window, int margin) {
   auto load = [](const auto* q) { if constexpr (UNIFORM) return uniform_load(q); else return *q; };
   const int H = hist_window < 1 ? 1 : (hist_window > FP8LM_HIST ? FP8LM_HIST : hist_window);
   int bits = 0;
-  for (int h = 0; h < H; ++h) bits = max(bits, (int)f2u(load(&M->amax_hist[h])));
+  for (int h = 0; h < H; ++h) {
+    const int b = (int)f2u(load(&M->amax_hist[h]));
+    bits = b <= 0x7F800000 ? max(bits, b) : bits;          // a NaN (of a caller's making) is smaller than nothing there
+  }
   if (bits == 0) return kKeepScale;
   const int k = pow2_exp(fmax_bits, u2f((uint32_t)bits)) + load(&M->mu_exp) - margin;
   return k < -126 ? -126 : (k > 126 ? 126 : k);

@@ -10,6 +10,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle as O
 import parity as P
 from conftest import say
 from paper_2310_18313_amd import binding as B
@@ -188,3 +189,41 @@ def test_adam_step_with_a_pair_of_moment_buffers_equals_the_two_pass_step(grad_f
                       (pair.m, pair.m_other, B.adam_hparams(wl.lr, 99, wcopy=wcopy, m_scale_mode=B.MSCALE_PREDICTED))):
         with pytest.raises((B.Fp8lmError, ValueError)):
             args(mi, mo, h)
+
+
+@pytest.mark.parametrize("fmt,dtype", [(B.E5M2, torch.bfloat16), (B.E4M3, torch.float32)])
+def test_odd_entries_of_the_amax_history(fmt, dtype):
+    """A history that a caller has written: NaN, negative, subnormal and zero entries.  The delayed cast against the
+    oracle, the one-call quantisation against the two calls: the scale the codes are made with is the one in the metadata."""
+    odd = [np.nan, -3.0, 0.5, 1e-42, -0.0, 0.02, -np.nan, 3e38]
+    cases = [(a, b) for a in odd for b in odd]
+    lay = synth.Layout([f"t{i}" for i in range(len(cases))], [4096 + 19] * len(cases))
+    wl = synth.Workload("odd-history", lay, lr=1e-3, sigma=1e-3, hist_window=2)
+    nt, cfg, ctx = lay.n_tensors, B.autoscale_cfg(hist_window=2), B.Context(lay.tensors())
+    tens, ocfg = O.tensors_array(lay.tensors()), P.oracle_cfg(cfg)
+    grad = torch.zeros(lay.total, dtype=dtype, device=DEV)
+    synth.fill_gradients(grad, wl, 5, 1)
+    meta = B.meta_to_numpy(ctx.new_meta(cfg), nt)
+    meta["amax_hist"][:, :2] = np.array(cases, np.float32)
+    meta["scale"], meta["inv_scale"] = 2.0 ** 10, 2.0 ** -10
+    src, kind = (grad.cpu().numpy(), O.SRC_F32) if dtype == torch.float32 else (synth.bits16(grad), O.SRC_BF16)
+    ref, ref_meta = np.zeros(lay.total, np.uint8), meta.copy()
+    O.cast_fp8_delayed(src, tens, ref, fmt, ref_meta, ocfg, src_type=kind)
+    q, d_meta = torch.zeros(lay.total, dtype=torch.uint8, device=DEV), B.meta_from_numpy(meta, DEV)
+    say(f"odd history, delayed cast fmt={fmt} {dtype}")
+    ctx.cast_fp8_delayed(grad, q, fmt, d_meta, cfg)
+    got, got_meta = q.cpu().numpy(), B.meta_to_numpy(d_meta, nt)
+    for t, (off, n) in enumerate(lay.tensors()):
+        assert np.array_equal(got[off:off + n], ref[off:off + n]), (cases[t], got_meta[t], ref_meta[t])
+        bad = P.meta_equal(got_meta[t], ref_meta[t], P.ALL_FIELDS)
+        assert not bad, (cases[t], bad, got_meta[t], ref_meta[t])
+    say(f"odd history, one call and two calls fmt={fmt} {dtype}")
+    one, two = B.meta_from_numpy(meta, DEV), B.meta_from_numpy(meta, DEV)
+    q1, q2 = torch.zeros_like(q), torch.zeros_like(q)
+    ctx.quantize_fp8(grad, q1, fmt, one, cfg)
+    ctx.amax_scale(grad, fmt, two, cfg)
+    ctx.cast_fp8(grad, q2, fmt, two, cfg)
+    a, b = B.meta_to_numpy(one, nt), B.meta_to_numpy(two, nt)
+    for t, (off, n) in enumerate(lay.tensors()):
+        assert torch.equal(q1[off:off + n], q2[off:off + n]), cases[t]
+        assert a[t].tobytes() == b[t].tobytes(), (cases[t], a[t], b[t])
