@@ -269,7 +269,8 @@ Tables marked_tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   const long long units = (long long)c->n_chunks << tb.unit_shift;
   // with nothing marked the workgroups only cost their start; two thirds of 1.8e9 elements marked (heavy tails) took 1089 us
   // with four workgroups per compute unit, 944 with eight, 935 with sixteen
-  *grid = (int)std::min<long long>((units > 65536 ? 8ll : 4ll) * c->num_cus, units);
+  const int per_cu = std::min(units > 65536 ? 8 : 4, c->blocks_per_cu);
+  *grid = (int)std::min<long long>((long long)per_cu * c->num_cus, units);
   return tb;
 }
 
@@ -1135,7 +1136,11 @@ fp8lm_status fp8lm_memory_skeleton(fp8lm_ctx* c, int32_t shape, void* const* buf
   p.n_tiles = n_elems / kTile;
   p.sink = reinterpret_cast<uint32_t*>(c->d_partials);
   const dim3 b(kThreads);
-  auto grid = [&](int un) { return dim3((unsigned)std::min(kMaxGrid, (p.n_tiles + un - 1) / un)); };
+  p.ranges = shape == FP8LM_SKEL_UPDATE_RANGES || c->blocks_per_cu < kMaxBlocksPerCu ? 1 : 0;
+  auto grid = [&](int un) {
+    const long long all = (p.n_tiles + un - 1) / un;
+    return dim3((unsigned)std::min(p.ranges ? (long long)c->num_cus * c->blocks_per_cu : kMaxGrid, all));
+  };
   hipStream_t s = (hipStream_t)stream;
   Timed tm(c, s, FP8LM_K_SKELETON);
   switch (shape) {
@@ -1164,11 +1169,9 @@ fp8lm_status fp8lm_memory_skeleton(fp8lm_ctx* c, int32_t shape, void* const* buf
       p.s2[0] = static_cast<const uint16_t*>(bufs[2]); p.s2[1] = static_cast<const uint16_t*>(bufs[3]);
       p.d1[0] = static_cast<uint8_t*>(bufs[1]); p.d1[1] = static_cast<uint8_t*>(bufs[4]);
       p.d2[0] = static_cast<uint16_t*>(bufs[2]); p.d2[1] = static_cast<uint16_t*>(bufs[3]);
-      if (shape == FP8LM_SKEL_UPDATE) hipLaunchKernelGGL((skeleton_kernel<2, 2, 2, 2, kUnUpdate>), grid(kUnUpdate), b, 0, s, p);
+      if (shape == FP8LM_SKEL_UPDATE || shape == FP8LM_SKEL_UPDATE_RANGES) hipLaunchKernelGGL((skeleton_kernel<2, 2, 2, 2, kUnUpdate>), grid(kUnUpdate), b, 0, s, p);
       else if (shape == FP8LM_SKEL_UPDATE_READS) hipLaunchKernelGGL((skeleton_kernel<2, 2, 0, 0, kUnUpdate>), grid(kUnUpdate), b, 0, s, p);
-      else if (shape == FP8LM_SKEL_UPDATE_WRITES) hipLaunchKernelGGL((skeleton_kernel<0, 0, 2, 2, kUnUpdate>), grid(kUnUpdate), b, 0, s, p);
-      else hipLaunchKernelGGL((skeleton_kernel<2, 2, 2, 2, 1, true>),
-                              dim3((unsigned)std::min<long long>((long long)c->num_cus * kMaxBlocksPerCu, p.n_tiles)), b, 0, s, p);
+      else hipLaunchKernelGGL((skeleton_kernel<0, 0, 2, 2, kUnUpdate>), grid(kUnUpdate), b, 0, s, p);
       break;
   }
   return after_launch();

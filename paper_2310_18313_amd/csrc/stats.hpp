@@ -239,8 +239,6 @@ __global__ __launch_bounds__(kThreads) void copy_kernel(const uint4* __restrict_
 // Memory-only skeletons of the hot kernels: the same grid, walk, access widths, access layout and
 // cache policies as the kernels they stand for, with the arithmetic replaced by XORs.  What they reach is the
 // bandwidth ceiling of that access pattern on this machine; the real kernels are measured against it.
-//   RANGES : 0: a workgroup takes UN tiles and ends, as the kernels do; 1: a persistent grid, every workgroup walking a
-//   range of its own, which shows where a buffer lies in HBM more clearly than the kernels feel it;
 //   NS1 / NS2 : number of 8-bit / 16-bit streams read;  ND1 / ND2 : number of 8-bit / 16-bit streams written.
 // A thread takes elements [8L, 8L+8) of both halves of a 4096-element tile (L = thread index), like the update and
 // cast kernels: 64-bit accesses on 8-bit streams, 128-bit accesses on 16-bit streams, contiguous over the workgroup.
@@ -250,13 +248,15 @@ struct SkeletonParams {
   uint8_t* d1[2];
   uint16_t* d2[2];
   long long n_tiles;
+  int32_t ranges;        // 0: a workgroup takes UN tiles and ends, as the kernels do; 1: a persistent grid, every workgroup walking a
+                         // range of its own, as they do under a limit on workgroups; shows where a buffer lies in HBM more clearly
   uint32_t* sink;        // a word that pure reads could write, so that they cannot be optimised away
 };
-template <int NS1, int NS2, int ND1, int ND2, int UN, bool RANGES = false>
+template <int NS1, int NS2, int ND1, int ND2, int UN>
 __global__ __launch_bounds__(kThreads) void skeleton_kernel(SkeletonParams p) {
-  const long long t0 = RANGES ? p.n_tiles * blockIdx.x / gridDim.x : (long long)blockIdx.x * UN;
-  const long long t1 = RANGES ? p.n_tiles * (blockIdx.x + 1) / gridDim.x : p.n_tiles;
-  const long long stride = RANGES ? UN : (long long)gridDim.x * UN;      // one round unless the grid is at its limit
+  const long long t0 = p.ranges ? p.n_tiles * blockIdx.x / gridDim.x : (long long)blockIdx.x * UN;
+  const long long t1 = p.ranges ? p.n_tiles * (blockIdx.x + 1) / gridDim.x : p.n_tiles;
+  const long long stride = p.ranges ? UN : (long long)gridDim.x * UN;      // one round unless the grid is at its limit
   uint32_t acc = 0;
   auto body = [&](long long tile, auto un_tag) {
     constexpr int U = decltype(un_tag)::value;
