@@ -161,10 +161,11 @@ fp8lm_status fp8lm_destroy(fp8lm_ctx* ctx);
  * that a launch uses at most, 1..15, each walking one contiguous range of chunks; 16 = no limit: chunks are cut into
  * units of one to four tiles of 4096 elements, one workgroup each (measured faster at every size on MI355X).
  * single_pass_min_chunks: how the per-tensor statistics of the workgroups are combined.  With at least
- * this many chunks per workgroup, in the same launch (each workgroup bumps a per-tensor ticket, the one
- * that completes it finishes the tensor); with fewer, in a second tiny launch, because the tickets then
- * cost more than the data.  0 = always in the same launch; 2^30, the default: the library chooses (tickets
- * for the smallest launches only); results are identical either way.
+ * this many chunks per workgroup of the launch, in the same launch (each workgroup bumps a per-tensor ticket, the
+ * one that completes it finishes the tensor); with fewer, in a second tiny launch, because the tickets then
+ * cost more than the data.  0 = always in the same launch (without a limit on workgroups, a large launch then has 16
+ * per compute unit that walk ranges); 2^30, the default: the library chooses (tickets for the smallest launches
+ * only); results are identical either way.
  * Rebuilds the chunk table (synchronises the device; not to be called while a stream is being captured).
  * A HIP graph captured from this context before the call holds the old tables and must not be replayed
  * afterwards.  On an error the context keeps its previous tuning and tables.

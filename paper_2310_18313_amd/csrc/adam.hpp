@@ -82,13 +82,13 @@ struct InitCastOp {
     }
   }
   using Stats = BlockStats<1, 2>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
+  __device__ __forceinline__ void flush(long long u) {
     BlockStats<1, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.ct[0] = n_sat;
     s.ct[1] = n_und;
     s.orv = 0;
-    collect<FINISH>(tb, *this, t, u, s);
+    collect(tb, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -339,11 +339,11 @@ struct AdamAmaxOp {
     for (int j = 0; j < valid; ++j) elem(fp8_to_f32<GFMT>(p.grad[pos + j]), fp8_to_f32<kE4M3>(p.m[pos + j]));
   }
   using Stats = BlockStats<1, 0>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
+  __device__ __forceinline__ void flush(long long u) {
     BlockStats<1, 0, uint32_t> s;
     s.mx[0] = acc;
     s.orv = 0;
-    collect<FINISH>(tb, *this, t, u, s);
+    collect(tb, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const uint32_t abits = s.mx[0];
@@ -604,7 +604,7 @@ struct AdamUpdateOp {
   }
 
   using Stats = BlockStats<3, STATS ? 8 : 0>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
+  __device__ __forceinline__ void flush(long long u) {
     BlockStats<3, STATS ? 8 : 0, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = f2u(wmax);
@@ -615,7 +615,7 @@ struct AdamUpdateOp {
       for (int i = 0; i < 8; ++i) s.ct[i] = cnt[i] + (first_lane ? wcnt[i] : 0u);
     }
     s.orv = nf;
-    collect<FINISH>(tb, *this, t, u, s);
+    collect(tb, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     unsigned long long c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -741,7 +741,7 @@ struct AdamMomentRedoOp {
   }
   static constexpr bool kFinishes = false;     // nothing to reduce: the metadata is complete
   using Stats = BlockStats<1, 0>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int, long long) {}
+  __device__ __forceinline__ void flush(long long) {}
   __device__ void finalize(int, const TensorDesc&, const Stats&) {}
 };
 
@@ -888,13 +888,13 @@ struct AdamUpdateVarOp {
     M.n_underflow = 0;
   }
   using Stats = BlockStats<3, 0>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
+  __device__ __forceinline__ void flush(long long u) {
     BlockStats<3, 0, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = f2u(wmax);
     s.mx[2] = f2u(mmax);
     s.orv = nf;
-    collect<FINISH>(tb, *this, t, u, s);
+    collect(tb, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float A_v = u2f(s.mx[0]), A_w = u2f(s.mx[1]), A_m = u2f(s.mx[2]);

@@ -256,17 +256,26 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   // In the deferred form a second launch finishes the tensors; see walk.hpp for the two forms' costs.  Unless told otherwise
   // tickets are for launches of at most 64 units: a step of 2^18 parameters (64 units) takes 26.7 us with and 35.9 without
   // them, one of 50 tensors with 66 000 elements in all 31.2 and 44.2; at 256 units 37.4 and 36.2, at 1024 141 and 36.
+  // A caller's threshold is compared with the chunks per workgroup of this launch.
   constexpr int kTicketUnits = 64;
   tb.deferred = c->single_pass_min_chunks == kLibraryChooses
                     ? units() > kTicketUnits
-                    : c->single_pass_min_chunks > 0 && c->n_chunks / grid_of(c) < c->single_pass_min_chunks;
+                    : c->single_pass_min_chunks > 0 && c->n_chunks / *grid < c->single_pass_min_chunks;
+  // tickets that a caller wants at any size: of a persistent grid, which has a ticket for each workgroup and tensor and not
+  // one for each unit (amax and cast of a GPT-7B layer: 0.57 ms instead of 3.05)
+  const long long persistent = (long long)c->num_cus * kMaxBlocksPerCu;
+  if (!tb.deferred && tb.one_unit && units() > persistent) {
+    tb.unit_elems = c->chunk_elems;
+    tb.unit_shift = tb.one_unit = 0;
+    *grid = grid_of(c);
+  }
   return tb;
 }
 // The tables and the grid of the second round of a speculation (walk_marked); `un` and `record` as for the first.
 Tables marked_tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   Tables tb = tables_of(c, un, record, grid);
-  tb.deferred = ((long long)c->n_chunks << tb.unit_shift) > 256;
   const long long units = (long long)c->n_chunks << tb.unit_shift;
+  if (c->single_pass_min_chunks == kLibraryChooses) tb.deferred = units > 256;
   // with nothing marked the workgroups only cost their start; two thirds of 1.8e9 elements marked (heavy tails) took 1089 us
   // with four workgroups per compute unit, 944 with eight, 935 with sixteen
   const int per_cu = std::min(units > 65536 ? 8 : 4, c->blocks_per_cu);

@@ -163,11 +163,11 @@ struct AmaxOp {
     for (int j = 0; j < valid; ++j) src_fold1<SRC>(acc, q[j]);
   }
   using Stats = BlockStats<1, 0>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
+  __device__ __forceinline__ void flush(long long u) {
     BlockStats<1, 0, uint32_t> s;
     s.mx[0] = src_final<SRC>(acc);
     s.orv = 0;
-    collect<FINISH>(tb, *this, t, u, s);
+    collect(tb, u, s);
   }
   // scalar epilogue, one thread per tensor
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
@@ -504,7 +504,7 @@ struct CastOp {
   }
   static constexpr bool kFinishes = true;      // walk_marked
   using Stats = BlockStats<3, 2>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
+  __device__ __forceinline__ void flush(long long u) {
     BlockStats<3, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = src_final<SRC>(amax16);
@@ -512,7 +512,7 @@ struct CastOp {
     s.ct[0] = n_elems - nz_top;                 // codes on the top magnitude
     s.ct[1] = (n_elems - nz_code) - z_in;       // zero codes that did not come from zero inputs
     s.orv = 0;
-    collect<FINISH>(tb, *this, t, u, s);
+    collect(tb, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -723,13 +723,13 @@ struct RequantOp {
     n_elems += valid;
   }
   using Stats = BlockStats<1, 2>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
+  __device__ __forceinline__ void flush(long long u) {
     BlockStats<1, 2, uint32_t> s;
     s.mx[0] = f2u(fmaxf(vmax, fp8_to_f32<FMT>(src_final<kSrcBF16>(cmax))));
     s.ct[0] = n_elems - nz_top;
     s.ct[1] = nz_in - nz_code;                 // non-zero codes in, zero codes out (a NaN code is non-zero on both sides)
     s.orv = nonfinite;
-    collect<FINISH>(tb, *this, t, u, s);
+    collect(tb, u, s);
   }
   __device__ void finalize(int t, const TensorDesc&, const Stats& s) {
     const float vm = u2f(s.mx[0]);
@@ -880,14 +880,14 @@ struct SumOp {
     n_elems += valid;
   }
   using Stats = BlockStats<2, 2>;
-  template <bool FINISH> __device__ __forceinline__ void flush(int t, long long u) {
+  __device__ __forceinline__ void flush(long long u) {
     BlockStats<2, 2, uint32_t> s;
     s.mx[0] = f2u(vmax);
     s.mx[1] = amax_bits;
     s.ct[0] = n_top + (n_fast - nz_top);              // codes on the top magnitude
     s.ct[1] = n_und + ((n_fast - nz_code) - z_acc);   // zero codes that did not come from zero sums
     s.orv = 0;
-    collect<FINISH>(tb, *this, t, u, s);
+    collect(tb, u, s);
   }
   __device__ void finalize(int t, const TensorDesc& d, const Stats& s) {
     const float vm = u2f(s.mx[0]);

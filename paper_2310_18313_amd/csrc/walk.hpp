@@ -167,9 +167,9 @@ constexpr int kTotalWords = 16;       // 4 words of maxima and mask, up to 8 cou
 //
 //  * deferred: a second, tiny launch combines the records and runs the tensors' scalar epilogues: one workgroup per
 //    tensor, or one per 512 chunks of a large one, of which the last to arrive adds up what the others left.
-//  * single pass: every workgroup bumps a per-tensor ticket, the one that completes it reads the records of the tensor.  A
-//    ticket costs every workgroup about 20 ns that do not overlap with those of other workgroups (12 ns for an
-//    atomic on an address all workgroups share, 8 ns for the release that makes the record visible).
+//  * single pass: every workgroup bumps a per-tensor ticket when it leaves the tensor, the one that completes it reads the
+//    records of the tensor.  A ticket costs about 50 ns that do not overlap with those of other workgroups, most of it
+//    the agent-scope release in front of it, which makes the record visible outside the workgroup's L2.
 //
 // Measured and not used: adding to per-tensor slots with fire-and-forget atomics instead of leaving records.  At device
 // scope they are served outside the L2s at about 15 ns each whichever line they go to: the update pass of 1.8e9
@@ -273,8 +273,12 @@ __device__ __forceinline__ bool ticket_last(const Tables& tb, int t, uint32_t ad
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");        // the stores of all lanes of this wavefront
     if (threadIdx.x == 0) {
       uint32_t* ticket = &tb.scratch[t].ticket;
-      const bool last = __hip_atomic_fetch_add(ticket, add, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + add == want;
-      if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+      // (relaxed: the fences on both sides order it, and a release of its own would write the L2 back a second time)
+      const bool last = __hip_atomic_fetch_add(ticket, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add == want;
+      if (last) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
+      }
       l_last = last;
     }
   }
@@ -289,19 +293,22 @@ __device__ __forceinline__ uint32_t units_of(const Tables& tb, const TensorDesc&
   return (uint32_t)((d.numel + tb.unit_elems - 1) / tb.unit_elems);
 }
 
-// Called by all threads at the end of unit u, a part of tensor t.  In the single-pass form the workgroup that completes
-// the tensor runs its scalar epilogue.
-template <bool FINISH, int NV, int NC, class Op>
-__device__ __forceinline__ void collect(const Tables& tb, Op& op, int t, long long u, const BlockStats<NV, NC, uint32_t>& s) {
+// Called by all threads at the end of unit u: its record.
+template <int NV, int NC>
+__device__ __forceinline__ void collect(const Tables& tb, long long u, const BlockStats<NV, NC, uint32_t>& s) {
   const uint4 r = block_combine(s);
   constexpr int kStored = NC == 0 ? 1 : (NC <= 4 ? 2 : 3);
   if (threadIdx.x < kStored) reinterpret_cast<uint4*>(tb.records + u * kRecordBytes<NC>)[threadIdx.x] = r;
-  if (!FINISH || tb.deferred) return;          // FINISH = false: walk_marked bumps the ticket once for all its units
+}
+// The single-pass form, called by all threads when the workgroup has collected the last of `done` units of tensor t in a
+// row: one ticket for all of them.  The workgroup that completes the tensor runs its scalar epilogue.
+template <class Op>
+__device__ __forceinline__ void finish_by_ticket(const Tables& tb, Op& op, int t, uint32_t done) {
   const TensorDesc d = tb.desc[t];
   const uint32_t n = units_of(tb, d);
-  if (!ticket_last(tb, t, 1u, n)) return;
+  if (!ticket_last(tb, t, done, n)) return;
   const long long u0 = (long long)d.first_chunk << tb.unit_shift;
-  BlockStats<NV, NC> total;
+  typename Op::Stats total;
   gather_records(tb, u0, u0 + n, total);
   if (threadIdx.x == 0) op.finalize(t, d, total);
 }
@@ -349,7 +356,7 @@ __global__ __launch_bounds__(kThreads) void epilogue_kernel(Tables tb, Params p)
 // flat buffers; does not depend on the tensor) and tiles(r, pos) (the rest, the whole workgroup together; the op chooses
 // which 16 elements of a tile a thread takes); full_group(pos): the 16 consecutive elements starting at `pos`, handled by
 // the calling thread alone with vector accesses (any subset of the threads may call it); group(pos, valid) with
-// 1 <= valid <= 16 for everything else, element by element; flush(t, unit) (called by all threads at the end of a
+// 1 <= valid <= 16 for everything else, element by element; flush(unit) (called by all threads at the end of a
 // unit: it fills a BlockStats and hands it to `collect`); and for the tensor's scalar epilogue
 // finalize(t, desc, stats), run by one thread once the totals of all workgroups are known.
 //
@@ -360,13 +367,14 @@ __global__ __launch_bounds__(kThreads) void epilogue_kernel(Tables tb, Params p)
 // XOR-only traffic of 1.8e9 elements in one HBM region, TB/s, persistent / one tile per workgroup: update shape 5.13 / 5.5
 // (5.9 with two or three workgroups per compute unit), cast shape 5.37 / 6.45, one-to-one copy 5.23 / 6.54, reads alone
 // 6.95 / 6.95.  Two tiles per workgroup cost 5 % of the cast shape, four consecutive ones 2 to 8 % of the update shape.
-template <int UN, bool FINISH = true, class Op>
-__device__ __forceinline__ void walk_unit(const Tables& tb, Op& op, long long u) {
+// Unit u.  Returns its tensor and adds 1 to `done`, unless the unit is empty.
+template <int UN, class Op>
+__device__ __forceinline__ int walk_unit(const Tables& tb, Op& op, long long u, uint32_t& done) {
   const ChunkDesc c = uniform_load(tb.chunks + (u >> tb.unit_shift));
   const int e0 = ((int)u & ((1 << tb.unit_shift) - 1)) * tb.unit_elems;
   const int len = min(c.len - e0, tb.unit_elems);
-  if (len <= 0) return;                        // the last chunk of a tensor can have fewer units
   const int t = c.tensor;
+  if (len <= 0) return t;                      // the last chunk of a tensor can have fewer units
   const long long base = c.base + e0;
   const int ntiles = len / kTile;
   // the loads of the first tiles go out before anything about the tensor but its address is known
@@ -398,7 +406,9 @@ __device__ __forceinline__ void walk_unit(const Tables& tb, Op& op, long long u)
   // elements waits for every load in turn (the update of 600 ragged tensors: 38 us, 14 us this way)
   const int last = whole + kThreads - 1 - (int)threadIdx.x;
   if (last < len) op.group(base + last, 1);
-  op.template flush<FINISH>(t, u);
+  op.flush(u);
+  ++done;
+  return t;
 }
 
 template <int UN, class Op>
@@ -409,7 +419,14 @@ __device__ __forceinline__ void walk_units(const Tables& tb, Op& op) {
     u = b * U / G;
     end = (b + 1) * U / G;
   }
-  for (; u < end; ++u) walk_unit<UN>(tb, op, u);
+  uint32_t done = 0;
+  for (; u < end; ++u) {
+    const int t = walk_unit<UN>(tb, op, u, done);
+    if (tb.deferred || done == 0) continue;
+    if (u + 1 < end && uniform_load(tb.chunks + ((u + 1) >> tb.unit_shift)).tensor == t) continue;
+    finish_by_ticket(tb, op, t, done);
+    done = 0;
+  }
 }
 
 // ---- the second round of a speculation ------------------------------------------------------------------
@@ -480,13 +497,10 @@ __device__ __forceinline__ void walk_marked(const Tables& tb, Op& op) {
       const TensorDesc d = uniform_load(tb.desc + t);
       const long long units = units_of(tb, d), u0 = (long long)d.first_chunk << tb.unit_shift;
       const long long k0 = max(lo - first, 0ll), k1 = min(hi - first, units);
-      for (long long k = k0; k < k1; ++k) walk_unit<UN, false>(tb, op, u0 + k);
+      uint32_t done = 0;
+      for (long long k = k0; k < k1; ++k) walk_unit<UN>(tb, op, u0 + k, done);
       if constexpr (Op::kFinishes) {
-        if (!tb.deferred && ticket_last(tb, t, (uint32_t)(k1 - k0), (uint32_t)units)) {
-          typename Op::Stats s;
-          gather_records(tb, u0, u0 + units, s);
-          if (threadIdx.x == 0) op.finalize(t, d, s);
-        }
+        if (!tb.deferred) finish_by_ticket(tb, op, t, done);
       }
     }
   }

@@ -108,3 +108,35 @@ def test_a_limit_on_workgroups_holds_for_every_launch(lib, sizes, limit):
             assert 1 <= grid <= limit * CUS, (shape, name, grid)
     assert seen >= WALKS
     lib.L.fp8lm_destroy(h)
+
+
+@pytest.mark.parametrize("sizes", LISTS)
+def test_a_caller_chooses_how_statistics_are_combined(lib, sizes):
+    """single_pass_min_chunks = 0: never a second launch, not in the second round of a speculation either, and no more
+    tickets than a persistent grid has workgroups.  More than a workgroup ever has: always a second launch.  In between: the
+    chunks per workgroup of the grid that is launched decide."""
+    chunks = sum((n + 16383) // 16384 for n in LISTS[sizes])
+    for per_cu in (16, 7, 1):
+        for least in (0, 2, 5, FREE - 1):
+            h = lib.context(LISTS[sizes], (16384, per_cu, least))
+            for what, call in lib.calls(h).items():
+                if "error stats" in what:                          # sums in a fixed order: always a second launch
+                    continue
+                notes = lib.notes(call)
+                combining = [n for n in notes if n[0] in WALKS and n[0] != "adam_moment_redo"]    # that one finds nothing out
+                for name, grid, tables in combining:
+                    if name != "cast_marked":                      # decides as the cast before it
+                        deferred = least > 0 and chunks // grid < least
+                    assert tables["deferred"] == deferred, (what, name, grid, tables)
+                    assert least > 0 or grid <= 16 * CUS, (what, name, grid)
+                assert [n[0] for n in notes].count("epilogue") == sum(t["deferred"] for _, _, t in combining), (what, notes)
+            lib.L.fp8lm_destroy(h)
+
+
+def test_the_library_takes_tickets_for_the_smallest_launches_only(lib):
+    for numel, tickets in ((64 * 4096, True), (64 * 4096 + 1, False), (1 << 28, False)):
+        h = lib.context([numel])
+        (name, grid, tables), *rest = lib.notes(lib.calls(h)["requantize"])
+        assert name == "requantize" and grid == tables["n_chunks"] << tables["unit_shift"]
+        assert tables["one_unit"] and bool(tables["deferred"]) is not tickets and len(rest) == (0 if tickets else 1)
+        lib.L.fp8lm_destroy(h)
