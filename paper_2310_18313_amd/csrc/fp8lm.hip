@@ -271,9 +271,10 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   }
   return tb;
 }
-// The tables and the grid of the second round of a speculation (walk_marked); `un` and `record` as for the first.
-Tables marked_tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
-  Tables tb = tables_of(c, un, record, grid);
+// The tables and the grid of the second round of a speculation (walk_marked), from the tables of the first: the marks are
+// counts of its units.
+Tables marked_tables_of(const fp8lm_ctx* c, const Tables& first, int* grid) {
+  Tables tb = first;
   const long long units = (long long)c->n_chunks << tb.unit_shift;
   if (c->single_pass_min_chunks == kLibraryChooses) tb.deferred = units > 256;
   // with nothing marked the workgroups only cost their start; two thirds of 1.8e9 elements marked (heavy tails) took 1089 us
@@ -316,36 +317,28 @@ fp8lm_status after_launch() {
 // Launches a kernel that walks the units and, in the deferred form, the launch that finishes its tensors.
 template <class Stats> struct RecordOf;
 template <int NV, int NC> struct RecordOf<BlockStats<NV, NC>> { static constexpr int bytes = kRecordBytes<NC>; };
-template <class Op, class Params, class Kernel>
+template <class Op, bool MARKED = false, class Params, class Kernel>
 void launch_walk_on(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, const Tables& tb, int grid) {
   const dim3 b(kThreads);
   hipLaunchKernelGGL(kernel, dim3(grid), b, 0, s, tb, p);
-  if (tb.deferred) hipLaunchKernelGGL((epilogue_kernel<Op, Params>), dim3(std::min<int>(c->n_epi, 8 * c->num_cus)), b, 0, s, tb, p);
+  if (tb.deferred) hipLaunchKernelGGL((epilogue_kernel<Op, Params, MARKED>), dim3(std::min<int>(c->n_epi, 8 * c->num_cus)), b, 0, s, tb, p);
 }
-// The same for the second round of a speculation.
+// ... on the usual tables, which it returns.
 template <class Op, class Params, class Kernel>
-void launch_marked(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, const Tables& tb, int grid) {
-  const dim3 b(kThreads);
-  hipLaunchKernelGGL(kernel, dim3(grid), b, 0, s, tb, p);
-  if (tb.deferred) hipLaunchKernelGGL((epilogue_kernel<Op, Params, true>), dim3(std::min<int>(c->n_epi, 8 * c->num_cus)), b, 0, s, tb, p);
-}
-template <class Op, class Params, class Kernel>
-void launch_walk(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, int un = 1) {
+Tables launch_walk(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, int un = 1) {
   int grid = 0;
   const Tables tb = tables_of(c, un, RecordOf<typename Op::Stats>::bytes, &grid);
   launch_walk_on<Op>(c, s, kernel, p, tb, grid);
+  return tb;
 }
 
 // Selects the adam_update_kernel instantiation.
 template <int GFMT, int WCOPY>
-void launch_update(fp8lm_ctx* c, hipStream_t s, const AdamParams& p, bool fast, bool stats) {
-  if (fast) {
-    if (stats) launch_walk<AdamUpdateOp<GFMT, WCOPY, true, true>>(c, s, adam_update_kernel<GFMT, WCOPY, true, true>, p);
-    else launch_walk<AdamUpdateOp<GFMT, WCOPY, true, false>>(c, s, adam_update_kernel<GFMT, WCOPY, true, false>, p);
-  } else {
-    if (stats) launch_walk<AdamUpdateOp<GFMT, WCOPY, false, true>>(c, s, adam_update_kernel<GFMT, WCOPY, false, true>, p);
-    else launch_walk<AdamUpdateOp<GFMT, WCOPY, false, false>>(c, s, adam_update_kernel<GFMT, WCOPY, false, false>, p);
-  }
+Tables launch_update(fp8lm_ctx* c, hipStream_t s, const AdamParams& p, bool fast, bool stats) {
+#define FP8LM_UPDATE(F, S) launch_walk<AdamUpdateOp<GFMT, WCOPY, F, S>>(c, s, adam_update_kernel<GFMT, WCOPY, F, S>, p, kUnUpdate)
+  if (fast) return stats ? FP8LM_UPDATE(true, true) : FP8LM_UPDATE(true, false);
+  return stats ? FP8LM_UPDATE(false, true) : FP8LM_UPDATE(false, false);
+#undef FP8LM_UPDATE
 }
 
 // Selects the adam_update_var_kernel instantiation (every master / second-moment format pair except the default).
@@ -552,14 +545,15 @@ static fp8lm_status cast_impl(fp8lm_ctx* c, const void* src, fp8lm_src src_type,
   p.m_meta = m_meta;
   p.b1 = beta1;
   p.omb1 = (float)(1.0 - (double)beta1);
+  Tables tb;
   {
     Timed tm(c, s, FP8LM_K_CAST);
 #define FP8LM_CAST_LAUNCH(F, S)                                                                           \
     do {                                                                                                    \
-      if (delayed && fuse) launch_walk<CastOp<F, true, true, S>>(c, s, cast_kernel<F, true, true, S>, p, kUnCast<S>);          \
-      else if (delayed) launch_walk<CastOp<F, true, false, S>>(c, s, cast_kernel<F, true, false, S>, p, kUnCast<S>);            \
-      else if (fuse) launch_walk<CastOp<F, false, true, S>>(c, s, cast_kernel<F, false, true, S>, p, kUnCast<S>);               \
-      else launch_walk<CastOp<F, false, false, S>>(c, s, cast_kernel<F, false, false, S>, p, kUnCast<S>);                        \
+      if (delayed && fuse) tb = launch_walk<CastOp<F, true, true, S>>(c, s, cast_kernel<F, true, true, S>, p, kUnCast<S>);     \
+      else if (delayed) tb = launch_walk<CastOp<F, true, false, S>>(c, s, cast_kernel<F, true, false, S>, p, kUnCast<S>);       \
+      else if (fuse) tb = launch_walk<CastOp<F, false, true, S>>(c, s, cast_kernel<F, false, true, S>, p, kUnCast<S>);          \
+      else tb = launch_walk<CastOp<F, false, false, S>>(c, s, cast_kernel<F, false, false, S>, p, kUnCast<S>);                   \
     } while (0)
 #define FP8LM_CAST_SRC(S)                                                                                   \
     do {                                                                                                    \
@@ -577,13 +571,13 @@ static fp8lm_status cast_impl(fp8lm_ctx* c, const void* src, fp8lm_src src_type,
     // the tensors whose scale turned out different, with the plain cast
     {
       int grid = 0;
-      const Tables rt = marked_tables_of(c, src_type == FP8LM_SRC_F32 ? kUnCast<kSrcF32> : kUnCast<kSrcBF16>, 32, &grid);
+      const Tables rt = marked_tables_of(c, tb, &grid);
       p.speculative = 0;
       Timed tm(c, s, FP8LM_K_CAST);
 #define FP8LM_REDO_LAUNCH(F, S)                                                                            \
       do {                                                                                                  \
-        if (fuse) launch_marked<CastOp<F, false, true, S>>(c, s, cast_marked_kernel<F, true, S>, p, rt, grid);    \
-        else launch_marked<CastOp<F, false, false, S>>(c, s, cast_marked_kernel<F, false, S>, p, rt, grid);       \
+        if (fuse) launch_walk_on<CastOp<F, false, true, S>, true>(c, s, cast_marked_kernel<F, true, S>, p, rt, grid);    \
+        else launch_walk_on<CastOp<F, false, false, S>, true>(c, s, cast_marked_kernel<F, false, S>, p, rt, grid);       \
       } while (0)
 #define FP8LM_REDO_SRC(S)                                                                                  \
       do {                                                                                                  \
@@ -877,22 +871,23 @@ static fp8lm_status adam_launch(fp8lm_ctx* c, const uint8_t* grad, fp8lm_fmt gra
   }
   fp8lm_status st = after_launch();
   if (st != FP8LM_OK) return st;
+  Tables first{};
   if (variant) {
     Timed tm(c, s, FP8LM_K_ADAM_UPDATE);
     launch_update_variant(c, s, p, e5, hp->master_fmt, hp->v_fmt);
   } else {
     Timed tm(c, s, FP8LM_K_ADAM_UPDATE);
-    if (e5 && q8) launch_update<kE5M2, FP8LM_WCOPY_E4M3>(c, s, p, fast, stats);
-    else if (e5) launch_update<kE5M2, FP8LM_WCOPY_BF16>(c, s, p, fast, stats);
-    else if (q8) launch_update<kE4M3, FP8LM_WCOPY_E4M3>(c, s, p, fast, stats);
-    else launch_update<kE4M3, FP8LM_WCOPY_BF16>(c, s, p, fast, stats);
+    if (e5 && q8) first = launch_update<kE5M2, FP8LM_WCOPY_E4M3>(c, s, p, fast, stats);
+    else if (e5) first = launch_update<kE5M2, FP8LM_WCOPY_BF16>(c, s, p, fast, stats);
+    else if (q8) first = launch_update<kE4M3, FP8LM_WCOPY_E4M3>(c, s, p, fast, stats);
+    else first = launch_update<kE4M3, FP8LM_WCOPY_BF16>(c, s, p, fast, stats);
   }
   st = after_launch();
   if (st != FP8LM_OK || !spec_m) return st;
   // tensors whose first-moment scale turned out different: the moment once more
   {
     int grid = 0;
-    const Tables rt = marked_tables_of(c, kUnUpdate, 16, &grid);
+    const Tables rt = marked_tables_of(c, first, &grid);
     const dim3 g(grid), b(kThreads);
     Timed tm(c, s, FP8LM_K_ADAM_AMAX);
     if (e5) hipLaunchKernelGGL((adam_moment_redo_kernel<kE5M2>), g, b, 0, s, rt, p);

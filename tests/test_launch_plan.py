@@ -140,3 +140,17 @@ def test_the_library_takes_tickets_for_the_smallest_launches_only(lib):
         assert name == "requantize" and grid == tables["n_chunks"] << tables["unit_shift"]
         assert tables["one_unit"] and bool(tables["deferred"]) is not tickets and len(rest) == (0 if tickets else 1)
         lib.L.fp8lm_destroy(h)
+
+
+@pytest.mark.parametrize("sizes", LISTS)
+def test_both_rounds_of_a_speculation_cut_the_tensors_alike(lib, sizes):
+    """The first round marks a tensor with the number of its units, the second deals these units out."""
+    for tuning in (None, (4096, 16, FREE), (12288, 16, 0), (1 << 20, 5, FREE)):
+        h = lib.context(LISTS[sizes], tuning)
+        for what, call in lib.calls(h).items():
+            if what.split()[0] not in ("quantize",) and what != "adam pair":
+                continue
+            walks = [t for name, _, t in lib.notes(call) if name in WALKS]
+            assert len(walks) == 2, what
+            assert [(t["unit_elems"], t["unit_shift"]) for t in walks[1:]] == [(walks[0]["unit_elems"], walks[0]["unit_shift"])], (what, walks)
+        lib.L.fp8lm_destroy(h)
