@@ -106,6 +106,7 @@ struct fp8lm_ctx {
   // tensors done again, elements done again) for the gradient and for the first moment
   uint32_t spec_call = 0;
   uint32_t* d_marked_call = nullptr;
+  uint32_t* d_redo = nullptr;           // [n_tensors, whole quads] marks
   int spec_kind = 0;                    // what the call speculates about: 0 gradient scales, 1 first-moment scales
   unsigned long long* d_spec_totals = nullptr;
   // what the last fused cast measured for (checked by the Adam step that wants to use it)
@@ -239,6 +240,7 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   tb.n_tensors = c->n_tensors;
   tb.call = c->spec_call;
   tb.marked_call = c->d_marked_call;
+  tb.redo = c->d_redo;
   tb.spec_totals = c->d_spec_totals ? c->d_spec_totals + 3 * c->spec_kind : nullptr;
   tb.n_epi = c->n_epi;
   tb.n_chunks = c->n_chunks;
@@ -435,6 +437,9 @@ fp8lm_status fp8lm_create(fp8lm_ctx** out, const fp8lm_tensor* tensors, int32_t 
     if (e == hipSuccess) e = hipMemset(c->d_partials, 0, records * sizeof(Partial));
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_marked_call, sizeof(uint32_t));
     if (e == hipSuccess) e = hipMemset(c->d_marked_call, 0, sizeof(uint32_t));
+    const size_t marks = ((size_t)n + 3) / 4 * 16 + 16;
+    if (e == hipSuccess) e = hipMalloc((void**)&c->d_redo, marks);
+    if (e == hipSuccess) e = hipMemset(c->d_redo, 0, marks);
     if (e == hipSuccess) e = hipMalloc((void**)&c->d_spec_totals, 6 * sizeof(unsigned long long));     // gradient, first moment
     if (e == hipSuccess) e = hipMemset(c->d_spec_totals, 0, 6 * sizeof(unsigned long long));
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -452,6 +457,7 @@ fp8lm_status fp8lm_destroy(fp8lm_ctx* c) {
   if (c->d_scratch) (void)hipFree(c->d_scratch);
   if (c->d_partials) (void)hipFree(c->d_partials);
   if (c->d_marked_call) (void)hipFree(c->d_marked_call);
+  if (c->d_redo) (void)hipFree(c->d_redo);
   if (c->d_spec_totals) (void)hipFree(c->d_spec_totals);
   for (auto& s : c->stamps) { (void)hipEventDestroy(s.a); (void)hipEventDestroy(s.b); }
   for (auto& e : c->free_events) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }

@@ -44,7 +44,7 @@ __host__ __device__ inline int epilogue_groups(int32_t n_chunks) {
 // by the first Adam pass to the second, and what else that needs to know of a tensor.
 struct alignas(128) Scratch {
   uint32_t ticket;                // units finished, or epilogue workgroups
-  uint32_t redo;                  // a speculation that failed: the tensor's units, which have to be done again; otherwise 0
+  uint32_t pad;
   float old_scale, old_inv;       // the scale the first moment's meta held before its speculation
   struct Pending {
     float sm, ism, sv, isv, sw, isw, sq, isq;
@@ -78,10 +78,12 @@ struct Tables {
   int32_t one_unit;               // 1: the grid has one workgroup per unit; 0: a workgroup walks a contiguous range of units
   int32_t deferred;               // 1: workgroups only leave their records; an epilogue launch finishes the tensors
   int32_t n_tensors;
-  // speculation: the number of this call, where the last call that marked a tensor leaves its number, running totals (calls,
-  // tensors done again, elements done again)
+  // speculation: the number of this call, where the last call that marked a tensor leaves its number, the marks (a tensor's
+  // units, which have to be done again, or 0; padded with zeros to whole quads), running totals (calls, tensors done
+  // again, elements done again)
   uint32_t call;
   uint32_t* marked_call;
+  uint32_t* redo;
   unsigned long long* spec_totals;
 };
 
@@ -322,7 +324,7 @@ __global__ __launch_bounds__(kThreads) void epilogue_kernel(Tables tb, Params p)
     const EpilogueDesc e = tb.epi[i];
     const TensorDesc& d = e.d;
     const int t = e.tensor, K = epilogue_groups(d.n_chunks);
-    if (MARKED && tb.scratch[t].redo == 0) continue;
+    if (MARKED && uniform_load(tb.redo + t) == 0) continue;
     const long long n = units_of(tb, d), u0 = (long long)d.first_chunk << tb.unit_shift;
     typename Op::Stats s;
     gather_records(tb, u0 + n * e.k / K, u0 + n * (e.k + 1) / K, s);
@@ -434,15 +436,17 @@ __device__ __forceinline__ void walk_units(const Tables& tb, Op& op) {
 // units once more.  Mostly nothing is marked: then a workgroup reads
 // one word and ends.  Otherwise every workgroup adds up the marked units of all tensors and takes a contiguous share
 // of them, so that one marked tensor keeps the whole chip busy as well as many do.  (Two small kernels that built a list
-// before it cost 10 us per call whether or not there was anything to do.)  The tensors are finished by tickets or by a launch of
+// before it cost 10 us per call whether or not there was anything to do.)  The marks lie side by side, a thread adds up those
+// of a segment of neighbouring tensors, and only the segments of the workgroup's share are looked at one by one; the running
+// totals are kept by the first workgroup.  (One word per 128 bytes, 256 tensors at a time, and two device-scope atomics per
+// marked tensor for the totals: 459 us for 20 000 tensors of which a third is marked, 198 us this way.)  The tensors
+// are finished by tickets or by a launch of
 // their own, as after any other pass: tickets of 1024 workgroups are 60 us, so they are for the smallest launches.
 __device__ __forceinline__ void mark_redo(const Tables& tb, int t, const TensorDesc& d, bool redo) {
-  tb.scratch[t].redo = redo ? units_of(tb, d) : 0u;
-  if (!redo) return;
-  __hip_atomic_store(tb.marked_call, tb.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  (void)__hip_atomic_fetch_add(&tb.spec_totals[1], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  (void)__hip_atomic_fetch_add(&tb.spec_totals[2], (unsigned long long)d.numel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  tb.redo[t] = redo ? units_of(tb, d) : 0u;
+  if (redo) __hip_atomic_store(tb.marked_call, tb.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);    // the next kernel reads it
 }
+struct alignas(16) Quad4 { uint32_t n[4]; };
 template <int UN, class Op>
 __device__ __forceinline__ void walk_marked(const Tables& tb, Op& op) {
   if (blockIdx.x == 0 && threadIdx.x == 0) tb.spec_totals[0] += 1;
@@ -450,57 +454,81 @@ __device__ __forceinline__ void walk_marked(const Tables& tb, Op& op) {
   __shared__ uint32_t l_sum[kWaves], l_count[kWaves];
   __shared__ struct { uint32_t at; int32_t t; } l_share[kThreads];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  uint32_t mine = 0;                             // (all units of a launch fit 32 bits)
-  for (int t = threadIdx.x; t < tb.n_tensors; t += kThreads) mine += tb.scratch[t].redo;
-  mine = wave_sum_u32(mine);
-  if (lane == 63) l_sum[wave] = mine;
-  __syncthreads();
-  const long long total = (long long)l_sum[0] + l_sum[1] + l_sum[2] + l_sum[3];
-  const long long lo = total * blockIdx.x / gridDim.x, hi = total * (blockIdx.x + 1) / gridDim.x;
-  if (lo == hi) return;
-  long long base = 0;                            // marked units of the tensors before this block of them
-  for (int t0 = 0; t0 < tb.n_tensors && base < hi; t0 += kThreads) {
-    // a thread per tensor: where its marked units lie among all, and whether this workgroup's share reaches into them
-    const int ti = t0 + threadIdx.x;
-    const uint32_t n = ti < tb.n_tensors ? tb.scratch[ti].redo : 0u;
-    uint32_t upto = n;
+  // a thread per segment of `per` tensors: its marked units
+  const int per = 4 * ((tb.n_tensors + 4 * kThreads - 1) / (4 * kThreads)), t0 = per * (int)threadIdx.x;
+  const int n4 = (tb.n_tensors + 3) & ~3;
+  uint32_t n = 0;                                // (all units of a launch fit 32 bits)
+  for (int t = t0; t < min(t0 + per, n4); t += 4) {
+    const Quad4 q = *reinterpret_cast<const Quad4*>(tb.redo + t);
+    n += (q.n[0] + q.n[1]) + (q.n[2] + q.n[3]);
+  }
+  if (blockIdx.x == 0) {
+    unsigned long long tensors = 0, elems = 0;
+    for (int t = t0; t < min(t0 + per, tb.n_tensors); ++t) {
+      if (tb.redo[t] == 0) continue;
+      tensors += 1;
+      elems += (unsigned long long)tb.desc[t].numel;
+    }
+    tensors = wave_sum_u64(tensors);
+    elems = wave_sum_u64(elems);
+    if (lane == 0) {
+      (void)__hip_atomic_fetch_add(&tb.spec_totals[1], tensors, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      (void)__hip_atomic_fetch_add(&tb.spec_totals[2], elems, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+  }
+  // where the segments' units lie among all
+  uint32_t upto = n;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t x = (uint32_t)__shfl_up((int)upto, o, 64);
-      if (lane >= o) upto += x;
-    }
-    __syncthreads();                             // the previous use of the LDS arrays is over
-    if (lane == 63) l_sum[wave] = upto;
-    __syncthreads();
-    long long at = base + upto - n;
-    for (int w = 0; w < kWaves; ++w) {
-      if (w < wave) at += l_sum[w];
-      base += l_sum[w];
-    }
-    const bool share = n && at < hi && at + n > lo;
-    const unsigned long long ballot = __ballot(share);
-    if (lane == 0) l_count[wave] = (uint32_t)__popcll(ballot);
-    __syncthreads();
-    int count = 0, place = __popcll(ballot & ((1ull << lane) - 1));
-    for (int w = 0; w < kWaves; ++w) {
-      if (w < wave) place += (int)l_count[w];
-      count += (int)l_count[w];
-    }
-    if (share) {
-      l_share[place].at = (uint32_t)at;
-      l_share[place].t = ti;
-    }
-    __syncthreads();
-    for (int i = 0; i < count; ++i) {
-      const int t = __builtin_amdgcn_readfirstlane(l_share[i].t);
-      const long long first = (uint32_t)__builtin_amdgcn_readfirstlane((int)l_share[i].at);
-      const TensorDesc d = uniform_load(tb.desc + t);
-      const long long units = units_of(tb, d), u0 = (long long)d.first_chunk << tb.unit_shift;
-      const long long k0 = max(lo - first, 0ll), k1 = min(hi - first, units);
-      uint32_t done = 0;
-      for (long long k = k0; k < k1; ++k) walk_unit<UN>(tb, op, u0 + k, done);
-      if constexpr (Op::kFinishes) {
-        if (!tb.deferred) finish_by_ticket(tb, op, t, done);
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t x = (uint32_t)__shfl_up((int)upto, o, 64);
+    if (lane >= o) upto += x;
+  }
+  if (lane == 63) l_sum[wave] = upto;
+  __syncthreads();
+  uint32_t at = upto - n;
+  long long total = 0;
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wave) at += l_sum[w];
+    total += l_sum[w];
+  }
+  // the segments that this workgroup's share reaches into, in order
+  const long long lo = total * blockIdx.x / gridDim.x, hi = total * (blockIdx.x + 1) / gridDim.x;
+  const bool share = n && (long long)at < hi && (long long)at + n > lo;
+  const unsigned long long ballot = __ballot(share);
+  if (lane == 0) l_count[wave] = (uint32_t)__popcll(ballot);
+  __syncthreads();
+  int count = 0, place = __popcll(ballot & ((1ull << lane) - 1));
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wave) place += (int)l_count[w];
+    count += (int)l_count[w];
+  }
+  if (share) {
+    l_share[place].at = at;
+    l_share[place].t = t0;
+  }
+  __syncthreads();
+  for (int i = 0; i < count; ++i) {
+    const int s0 = __builtin_amdgcn_readfirstlane(l_share[i].t);
+    long long first = (uint32_t)__builtin_amdgcn_readfirstlane((int)l_share[i].at);
+    for (int s = s0; s < min(s0 + per, n4) && first < hi; s += 4) {
+      const Quad4 q = uniform_load(reinterpret_cast<const Quad4*>(tb.redo + s));
+      const long long quad = (long long)q.n[0] + q.n[1] + q.n[2] + q.n[3];
+      if (first + quad <= lo) {
+        first += quad;
+        continue;
+      }
+#pragma unroll 1
+      for (int t = s; t < s + 4; ++t) {
+        const long long units = uniform_load(tb.redo + t);
+        const long long k0 = max(lo - first, 0ll), k1 = min(hi - first, units);
+        first += units;
+        if (k0 >= k1) continue;
+        const long long u0 = (long long)uniform_load(&tb.desc[t].first_chunk) << tb.unit_shift;
+        uint32_t done = 0;
+        for (long long k = k0; k < k1; ++k) walk_unit<UN>(tb, op, u0 + k, done);
+        if constexpr (Op::kFinishes) {
+          if (!tb.deferred) finish_by_ticket(tb, op, t, done);
+        }
       }
     }
   }
