@@ -294,6 +294,7 @@ struct CastOp {
   const Tables& tb;
   float scale;
   bool careful;
+  bool measure;           // a speculation with nothing to go by: only the amax is wanted
   float inv_sg, inv_sm;   // FUSE
   float cm, cg;           // FUSE: beta1 / s_m and (1 - beta1) / s_g, if folding the scales changes no rounding
   bool fold;
@@ -314,6 +315,7 @@ struct CastOp {
       e = predicted_exponent<true>(p.meta + t, p.fmax_bits, p.hist_window, p.margin);
       if (e != kKeepScale) scale = pow2f(e);
     }
+    measure = DELAYED && p.speculative && e == kKeepScale;
     careful = !DELAYED && (uniform_load(&p.meta[t].flags) & FP8LM_FLAG_NONFINITE) != 0;
     if constexpr (FUSE) {
       inv_sg = e != kKeepScale ? pow2f(-e) : uniform_load(&p.meta[t].inv_scale);
@@ -442,6 +444,9 @@ struct CastOp {
       const uint32_t top = src_final<SRC>(gmax);
       if constexpr (DELAYED) {
         src_fold1<SRC>(amax16, top);
+        // Without a history (the first call) the speculation of a tensor cannot hold unless all of it is zero, so only zeros are
+        // written: 5 bytes per element in both rounds, as amax pass and cast have, instead of 6 (125e6 elements: 160 us, 137 this way).
+        if (measure && top != 0) continue;
         if (top >= SrcTraits<SRC>::kNonfinite) {
           // rare: this group holds inf/NaN; element by element, and again from memory: no registers for it
           if constexpr (kSplit) {
@@ -557,7 +562,7 @@ struct CastOp {
       M.amax = A;
       push_history(M, A, p.hist_window);
       M.flags = scale_from_history(M, p.fmax_bits, p.hist_window, p.margin);
-      held = M.scale == used;
+      held = M.scale == used && (e != kKeepScale || abits == 0);      // (without a history only zeros have been cast)
     }
     return held;
   }
