@@ -60,7 +60,9 @@ struct QuantStatsOp {
   // workgroup.  What bounds this is the vector unit: two conversions and three float64 fused multiply-adds per element
   // are what it cannot do without, so everything else is asked of the group as a whole first, by integer maxima and
   // minima of the reference's bits and tests of four codes at a time: mostly nothing is zero, on the top code or not finite.
-  // (Element by element, 25 instructions: 157 us for 125e6 elements with an fp32 reference.)
+  // Only a group with something that is not finite goes element by element.  1.3e8 elements, fp32 reference, E4M3: 136 us,
+  // 140 where every wavefront meets zeros (element by element: 25 instructions, 215 us; 340 where a group with a zero was left to
+  // a loop that picks its elements out of registers).
   static constexpr int kRuns = kLoads, kRun = kGroup / kRuns;
   struct Regs { uint4 r[kLoads]; uint32_t q[4]; };
   template <bool kSplit> __device__ __forceinline__ void load(Regs& g, long long pos0) const {
@@ -80,13 +82,23 @@ struct QuantStatsOp {
       }
     }
   }
+  // bit 7 of byte i: element 4 k + i of the reference is not zero
+  static __device__ __forceinline__ uint32_t nonzero_refs(const uint32_t (&w)[kW], int k) {
+    if constexpr (kSrc16<SRC>) {
+      const uint32_t lo = (w[2 * k] & 0x7FFF7FFFu) + 0x7FFF7FFFu, hi = (w[2 * k + 1] & 0x7FFF7FFFu) + 0x7FFF7FFFu;
+      return __builtin_amdgcn_perm(hi, lo, 0x07050301u) & 0x80808080u;
+    } else {
+      auto m = [&](int i) { return (w[4 * k + i] & 0x7FFFFFFFu) + 0x7FFFFFFFu; };
+      return (__builtin_amdgcn_perm(m(1), m(0), 0x0C0C0703u) | __builtin_amdgcn_perm(m(3), m(2), 0x07030C0Cu)) & 0x80808080u;
+    }
+  }
   __device__ __forceinline__ void accumulate(const Regs& g) {
     uint32_t w[kW];
 #pragma unroll
     for (int k = 0; k < kLoads; ++k) {
       w[4 * k] = g.r[k].x; w[4 * k + 1] = g.r[k].y; w[4 * k + 2] = g.r[k].z; w[4 * k + 3] = g.r[k].w;
     }
-    uint32_t gmax = 0, gmin = 0xFFFFFFFFu, all_nz = 0x80808080u, any = 0;
+    uint32_t gmax = 0, gmin = 0xFFFFFFFFu, all_nz = 0x80808080u, top = 0;
 #pragma unroll
     for (int j = 0; j < kW; ++j) {
       src_fold<SRC>(gmax, w[j]);
@@ -96,23 +108,37 @@ struct QuantStatsOp {
     for (int k = 0; k < 4; ++k) {
       const uint32_t mag = g.q[k] & 0x7F7F7F7Fu;
       all_nz &= mag + 0x7F7F7F7Fu;                                         // bit 7 of a byte: its magnitude is not zero
-      any |= mag + (0x80808080u - Fp8Traits<FMT>::kTopX4);                 // ... it is the top code or beyond it
+      top |= mag + (0x80808080u - Fp8Traits<FMT>::kTopX4);                 // ... it is the top code or beyond it
     }
-    if (src_final<SRC>(gmax) >= SrcTraits<SRC>::kNonfinite || src_final_min<SRC>(gmin) == 0 || all_nz != 0x80808080u || (any & 0x80808080u)) {
-#pragma unroll 1
-      for (int j = 0; j < 16; ++j) {
-        uint32_t bits = 0, code = 0;                                       // (no dynamic index into registers)
+    if (src_final<SRC>(gmax) >= SrcTraits<SRC>::kNonfinite || src_final_min<SRC>(gmin) == 0 || all_nz != 0x80808080u || (top & 0x80808080u)) {
+      uint32_t beyond = 0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          if (i != j) continue;
-          bits = kSrc16<SRC> ? (w[(i >> 1) % kW] >> ((i & 1) * 16)) & 0xFFFFu : w[i % kW];
-          code = (g.q[i >> 2] >> ((i & 3) * 8)) & 0xFFu;
+      for (int k = 0; k < 4; ++k) beyond |= (g.q[k] & 0x7F7F7F7Fu) + (0x7F7F7F7Fu - Fp8Traits<FMT>::kTopX4);
+      if (src_final<SRC>(gmax) >= SrcTraits<SRC>::kNonfinite || (beyond & 0x80808080u)) {
+#pragma unroll 1
+        for (int j = 0; j < 16; ++j) {
+          uint32_t bits = 0, code = 0;                                     // (no dynamic index into registers)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            if (i != j) continue;
+            bits = kSrc16<SRC> ? (w[(i >> 1) % kW] >> ((i & 1) * 16)) & 0xFFFFu : w[i % kW];
+            code = (g.q[i >> 2] >> ((i & 3) * 8)) & 0xFFu;
+          }
+          one(bits, code);
         }
-        one(bits, code);
+        return;
       }
-      return;
+      // zeros or top codes among them (a gradient with unused rows, one that underflows): counted four at a time
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint32_t mag = g.q[k] & 0x7F7F7F7Fu, nz_code = mag + 0x7F7F7F7Fu, nz = nonzero_refs(w, k);
+        n_nonzero += __popc(nz);
+        n_under += __popc(nz & ~nz_code);
+        n_over += 4 - nonzero_bytes7(mag ^ Fp8Traits<FMT>::kTopX4);
+      }
+    } else {
+      n_nonzero += kGroup;
     }
-    n_nonzero += kGroup;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float2_t lo = fp8x2_to_f32<FMT, false>(g.q[k]), hi = fp8x2_to_f32<FMT, true>(g.q[k]);
@@ -161,8 +187,10 @@ struct QuantStatsOp {
 // persistent grid, workgroup b walking the chunks [b*C/G, (b+1)*C/G), one record per (workgroup, tensor) pair.  The
 // workgroups that touch tensor t are consecutive and a workgroup touches consecutive tensors, so record b + t is unique
 // and the records of a tensor are contiguous.  (The kernel only reads: the order of the walk costs nothing here.)
+// Seven wavefronts per SIMD: with an fp32 reference the allocator would take 75 registers, three too many for that, for the
+// paths that are seldom taken (72 do without spilling).
 template <int FMT, int SRC>
-__global__ __launch_bounds__(kThreads) void quant_stats_kernel(Tables tb, StatsParams p) {
+__global__ __launch_bounds__(kThreads, 7) void quant_stats_kernel(Tables tb, StatsParams p) {
   QuantStatsOp<FMT, SRC> op(p, tb);
   const long long C = tb.n_chunks, b = blockIdx.x, G = gridDim.x;
   int cur = -1;
