@@ -281,7 +281,8 @@ def main() -> int:
                          "spec: the same results through fp8lm_quantize_fp8, which casts with the predicted scale while "
                          "measuring the amax and casts again only the tensors whose scale changed (17 B/param + redone "
                          "tensors); fused: same results, the cast also does the Adam step's first pass (18 B/param, one "
-                         "GPU only); spec-fused: both (16 B/param + redone tensors); spec-m2: spec, and the Adam step "
+                         "GPU only); spec-fused: both (16 B/param + redone tensors; what OptimizerState.step(speculative=True) "
+                         "does unless it is told to leave the moment to the Adam step); spec-m2: spec, and the Adam step "
                          "through fp8lm_adam_step_fp8_m2, which drops the read-only pass for a second first-moment buffer "
                          "(same results; 15 B/param + redone tensors; state 7 instead of 6 B/param); single: delayed "
                          "gradient scaling + predicted first-moment scale (15 B/param, results differ: looser scales)")

@@ -55,13 +55,17 @@ def run(wl, seed, steps, small_steps, big_steps, big_ids=None, track_mu=False, p
     grad.zero_()
     tot = dict(elements=0, m_diff=0, w_diff=0, q_diff=0, w_amax_ulp=0)
     mus = []
+    own_passes = 0
+    st.ctx.set_timing(True)
     for step in range(1, steps + 1):
         synth.fill_gradients(grad, wl, seed, step)
         mode, delayed = (paths or {}).get(step, (B.MSCALE_EXACT_PASS, False))
+        own_passes += mode == B.MSCALE_EXACT_PASS
         hp = B.adam_hparams(wl.lr, step, m_scale_mode=mode)
         ids = (small if step in small_steps else []) + (big if step in big_steps else [])
         snaps = [P.Snapshot(st, grad, t) for t in ids]
-        st.step(grad, hp, delayed=delayed, speculative=speculative and not delayed, pair_m=step in pair_steps)
+        st.step(grad, hp, delayed=delayed, speculative=speculative and not delayed, pair_m=step in pair_steps,
+                own_moment_pass=True)
         torch.cuda.synchronize()
         if ids:
             say(f"{wl.name} step {step} (moment-scale mode {mode}, delayed {delayed}): checking {len(ids)} tensors, "
@@ -72,6 +76,9 @@ def run(wl, seed, steps, small_steps, big_steps, big_ids=None, track_mu=False, p
         if track_mu:
             mus.append(B.meta_to_numpy(st.g_meta, lay.n_tensors)["mu_exp"].copy())
     say(f"{wl.name}: {tot}")
+    # the Adam step's own pass (with a pair of moment buffers: its second round) where the exact scale is its business
+    assert st.ctx.get_timing()["adam_amax"][0] == own_passes
+    st.ctx.set_timing(False)
     # exact arithmetic is the default: nothing may differ
     assert tot["m_diff"] == 0 and tot["w_diff"] == 0 and tot["q_diff"] == 0
     return st, tot, mus
@@ -95,8 +102,9 @@ def test_gpt13b_in_the_benchmark_configuration():
 def test_gpt7b_five_steps_with_amax_history():
     wl = synth.workload("gpt7b")
     assert wl.hist_window == 4
-    # steps 1-2 on the two-pass path, then the one-GPU fused cast, then the single-pass path (delayed gradient
-    # scale + predicted moment scale): the three paths bench.py times, at full size and default tuning
+    # step 1 on the two-pass path, step 2 with a pair of moment buffers, then the one-GPU fused cast, then the single-pass path
+    # (delayed gradient scale + predicted moment scale), then the fused cast with a delayed scale: the paths bench.py
+    # times, at full size and default tuning
     paths = {3: (B.MSCALE_FROM_CAST, False), 4: (B.MSCALE_PREDICTED, True), 5: (B.MSCALE_FROM_CAST, True)}
     # every small tensor at every step; the five large shapes at steps 2, 3 and 4, one per path.  Step 2
     # goes through fp8lm_adam_step_fp8_m2 (first moment read from one buffer of a pair, written to the other).
@@ -230,8 +238,8 @@ def test_one_tensor_with_more_than_two_to_the_31_elements():
         fill(40 + step, 1e-4, 1.0 if step == 1 else -0.75, 0.0)   # the largest gradient of every piece, same place
         hp = B.adam_hparams(3e-4, step, stats=1)
         snaps = [P.Snapshot(split, buf, t) for t in checked]
-        huge.step(buf, hp)
-        split.step(buf, hp)
+        huge.step(buf, hp, own_moment_pass=True)
+        split.step(buf, hp, own_moment_pass=step == 1)
         torch.cuda.synchronize()
         say(f"huge tensor step {step}: oracle on pieces {checked}")
         r = P.check_step(split, snaps, hp, what=f"pieces, step {step}")

@@ -162,6 +162,7 @@ def run_lockstep(wl, seed, steps, ids=None, grad_fmt=B.E5M2, wcopy=B.WCOPY_E4M3,
     del w0
     grad = torch.zeros(max(wl.layout.total, 16), dtype=torch.bfloat16, device=DEV)
     tot = dict(elements=0, m_diff=0, w_diff=0, q_diff=0, w_amax_ulp=0)
+    st.ctx.set_timing(True)
     for step in range(1, steps + 1):
         synth.fill_gradients(grad, wl, seed, step)
         hp = B.adam_hparams(lr or wl.lr, step, v_scaled=v_scaled, wcopy=wcopy, stats=stats, exact=exact)
@@ -169,13 +170,15 @@ def run_lockstep(wl, seed, steps, ids=None, grad_fmt=B.E5M2, wcopy=B.WCOPY_E4M3,
         snaps = [P.Snapshot(st, grad, t) for t in ids] if checked else []
         say(f"{wl.name} seed={seed} step={step} fmt={grad_fmt} wcopy={wcopy} v_scaled={v_scaled} stats={stats} exact={exact} checked={checked}"
             + ("" if exact else "  [exact=0: checked against the documented looser contract, outside the 1-ulp bar by design]"))
-        st.step(grad, hp)
+        st.step(grad, hp, own_moment_pass=True)
         torch.cuda.synchronize()
         if checked:
             r = P.check_step(st, snaps, hp, what=f"{wl.name} step {step}")
             for k in tot:
                 tot[k] = max(tot[k], r[k]) if k == "w_amax_ulp" else tot[k] + r[k]
     say(f"  -> {tot}")
+    assert st.ctx.get_timing()["adam_amax"][0] == steps          # the Adam step's own pass over gradient and moment
+    st.ctx.set_timing(False)
     return st, tot
 
 
@@ -217,7 +220,7 @@ def test_free_running_oracle_and_gpu_end_in_the_same_state(name, steps):
         synth.fill_gradients(grad, wl, 4, step)
         hp = B.adam_hparams(wl.lr, step)
         say(f"free-running {name} step {step}")
-        st.step(grad, hp)
+        st.step(grad, hp, own_moment_pass=step % 2 == 0)            # both places where the new moment is measured
         fr.step(synth.bits16(grad), hp)
     torch.cuda.synchronize()
     fr.assert_equal_to(st, f"{name} after {steps} free-running steps")
@@ -241,7 +244,7 @@ def test_three_hundred_free_running_steps_with_heavy_tails(mu_rule):
     for step in range(1, 301):
         synth.fill_gradients(grad, wl, 21, step)
         hp = B.adam_hparams(wl.lr, step)
-        st.step(grad, hp)
+        st.step(grad, hp, own_moment_pass=step % 2 == 0)
         fr.step(synth.bits16(grad), hp)
         if step in (50, 150, 300):
             say(f"long free-running run, mu rule {mu_rule}: comparing at step {step}")
@@ -279,7 +282,7 @@ def test_twenty_thousand_small_tensors(single_pass):
         g.manual_seed(1000 + step)
         grad = (torch.randn(lay.total, device=DEV, generator=g) * sig * (20.0 if step == 3 else 1.0)).to(torch.bfloat16)
         hp = B.adam_hparams(wl.lr, step)
-        st.step(grad, hp)
+        st.step(grad, hp, own_moment_pass=step != 2)
         fr.step(synth.bits16(grad), hp)
     torch.cuda.synchronize()
     say("comparing 20 000 tensors")
@@ -327,7 +330,7 @@ def test_nonfinite_zero_and_extreme_gradients():
         hp = B.adam_hparams(1e-3, step, stats=1, exact=1)
         snaps = [P.Snapshot(st, grad, t) for t in ids]
         say(f"special step {step}")
-        st.step(grad, hp)
+        st.step(grad, hp, own_moment_pass=True)
         torch.cuda.synchronize()
         P.check_step(st, snaps, hp, what=f"special step {step}")
     gm = B.meta_to_numpy(st.g_meta, lay.n_tensors)
@@ -433,7 +436,7 @@ def test_delayed_scaling_and_moment_scale_modes(grad_fmt, m_scale_mode):
             hp = B.adam_hparams(wl.lr, step, stats=1, m_scale_mode=m_scale_mode)
             snaps = [P.Snapshot(st, grad, t) for t in ids]
             say(f"{wl.name} fmt={grad_fmt} m_scale_mode={m_scale_mode} step={step} delayed={delayed}")
-            st.step(grad, hp, delayed=delayed)
+            st.step(grad, hp, delayed=delayed, own_moment_pass=True)
             torch.cuda.synchronize()
             r = P.check_step(st, snaps, hp, what=f"{wl.name} variants step {step}", delayed=delayed)
             assert r["m_diff"] == 0 and r["w_diff"] == 0 and r["q_diff"] == 0
@@ -692,7 +695,7 @@ def test_master_weight_and_second_moment_formats(master_fmt, v_fmt):
             hp = B.adam_hparams(wl.lr, step, master_fmt=master_fmt, v_fmt=v_fmt, m_scale_mode=mode)
             snaps = [P.Snapshot(st, grad, t) for t in ids]
             say(f"{wl.name} master_fmt={master_fmt} v_fmt={v_fmt} step={step} mode={mode}")
-            st.step(grad, hp)
+            st.step(grad, hp, own_moment_pass=True)
             torch.cuda.synchronize()
             P.check_step(st, snaps, hp, what=f"{wl.name} formats step {step}")
     with pytest.raises(B.Fp8lmError):                        # counters are not available for these formats
@@ -805,7 +808,7 @@ def test_whole_path_from_fp16_and_fp32_gradients(dtype, grad_fmt):
             hp = B.adam_hparams(wl.lr, step, m_scale_mode=mode)
             snaps = [P.Snapshot(st, grad, t) for t in ids]
             say(f"{wl.name} dtype={dtype} fmt={grad_fmt} step={step} delayed={delayed} mode={mode}")
-            st.step(grad, hp, delayed=delayed)
+            st.step(grad, hp, delayed=delayed, own_moment_pass=True)
             torch.cuda.synchronize()
             P.check_step(st, snaps, hp, what=f"{wl.name} {dtype} step {step}", delayed=delayed)
 
@@ -1007,13 +1010,13 @@ def test_weight_copy_written_over_the_fp8_gradient(grad_fmt, route):
         hp = B.adam_hparams(wl.lr, step, stats=step % 2, m_scale_mode=mode)
         snaps = [P.Snapshot(two, grad, t) for t in ids]
         say(f"weight copy over the gradient: fmt={grad_fmt} route={route} step={step}")
-        two.step(grad, hp, speculative=(route == "spec"))
+        two.step(grad, hp, speculative=(route == "spec"), own_moment_pass=True)
         if route == "static":
             one.quantize_grad(grad)
             B.adam_step_fp8_static(lay.tensors(), one.g8, grad_fmt, one.g_meta, one.m, one.m_meta, one.v, one.v_meta,
                                    one.w, one.w_meta, one.g8, one.q_meta, hp)
         else:
-            one.step(grad, hp, speculative=(route == "spec"))
+            one.step(grad, hp, speculative=(route == "spec"), own_moment_pass=step != 4)
         torch.cuda.synchronize()
         P.check_step(two, snaps, hp, what=f"two buffers, step {step}")
         for k in ("m", "v", "w", "wq", "g_meta", "m_meta", "v_meta", "w_meta", "q_meta"):
@@ -1061,7 +1064,7 @@ def test_region_aware_placement_changes_no_result():
         synth.fill_gradients(placed.grad, wl, 3, step)
         hp = B.adam_hparams(wl.lr, step)
         placed.step(placed.grad, hp, speculative=True)
-        plain.step(placed.grad, hp, speculative=True)
+        plain.step(placed.grad, hp, speculative=True, own_moment_pass=True)
         torch.cuda.synchronize()
         for k in ("g8", "m", "v", "w", "wq", "g_meta", "m_meta", "v_meta", "w_meta", "q_meta"):
             a, b = getattr(placed, k), getattr(plain, k)
@@ -1118,7 +1121,8 @@ def test_striped_arena_is_ordinary_memory_and_gives_it_back():
     assert torch.cuda.mem_get_info(0)[0] >= free0 - (64 << 20) - 2 * lay.total - (1 << 20)
 
 
-def test_a_step_replayed_from_a_hip_graph_equals_the_eager_step():
+@pytest.mark.parametrize("own_moment_pass", [True, False])
+def test_a_step_replayed_from_a_hip_graph_equals_the_eager_step(own_moment_pass):
     """None of the hot-path calls synchronises, allocates or clears memory with a memset, so a whole step can be
     captured once and replayed; the hyper-parameters are baked in at capture, so every replay is the same step."""
     wl = synth.Workload("mid", synth.gpt_layout(256, 2, 1024, 1000), lr=1e-3, sigma=None)
@@ -1131,7 +1135,7 @@ def test_a_step_replayed_from_a_hip_graph_equals_the_eager_step():
     hp = B.adam_hparams(wl.lr, 3)
     names = ("g8", "m", "v", "w", "wq", "g_meta", "m_meta", "v_meta", "w_meta", "q_meta")
     before = {k: getattr(st, k).clone() for k in names}
-    st.step(grad, hp)                                            # eager reference
+    st.step(grad, hp, own_moment_pass=own_moment_pass)           # eager reference
     torch.cuda.synchronize()
     want = {k: getattr(st, k).clone() for k in names}
 
@@ -1146,7 +1150,7 @@ def test_a_step_replayed_from_a_hip_graph_equals_the_eager_step():
     side.wait_stream(torch.cuda.current_stream())
     say("capturing one step into a HIP graph")
     with torch.cuda.graph(graph, stream=side):
-        st.step(grad, hp)
+        st.step(grad, hp, own_moment_pass=own_moment_pass)
     torch.cuda.synchronize()
     for rep in range(3):
         restore()                                                # eager work between the replays
@@ -1184,8 +1188,8 @@ def test_parameter_groups_share_the_flat_buffers():
         snaps_d = [P.Snapshot(st_d, grad, t) for t in range(len(decay))]
         snaps_p = [P.Snapshot(st_p, grad, t) for t in range(len(plain))]
         say(f"parameter groups step {step}: {len(decay)} + {len(plain)} tensors")
-        st_d.step(grad, hp_d)
-        st_p.step(grad, hp_p)
+        st_d.step(grad, hp_d, own_moment_pass=True)
+        st_p.step(grad, hp_p, own_moment_pass=True)
         torch.cuda.synchronize()
         P.check_step(st_d, snaps_d, hp_d, what=f"decay group step {step}")
         P.check_step(st_p, snaps_p, hp_p, what=f"no-decay group step {step}")
@@ -1217,7 +1221,7 @@ def test_weight_decay_exemption_by_tensor_flag(master_fmt, exact):
         snaps_d = [P.Snapshot(st, grad, t) for t in with_decay]
         snaps_e = [P.Snapshot(st, grad, t) for t in exempt] if step < 3 else []
         say(f"tensor flags (master {master_fmt}, exact {exact}) step {step}: {len(with_decay)} decaying, {len(snaps_e)} exempt")
-        st.step(grad, hp)
+        st.step(grad, hp, own_moment_pass=True)
         torch.cuda.synchronize()
         P.check_step(st, snaps_d, hp, what=f"decaying tensors step {step}")
         if snaps_e:
@@ -1251,7 +1255,7 @@ def test_two_contexts_on_two_streams_at_once():
         say(f"two streams step {step}")
         for x, s in zip(st, streams):
             with torch.cuda.stream(s):
-                x.step(grad, hp)
+                x.step(grad, hp, own_moment_pass=x is st[0] or step == 1)
         torch.cuda.synchronize()
         for k, x in enumerate(st):
             P.check_step(x, snaps[k], hp, what=f"stream {k} step {step}")
@@ -1286,9 +1290,9 @@ def test_shards_of_the_greedy_distribution_step_like_the_whole_model():
             grad.mul_(32.0)                       # a jump the amax history and mu have to follow
         hp = B.adam_hparams(wl.lr, step)
         say(f"greedy shards step {step}")
-        whole.step(grad, hp)
+        whole.step(grad, hp, own_moment_pass=True)
         for sh in shards:
-            sh.step(grad, hp)
+            sh.step(grad, hp, own_moment_pass=step % 2 == 1)
         fr.step(synth.bits16(grad), hp)
     torch.cuda.synchronize()
     fr.assert_equal_to(whole, "whole model after 6 steps")
@@ -1309,6 +1313,7 @@ def test_random_layouts_and_hyper_parameters_match_the_oracle():
     n_cases = int(os.environ.get("FP8LM_RANDOM_CASES", "60"))
     rng = np.random.default_rng(int(os.environ.get("FP8LM_RANDOM_SEED", "20231018")))
     rng2 = np.random.default_rng(int(os.environ.get("FP8LM_RANDOM_SEED", "20231018")) + 1)    # draws added later: the cases above stay what they were
+    rng3 = np.random.default_rng(int(os.environ.get("FP8LM_RANDOM_SEED", "20231018")) + 2)    # ... and later still
     dtypes = [torch.bfloat16, torch.float16, torch.float32]
     for case in range(n_cases):
         n_t = int(rng.integers(1, 7))
@@ -1350,12 +1355,13 @@ def test_random_layouts_and_hyper_parameters_match_the_oracle():
             # ... and so has the Adam step with the exact moment scale: through the pair of first-moment buffers
             pair_m = (bool(rng2.integers(0, 2)) and not delayed and (master_fmt, v_fmt) == (B.STATE_F16, B.STATE_F16)
                       and hp.stats == 0 and hp.m_scale_mode == B.MSCALE_EXACT_PASS)
+            own = bool(rng3.integers(0, 2))              # who measures the new first moment for the exact scale: the cast or the step
             snaps = [P.Snapshot(st, grad, t) for t in ids]
             say(f"random case {case} step {k}: numels={numels} dtype={dtype} sigma={sig:g} fmt={grad_fmt} wcopy={wcopy} "
                 f"master={master_fmt} v={v_fmt} lr={hp.lr:g} b1={hp.beta1:g} b2={hp.beta2:g} eps={hp.eps:g} wd={hp.weight_decay:g} "
-                f"t={hp.step} v_scaled={hp.v_scaled} stats={hp.stats} mode={hp.m_scale_mode} delayed={delayed} speculative={speculative} pair_m={pair_m} mu_rule={mu_rule} "
+                f"t={hp.step} v_scaled={hp.v_scaled} stats={hp.stats} mode={hp.m_scale_mode} delayed={delayed} speculative={speculative} pair_m={pair_m} own_moment_pass={own} mu_rule={mu_rule} "
                 f"exempt={flags.tolist()}")
-            st.step(grad, hp, delayed=delayed, speculative=speculative, pair_m=pair_m)
+            st.step(grad, hp, delayed=delayed, speculative=speculative, pair_m=pair_m, own_moment_pass=own)
             torch.cuda.synchronize()
             P.check_step(st, [x for x in snaps if not flags[x.t]], hp, what=f"random case {case} step {k}", delayed=delayed)
             if flags.any():

@@ -89,8 +89,8 @@ def test_speculative_path_matches_the_oracle_and_the_fused_adam_step():
         mode = B.MSCALE_FROM_CAST if step % 2 else B.MSCALE_EXACT_PASS
         snaps = [P.Snapshot(spec, grad, t) for t in ids]
         say(f"speculative path, whole step {step}, moment-scale mode {mode}")
-        plain.step(grad, B.adam_hparams(wl.lr, step))
-        spec.step(grad, B.adam_hparams(wl.lr, step, m_scale_mode=mode), speculative=True)
+        plain.step(grad, B.adam_hparams(wl.lr, step), own_moment_pass=True)
+        spec.step(grad, B.adam_hparams(wl.lr, step, m_scale_mode=mode), speculative=True, own_moment_pass=True)
         torch.cuda.synchronize()
         P.check_step(spec, snaps, B.adam_hparams(wl.lr, step, m_scale_mode=mode), what=f"speculative step {step}")
         for k in ("g8", "m", "v", "w", "wq", "g_meta", "m_meta", "v_meta", "w_meta", "q_meta"):
@@ -163,7 +163,7 @@ def test_adam_step_with_a_pair_of_moment_buffers_equals_the_two_pass_step(grad_f
         snaps = [P.Snapshot(plain, grad, t) for t in ids]
         before = pair.ctx.speculation_stats(moment=True)
         say(f"pair of moment buffers: fmt={grad_fmt} wcopy={wcopy} exact={exact} step={step} factor={f}")
-        plain.step(grad, hp)
+        plain.step(grad, hp, own_moment_pass=True)
         pair.step(grad, hp, pair_m=True, speculative=bool(step % 2))
         torch.cuda.synchronize()
         after = pair.ctx.speculation_stats(moment=True)
