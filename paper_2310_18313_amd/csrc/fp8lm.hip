@@ -278,11 +278,14 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
 Tables marked_tables_of(const fp8lm_ctx* c, const Tables& first, int* grid) {
   Tables tb = first;
   const long long units = (long long)c->n_chunks << tb.unit_shift;
+  // Mostly nothing is marked, and then a launch to finish with is 1.7 us for nothing, so tickets go up to more units than in
+  // the first round.  quantize_fp8 with nothing / everything marked, tickets against launch, us: 160 units 16.1 / 24.2
+  // against 17.7 / 23.1; 256 units 16.2 / 25.9 against 17.9 / 23.5; 400 units 16.5 / 28.6 against 18.1 / 24.3.
   if (c->single_pass_min_chunks == kLibraryChooses) tb.deferred = units > 256;
-  // with nothing marked the workgroups only cost their start; two thirds of 1.8e9 elements marked (heavy tails) took 1089 us
-  // with four workgroups per compute unit, 944 with eight, 935 with sixteen
-  const int per_cu = std::min(units > 65536 ? 8 : 4, c->blocks_per_cu);
-  *grid = (int)std::min<long long>((long long)per_cu * c->num_cus, units);
+  // Four workgroups per compute unit: with nothing marked they only cost their start, and more are no faster with much marked
+  // (two of eight tensors of 2^21 34.9 us with four, 38.8 with eight; of 2^27 699 and 707; all eight of 2^25 304 and 312;
+  // a step of a GPT-175B layer with two thirds marked 5455 and 5449).
+  *grid = (int)std::min<long long>((long long)std::min(4, c->blocks_per_cu) * c->num_cus, units);
   return tb;
 }
 
