@@ -149,12 +149,13 @@ __device__ __forceinline__ void refresh_scale(uint32_t fmax_bits, float bound, i
 // infinite: 16 and 12 instructions.  Where no intermediate comes near the ends of the exponent range the same
 // results take 5 and 6:
 //   sqrt(x):  y = rsq(x), s = x y, h = y / 2;  s + h (x - s^2), the residual exact in one fma.  Equal to the correctly
-//             rounded root for every one of the 2^24 significands and exponent parities (checked on the device).
+//             rounded root for every one of the 2^24 significands and exponent parities, with what v_rsq_f32 returns for
+//             them (an estimate one ulp further off would be wrong for a few: tests/short_arithmetic.hip tries all on the GPU).
 //   a / d:    r = rcp(d), r += r (1 - d r);  q = a r;  q - r (d q - a).  With r within one ulp of 1/d, which v_rcp_f32 is for
-//             every significand, the value before the last rounding is within 2^-22 ulp of a/d; the quotients that are
-//             this close to a rounding boundary were enumerated (for every d the a with 2 (a mod d) = d +- 32 at most:
-//             1.9e8 cases, r off by -1, 0 and 1 ulp): all round correctly but for d = 2 - 2^-23 and 2 - 3 2^-22 with an
-//             r that is off, where v_rcp_f32 returns the nearest.  The residual is formed as d q - a so that a = -0 gives -0.
+//             every significand (tried there too), the value before the last rounding is within 2^-22 ulp of a/d; the
+//             quotients this close to a rounding boundary are enumerated there (for every d the a with 2 (a mod d) = d +- 32 at
+//             most: 1.9e8 cases, r off by -1, 0 and 1 ulp): all round correctly but for d = 2 - 2^-23 and 2 - 3 2^-23 with
+//             an r that is off, where v_rcp_f32 returns the nearest.  The residual is formed as d q - a so that a = -0 gives -0.
 // And because scales are powers of two they can be folded into the coefficients without changing any rounding: b1 / s_m,
 // (1-b1) / s_g, (1-b2) / s_g^2, b2 / s_v, decay / s_w, and a common factor 2^j of x^(1/2), eps and a that centres the
 // root and the division in the exponent range.  What has to hold for all that is checked per tensor from the scales
@@ -373,21 +374,24 @@ template <bool FAST> __device__ __forceinline__ float adam_update(float m1, floa
   }
 }
 
+// The short root of x, from y = rsq(x), and the short quotient a / d, from r0 = rcp(d).
+__host__ __device__ __forceinline__ float short_root(float x, float y) {
+  const float s = x * y;
+  return __builtin_fmaf(__builtin_fmaf(-s, s, x), 0.5f * y, s);
+}
+__host__ __device__ __forceinline__ float short_quotient(float a, float d, float r0) {
+  const float r = __builtin_fmaf(__builtin_fmaf(-d, r0, 1.0f), r0, r0);
+  const float q = a * r;
+  return __builtin_fmaf(-__builtin_fmaf(d, q, -a), r, q);
+}
 // The same arithmetic with correctly rounded root and quotient for a tensor in the tame range (c as above).
 __device__ __forceinline__ void tame_update(float dg, float dm, float dv, float dw, const float (&c)[8], float lr, float& m1,
                                             float& v1, float& w1) {
   m1 = __builtin_fmaf(c[0], dm, c[1] * dg);
   v1 = __builtin_fmaf(c[3], dv, c[2] * (dg * dg));
   const float x = fmaxf(v1 * c[6], 0x1p-100f);           // zero: the root of 2^-100 vanishes against eps
-  const float y = __builtin_amdgcn_rsqf(x);
-  const float s0 = x * y;
-  const float s = __builtin_fmaf(__builtin_fmaf(-s0, s0, x), 0.5f * y, s0);
-  const float d = s + c[7], a = m1 * c[5];
-  const float r0 = __builtin_amdgcn_rcpf(d);
-  const float r = __builtin_fmaf(__builtin_fmaf(-d, r0, 1.0f), r0, r0);
-  const float q = a * r;
-  const float upd = __builtin_fmaf(-__builtin_fmaf(d, q, -a), r, q);
-  w1 = __builtin_fmaf(-lr, upd, dw * c[4]);
+  const float d = short_root(x, __builtin_amdgcn_rsqf(x)) + c[7];
+  w1 = __builtin_fmaf(-lr, short_quotient(m1 * c[5], d, __builtin_amdgcn_rcpf(d)), dw * c[4]);
 }
 
 template <int GFMT, int WCOPY, bool FAST, bool STATS>
