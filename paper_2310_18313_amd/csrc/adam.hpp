@@ -163,7 +163,7 @@ __device__ __forceinline__ void refresh_scale(uint32_t fmax_bits, float bound, i
 // of ranks that is not one is none), and every product and sum, in the plain order of operations and in this
 // one, is zero or normal, small ones by a margin of the 24 bits that an exact residual needs.
 // c: b1/s_m, (1-b1)/s_g, (1-b2)/s_g^2, b2/s_v, decay/s_w, 2^j/bc1, 4^j/bc2, 2^j eps.
-__device__ inline bool tame_range(const AdamParams& p, float isg, float ism, float isv, float isw, float decay, float (&c)[8]) {
+__host__ __device__ inline bool tame_range(const AdamParams& p, float isg, float ism, float isv, float isw, float decay, float (&c)[8]) {
   auto pow2 = [](float x) { const uint32_t b = f2u(x); return (b & 0x807FFFFFu) == 0 && b != 0 && b < 0x7F800000u; };
   auto ex = [](float x) { return (int)((f2u(x) >> 23) & 0xFFu) - 127; };       // floor(log2 |x|)
   if (!pow2(isg) || !pow2(ism) || !pow2(isv) || !pow2(isw)) return false;

@@ -18,8 +18,8 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef float float2_t __attribute__((ext_vector_type(2)));
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t f2u(float x) { return __builtin_bit_cast(uint32_t, x); }
-__device__ __forceinline__ float u2f(uint32_t x) { return __builtin_bit_cast(float, x); }
+__host__ __device__ __forceinline__ uint32_t f2u(float x) { return __builtin_bit_cast(uint32_t, x); }
+__host__ __device__ __forceinline__ float u2f(uint32_t x) { return __builtin_bit_cast(float, x); }
 
 template <int FMT> struct Fp8Traits;
 template <> struct Fp8Traits<kE4M3> {
@@ -227,7 +227,7 @@ __device__ __forceinline__ int pow2_exp(uint32_t fmax_bits, float A) {
   const uint32_t mf = fmax_bits & 0x7FFFFFu;
   return ma <= mf ? ef - ea : ef - ea - 1;
 }
-__device__ __forceinline__ float pow2f(int e) { return u2f((uint32_t)(e + 127) << 23); }  // e in [-126, 127]
+__host__ __device__ __forceinline__ float pow2f(int e) { return u2f((uint32_t)(e + 127) << 23); }  // e in [-126, 127]
 
 constexpr uint32_t kBitsE4M3Max = 0x43E00000u;  // 448
 constexpr uint32_t kBitsE5M2Max = 0x47600000u;  // 57344

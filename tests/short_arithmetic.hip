@@ -1,6 +1,6 @@
 // What the short root and division of the update pass rest on (adam.hpp: short_root, short_quotient), tried out:
 // quotients() on the host, over the quotients that lie closest to a rounding boundary; roots_and_reciprocals() on the GPU, over
-// every significand.
+// every significand; tame() says which tensors take them.
 #include <hip/hip_runtime.h>
 
 #include <atomic>
@@ -33,6 +33,14 @@ __global__ void estimates_kernel(uint32_t base, float* rcp, float* root, uint32_
 }  // namespace
 
 extern "C" {
+// hp: b1, 1 - b1, 1 / (1 - b1^t), b2, 1 - b2, 1 / (1 - b2^t), eps; inverse: of the scales of gradient, moments and weight.
+int tame(const float* hp, const float* inverse, float decay) {
+  fp8lm::AdamParams p{};
+  p.b1 = hp[0]; p.omb1 = hp[1]; p.rbc1 = hp[2]; p.b2 = hp[3]; p.omb2 = hp[4]; p.rbc2 = hp[5]; p.eps = hp[6];
+  float c[8];
+  return fp8lm::tame_range(p, inverse[0], inverse[1], inverse[2], inverse[3], decay, c);
+}
+
 // With significands A and D of 24 bits and k = 23 or 24 (so that the quotient of a = A / 2^23 and d = D / 2^23 has 24 bits), a / d is
 // A 2^k / D in units of its last place: close to a boundary between two roundings if 2 ((A 2^k) mod D) is close to D.  For every
 // `stride`-th D the A with a difference of at most 32 are solved for, and every quotient is taken with the reciprocal estimate

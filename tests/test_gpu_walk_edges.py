@@ -8,6 +8,7 @@ import torch
 
 import oracle as O
 import parity as P
+import tame_cases
 from conftest import say
 from paper_2310_18313_amd import binding as B
 from paper_2310_18313_amd import synth
@@ -43,23 +44,15 @@ def test_sizes_around_groups_tiles_units_and_chunks(sizes, dtype, own):
         P.check_step(st, snaps, hp, what=f"{sizes} step {step}")
 
 
-HPS = {
-    "plain": dict(lr=3e-4, step=100),
-    "first step": dict(lr=3e-4, step=1, beta2=0.999),
-    "no momentum": dict(lr=1e-2, step=7, beta1=0.0, beta2=0.0, weight_decay=0.0),
-    "small eps, late": dict(lr=0.0, step=100000, eps=2.0 ** -36, beta1=0.999, beta2=0.9999),
-    "large eps, full decay": dict(lr=1.0, step=3, eps=1024.0, weight_decay=1.0),
-}
-
-
-@pytest.mark.parametrize("hp", HPS)
+@pytest.mark.parametrize("hp", tame_cases.HPS)
 @pytest.mark.parametrize("gfmt,master,vfmt", [(B.E5M2, B.STATE_F16, B.STATE_F16), (B.E4M3, B.STATE_F32, B.STATE_F16),
                                               (B.E5M2, B.STATE_BF16, B.STATE_E4M3)])
 def test_update_around_the_ends_of_the_short_arithmetic(hp, gfmt, master, vfmt):
     """700 tensors of 4112 random codes, zeros of both signs among them, a tile and a group each, with scales drawn from ordinary
-    ones to well past every bound of the range in which the short root and division are taken."""
+    ones to well past every bound of the range in which the short root and division are taken (which tensors are inside, and
+    that every bound is met from both sides, is checked without a GPU)."""
     rng = np.random.default_rng(5)
-    nt, n = 700, 4112
+    nt, n = tame_cases.N_TENSORS, 4112
     lay = synth.Layout([f"t{i}" for i in range(nt)], [n] * nt)
     st, _ = P.make_state(synth.Workload("scales", lay, lr=1e-3), 0, gfmt, master_fmt=master, v_fmt=vfmt)
     total = lay.total
@@ -87,19 +80,14 @@ def test_update_around_the_ends_of_the_short_arithmetic(hp, gfmt, master, vfmt):
         t.view({1: torch.uint8, 2: torch.int16, 4: torch.int32}[t.element_size()])[:total].copy_(
             torch.from_numpy(host[k].view(ints[t.element_size()])))
     metas = {k: B.meta_to_numpy(getattr(st, k), nt) for k in ("g_meta", "m_meta", "v_meta", "w_meta", "q_meta")}
-    usual = rng.random(nt) < 0.3                      # tensors as a run has them; the others anywhere
-    exps = {"g_meta": np.where(usual, rng.integers(16, 32, nt), rng.integers(-30, 60, nt)),
-            "m_meta": np.where(usual, rng.integers(14, 26, nt), rng.integers(-34, 66, nt)),
-            "v_meta": np.where(usual, rng.integers(30, 45, nt), rng.integers(-64, 100, nt)),
-            "w_meta": np.where(usual, rng.integers(10, 18, nt), rng.integers(-62, 48, nt)) if master == B.STATE_F16 else np.zeros(nt, int)}
     payload = {"g_meta": 57344.0 if gfmt == B.E5M2 else 448.0, "m_meta": 448.0, "v_meta": 65504.0 if vfmt == B.STATE_F16 else 448.0,
                "w_meta": 65504.0 if master == B.STATE_F16 else 100.0}
-    for k, e in exps.items():
-        metas[k]["scale"], metas[k]["inv_scale"] = np.ldexp(1.0, e), np.ldexp(1.0, -e)
-        metas[k]["amax_deq"] = payload[k] * np.ldexp(1.0, -e)
+    for k, scale in tame_cases.scales(hp, master).items():
+        metas[k]["scale"], metas[k]["inv_scale"] = scale, np.float32(1.0) / scale
+        metas[k]["amax_deq"] = np.float32(payload[k]) * metas[k]["inv_scale"]
     for k, mt in metas.items():
         setattr(st, k, B.meta_from_numpy(mt, DEV))
-    h = B.adam_hparams(**HPS[hp], master_fmt=master, v_fmt=vfmt)
+    h = B.adam_hparams(**tame_cases.HPS[hp], master_fmt=master, v_fmt=vfmt)
     say(f"scales at the ends: {hp} gfmt={gfmt} master={master} v={vfmt}")
     st.adam(h)
     torch.cuda.synchronize()

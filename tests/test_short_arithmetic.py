@@ -1,10 +1,13 @@
 """The short root and division of the update pass against correctly rounded ones: every input that can go wrong."""
 import ctypes as C
 
+import numpy as np
 import pytest
 
 import short_arithmetic_build
+import tame_cases
 from conftest import say
+from paper_2310_18313_amd import binding as B
 
 
 @pytest.fixture(scope="module")
@@ -20,6 +23,33 @@ def test_quotients_next_to_a_rounding_boundary(lib):
     assert lib.quotients(0, 1, out, divisors) == 0
     assert list(out) == [186070940, 0, 3]
     assert set(divisors[:3]) == {0x3FFFFFFF, 0x3FFFFFFD}
+
+
+def test_cases_around_the_ends_of_the_range_reach_every_end(lib):
+    """The tensors that the GPU test of the update's ends steps: which of them take the short arithmetic, by the library's own
+    rule; of the others, every condition of the rule is the only one that some tensor misses, those apart that cannot be."""
+    alone, counts = set(), {}
+    for name, kw in tame_cases.HPS.items():
+        for master in (B.STATE_F16, B.STATE_F32):
+            const = tame_cases.host_constants(B.adam_hparams(**kw))
+            s = tame_cases.scales(name, master)
+            hp, short = (C.c_float * 7)(*const[:7]), 0
+            for t in range(tame_cases.N_TENSORS):
+                inv = [np.float32(1.0) / s[k][t] for k in ("g_meta", "m_meta", "v_meta", "w_meta")]
+                out = tame_cases.missed(const, inv)
+                assert bool(lib.tame(hp, (C.c_float * 4)(*inv), C.c_float(const[7]))) == (not out), (name, master, t, out)
+                short += not out
+                if len(out) == 1:
+                    alone |= out
+            counts[name, master] = short
+    assert alone == tame_cases.CONDITIONS
+    for (name, _), short in counts.items():
+        if name in ("small beta1", "small beta2"):
+            assert short == 0
+        elif name == "huge eps":
+            assert 0 < short < 50
+        else:
+            assert 200 < short < 500, (name, short)
 
 
 @pytest.mark.gpu
