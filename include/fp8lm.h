@@ -147,7 +147,8 @@ typedef struct {
 /*
  * Creates a context for a fixed tensor list on GPU `device`.
  *   tensors : host array of n entries, copied.  n >= 0.
- * Allocates the device-side tensor/chunk tables and the reduction scratch, and synchronises once.
+ * Allocates the device-side tensor/chunk tables and the reduction scratch, and synchronises once: about 144 bytes per
+ * 16384 elements (115 MB for 1.3e10), 330 per tensor and half a MiB.
  * Errors: INVALID_ARGUMENT (null, negative numel/offset), MISALIGNED, OVERLAP, TOO_LARGE, HIP.
  */
 fp8lm_status fp8lm_create(fp8lm_ctx** out, const fp8lm_tensor* tensors /*host*/, int32_t n, int device);

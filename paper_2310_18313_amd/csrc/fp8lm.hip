@@ -9,7 +9,8 @@
 //
 // Shape of every hot kernel
 //   * The tensor list is cut into chunks of `chunk_elems` elements that never straddle a tensor, a chunk into units
-//     of one tile (four in the read-only kernels).  A 256-thread workgroup takes one unit and ends, so that the chip
+//     of one, two or four tiles (the update one, the cast of 16-bit sources two, amax and re-quantisation four; see the
+//     end of walk.hpp).  A 256-thread workgroup takes one unit and ends, so that the chip
 //     sweeps through the buffers in order; a 5 K-element bias and a 250 M-element matrix are served by the same launch.
 //   * A thread handles 16 elements of a 4096-element tile, with 128-bit (64-bit on 8-bit
 //     streams of the update and cast kernels) accesses that are contiguous over the whole workgroup.
@@ -256,8 +257,9 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   }
   *grid = tb.one_unit ? (int)units() : grid_of(c);
   // In the deferred form a second launch finishes the tensors; see walk.hpp for the two forms' costs.  Unless told otherwise
-  // tickets are for launches of at most 64 units: a step of 2^18 parameters (64 units) takes 26.7 us with and 35.9 without
-  // them, one of 50 tensors with 66 000 elements in all 31.2 and 44.2; at 256 units 37.4 and 36.2, at 1024 141 and 36.
+  // tickets are for launches of at most 64 units, where they win whatever the list: a step of one tensor of 64 units takes
+  // 25.4 us with and 30.5 without them, one of 50 small tensors 25.1 and 30.5.  Above, it depends on the list (one tensor of 256
+  // units 27.1 and 30.6; 120 small tensors 30.9 and 30.5, 200 39.5 and 30.7), and at 512 units one tensor loses too (36.9 and 32.5).
   // A caller's threshold is compared with the chunks per workgroup of this launch.
   constexpr int kTicketUnits = 64;
   tb.deferred = c->single_pass_min_chunks == kLibraryChooses
@@ -1075,9 +1077,9 @@ fp8lm_status fp8lm_quant_error_stats(fp8lm_ctx* c, const void* ref, fp8lm_src re
     return after_launch();
   }
   StatsParams p{ref, q, q_meta, out, c->d_partials};
-  int grid = 0;
-  const Tables tb = tables_of(c, 1, 16, &grid);
-  grid = grid_of(c);
+  int unused = 0;
+  const Tables tb = tables_of(c, 1, 16, &unused);    // for its chunk table; the grid is persistent (see stats.hpp)
+  const int grid = grid_of(c);
   const dim3 ge(std::min<int>(c->n_tensors, 8 * c->num_cus));
   Timed tm(c, s, FP8LM_K_STATS);
 #define FP8LM_STATS_LAUNCH(F, S)                                                                             \

@@ -34,6 +34,7 @@ template <> struct SrcTraits<kSrcF32> {
   static constexpr uint32_t kNonfinite = 0x7F800000u;
   static __device__ __forceinline__ float dec(uint32_t bits) { return u2f(bits); }
 };
+template <int SRC> constexpr int kUnCast = SRC == kSrcF32 ? 1 : 2;      // tiles a workgroup of the cast takes at once (walk.hpp)
 template <int SRC> constexpr bool kSrc16 = sizeof(typename SrcTraits<SRC>::elem_t) == 2;
 template <int SRC> constexpr int kSrcWords = kSrc16<SRC> ? 8 : 16;     // 32-bit words of a 16-element group
 // folds one 32-bit word of the source (two 16-bit elements or one fp32) into a running maximum
@@ -774,12 +775,12 @@ struct SumOp {
   const SumParams& p;
   const Tables& tb;
   float vmax;
-  uint32_t amax_bits, n_elems, n_top, n_und;   // n_top / n_und: counted element by element (tails, NaN groups)
+  uint32_t amax_bits, n_top, n_und;            // n_top / n_und: counted element by element (tails, NaN groups)
   uint32_t n_fast, nz_top, nz_code, z_acc;     // whole groups: counted on the packed codes, as in the cast
   __device__ SumOp(const SumParams& p_, const Tables& tb_) : p(p_), tb(tb_) {}
   __device__ __forceinline__ void begin(int) {
     vmax = 0.0f;
-    amax_bits = n_elems = n_top = n_und = n_fast = nz_top = nz_code = z_acc = 0;
+    amax_bits = n_top = n_und = n_fast = nz_top = nz_code = z_acc = 0;
   }
   __device__ __forceinline__ bool fast() const { return true; }
   __device__ __forceinline__ uint32_t finish_one(float acc) {
@@ -867,7 +868,6 @@ struct SumOp {
       }
       finish_group(acc, pos + u * kTile);
     }
-    n_elems += UN * kGroup;
   }
   // 16 consecutive elements at `pos`, by this thread alone: the tile body with the thread's own offset taken out
   __device__ __forceinline__ void full_group(long long pos) {
@@ -882,7 +882,6 @@ struct SumOp {
       for (int r = 0; r < n; ++r) acc = acc + fp8_to_f32<FMT>(p.in.p[r][pos + j]);
       p.dst[pos + j] = (uint8_t)finish_one(acc);
     }
-    n_elems += valid;
   }
   using Stats = BlockStats<2, 2>;
   __device__ __forceinline__ void flush(long long u) {

@@ -170,8 +170,9 @@ constexpr int kTotalWords = 16;       // 4 words of maxima and mask, up to 8 cou
 //  * deferred: a second, tiny launch combines the records and runs the tensors' scalar epilogues: one workgroup per
 //    tensor, or one per 512 chunks of a large one, of which the last to arrive adds up what the others left.
 //  * single pass: every workgroup bumps a per-tensor ticket when it leaves the tensor, the one that completes it reads the
-//    records of the tensor.  A ticket costs about 50 ns that do not overlap with those of other workgroups, most of it
-//    the agent-scope release in front of it, which makes the record visible outside the workgroup's L2.
+//    records of the tensor.  A ticket costs 15 to 50 ns that do not overlap with those of other workgroups, most of it the
+//    agent-scope release in front of it, which makes the record visible outside the workgroup's L2 and writes back what
+//    else is in there (cast of a GPT-7B layer, 4096 persistent workgroups: 200 us more than the deferred form).
 //
 // Measured and not used: adding to per-tensor slots with fire-and-forget atomics instead of leaving records.  At device
 // scope they are served outside the L2s at about 15 ns each whichever line they go to: the update pass of 1.8e9
@@ -440,8 +441,7 @@ __device__ __forceinline__ void walk_units(const Tables& tb, Op& op) {
 // of a segment of neighbouring tensors, and only the segments of the workgroup's share are looked at one by one; the running
 // totals are kept by the first workgroup.  (One word per 128 bytes, 256 tensors at a time, and two device-scope atomics per
 // marked tensor for the totals: 459 us for 20 000 tensors of which a third is marked, 198 us this way.)  The tensors
-// are finished by tickets or by a launch of
-// their own, as after any other pass: tickets of 1024 workgroups are 60 us, so they are for the smallest launches.
+// are finished by tickets or by a launch of their own, as after any other pass.
 __device__ __forceinline__ void mark_redo(const Tables& tb, int t, const TensorDesc& d, bool redo) {
   tb.redo[t] = redo ? units_of(tb, d) : 0u;
   if (redo) __hip_atomic_store(tb.marked_call, tb.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);    // the next kernel reads it
@@ -544,11 +544,9 @@ __device__ __forceinline__ void walk_marked(const Tables& tb, Op& op) {
 // Tiles a workgroup takes at once (all their loads are issued before the first is used).  One tile keeps the window of
 // walk_units smallest, but then a workgroup's fixed costs (the chain table -> data, two barriers, the record) come once per 4096
 // elements: cast of GPT-125M with bf16 gradients, 1 / 2 / 4 tiles: 69 / 62 / 71 us (4: 207 registers, two wavefronts
-// per SIMD); re-quantisation 55 / 48 / 47 us; cast of fp32 gradients (201e6 elements) 228 / 240 us for 1 / 2.  The update pass
+// per SIMD; kUnCast); re-quantisation 55 / 48 / 47 us; cast of fp32 gradients (201e6 elements) 228 / 240 us for 1 / 2.  The update pass
 // does 40 to 70 instructions per element in the meantime and has no registers for a second tile.
 constexpr int kUnRead = 4;
-template <int SRC> constexpr int kUnCast = 2;
-template <> constexpr int kUnCast<2> = 1;        // fp32 sources
 constexpr int kUnRequant = 4;
 constexpr int kUnUpdate = 1;
 __host__ __device__ constexpr int sum_tiles(int ranks) { return ranks == 0 ? 1 : ranks <= 2 ? 4 : ranks <= 4 ? 2 : 1; }
