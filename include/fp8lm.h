@@ -507,8 +507,9 @@ fp8lm_status fp8lm_memory_skeleton(fp8lm_ctx* ctx, int32_t shape, void* const* b
 
 /*
  * Device memory whose pieces are chosen one by one: thin wrappers of the HIP virtual-memory calls, for callers that
- * lay their flat buffers out over the regions of HBM.  On MI355X a kernel that writes (the update pass, the cast)
- * runs up to 20 % slower while everything it writes lies in one 96 GiB region of the physical address space; a buffer
+ * lay their flat buffers out over the regions of HBM.  On MI355X traffic that writes runs slower while everything it
+ * writes lies in one 96 GiB region of the physical address space: up to 20 % where a persistent grid walks ranges
+ * (UPDATE_RANGES, a limit on workgroups), 0-3 % for the kernels as they sweep through their buffers by default; a buffer
  * whose address range alternates between pieces from two regions does not have that problem wherever a kernel is in
  * it.  Where a piece lies can only be measured (fp8lm_memory_skeleton, UPDATE_RANGES, across two pieces is faster than inside one
  * region), so the steps are separate: create pieces, map each somewhere, time it against a reference piece, then map
