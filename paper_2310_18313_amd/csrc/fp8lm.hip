@@ -265,10 +265,10 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   tb.deferred = c->single_pass_min_chunks == kLibraryChooses
                     ? units() > kTicketUnits
                     : c->single_pass_min_chunks > 0 && c->n_chunks / *grid < c->single_pass_min_chunks;
-  // tickets that a caller wants at any size: of a persistent grid, which has a ticket for each workgroup and tensor and not
-  // one for each unit (amax and cast of a GPT-7B layer: 0.57 ms instead of 3.05)
-  const long long persistent = (long long)c->num_cus * kMaxBlocksPerCu;
-  if (!tb.deferred && tb.one_unit && units() > persistent) {
+  // Tickets that a caller wants at any size: of a persistent grid of at most a workgroup per chunk, which has a ticket for each
+  // workgroup and tensor and not one for each unit.  amax and cast of two tensors, us, units / persistent: 256 units in all
+  // 16.3 / 16.5, 512 20.6 / 16.4, 1024 33.6 / 16.8, 8192 241 / 165; of a GPT-7B layer 3050 / 570.
+  if (!tb.deferred && tb.one_unit && units() > 256) {
     tb.unit_elems = c->chunk_elems;
     tb.unit_shift = tb.one_unit = 0;
     *grid = grid_of(c);

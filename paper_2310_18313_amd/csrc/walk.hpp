@@ -493,7 +493,7 @@ __device__ __forceinline__ void walk_marked(const Tables& tb, Op& op) {
   }
   // the segments that this workgroup's share reaches into, in order
   const long long lo = total * blockIdx.x / gridDim.x, hi = total * (blockIdx.x + 1) / gridDim.x;
-  const bool share = n && (long long)at < hi && (long long)at + n > lo;
+  const bool share = n && lo < hi && (long long)at < hi && (long long)at + n > lo;
   const unsigned long long ballot = __ballot(share);
   if (lane == 0) l_count[wave] = (uint32_t)__popcll(ballot);
   __syncthreads();
