@@ -165,8 +165,8 @@ fp8lm_status fp8lm_destroy(fp8lm_ctx* ctx);
  * this many chunks per workgroup of the launch, in the same launch (each workgroup bumps a per-tensor ticket, the
  * one that completes it finishes the tensor); with fewer, in a second tiny launch, because the tickets then
  * cost more than the data.  0 = always in the same launch (without a limit on workgroups, a launch of more than 256
- * units then has one for each chunk, at most 16 per compute unit, that walk ranges); 2^30, the default: the library chooses (tickets for the smallest launches
- * only); results are identical either way.
+ * units then has one for each chunk, at most 16 per compute unit, that walk ranges); 2^30, the default: the library
+ * chooses (tickets for the smallest launches only); results are identical either way.
  * Rebuilds the chunk table (synchronises the device; not to be called while a stream is being captured).
  * A HIP graph captured from this context before the call holds the old tables and must not be replayed
  * afterwards.  On an error the context keeps its previous tuning and tables.

@@ -227,10 +227,10 @@ int grid_of(const fp8lm_ctx* c) {
 // Tables of a launch whose workgroups take up to `un` tiles at once and leave records of `record` bytes, and its grid.
 // By default a workgroup per unit.  A unit is `un` tiles where that gives every compute unit four workgroups, otherwise
 // fewer (a small launch needs workgroups more than it needs loads in flight), and more where the record memory would not
-// do.  A persistent grid where the caller asked for a limit (fp8lm_set_tuning), or where there would be more workgroups than
-// a launch can have.
+// do.  A persistent grid where the caller asked for a limit (fp8lm_set_tuning), where there would be more workgroups than
+// a launch can have, and for `ranges`.
 constexpr long long kMaxGrid = 1ll << 23;          // x 256 threads stays below 2^32
-Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
+Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid, bool ranges = false) {
   Tables tb{};
   tb.desc = c->d_desc;
   tb.chunks = c->d_chunks;
@@ -247,7 +247,7 @@ Tables tables_of(const fp8lm_ctx* c, int un, int record, int* grid) {
   tb.n_chunks = c->n_chunks;
   tb.unit_elems = c->chunk_elems;
   auto units = [&] { return (long long)c->n_chunks << tb.unit_shift; };
-  if (c->blocks_per_cu >= kMaxBlocksPerCu) {
+  if (c->blocks_per_cu >= kMaxBlocksPerCu && !ranges) {
     while (tb.unit_elems % (2 * kTile) == 0 && (tb.unit_elems > un * kTile || units() < 4ll * c->num_cus) &&
            (size_t)(2 * units() * record) <= c->record_bytes) {
       tb.unit_elems /= 2;
@@ -332,11 +332,18 @@ void launch_walk_on(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p,
 }
 // ... on the usual tables, which it returns.
 template <class Op, class Params, class Kernel>
-Tables launch_walk(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, int un = 1) {
+Tables launch_walk(fp8lm_ctx* c, hipStream_t s, Kernel kernel, const Params& p, int un = 1, bool ranges = false) {
   int grid = 0;
-  const Tables tb = tables_of(c, un, RecordOf<typename Op::Stats>::bytes, &grid);
+  const Tables tb = tables_of(c, un, RecordOf<typename Op::Stats>::bytes, &grid, ranges);
   launch_walk_on<Op>(c, s, kernel, p, tb, grid);
   return tb;
+}
+// The amax pass reads one stream and writes nothing, so the order of the walk brings it little, and from 1 GiB on what a
+// workgroup does once per unit costs more: a persistent grid then.  us, a workgroup per unit / persistent: fp32 2^27 elements 84 /
+// 87, 2^30 645 / 622, 2^32 2565 / 2472; bf16 2^27 45 / 46, 2^30 326 / 321, 2^32 1281 / 1259.
+template <int MODE, int SRC> void launch_amax(fp8lm_ctx* c, hipStream_t s, const AmaxParams& p) {
+  const long long bytes = (long long)c->n_chunks * c->chunk_elems * (long long)sizeof(typename SrcTraits<SRC>::elem_t);
+  launch_walk<AmaxOp<MODE, SRC>>(c, s, amax_kernel<MODE, SRC>, p, kUnAmax<SRC>, bytes >= 1ll << 30);
 }
 
 // Selects the adam_update_kernel instantiation.
@@ -517,9 +524,9 @@ fp8lm_status fp8lm_amax_scale(fp8lm_ctx* c, const void* src, fp8lm_src src_type,
   AmaxParams p{src, meta, target == FP8LM_E4M3 ? kBitsE4M3Max : kBitsE5M2Max, cfg->hist_window, cfg->margin};
   hipStream_t s = (hipStream_t)stream;
   Timed tm(c, s, FP8LM_K_AMAX);
-  if (src_type == FP8LM_SRC_F32) launch_walk<AmaxOp<kAmaxForGradient, kSrcF32>>(c, s, amax_kernel<kAmaxForGradient, kSrcF32>, p, kUnRead);
-  else if (src_type == FP8LM_SRC_F16) launch_walk<AmaxOp<kAmaxForGradient, kSrcF16>>(c, s, amax_kernel<kAmaxForGradient, kSrcF16>, p, kUnRead);
-  else launch_walk<AmaxOp<kAmaxForGradient, kSrcBF16>>(c, s, amax_kernel<kAmaxForGradient, kSrcBF16>, p, kUnRead);
+  if (src_type == FP8LM_SRC_F32) launch_amax<kAmaxForGradient, kSrcF32>(c, s, p);
+  else if (src_type == FP8LM_SRC_F16) launch_amax<kAmaxForGradient, kSrcF16>(c, s, p);
+  else launch_amax<kAmaxForGradient, kSrcBF16>(c, s, p);
   return after_launch();
 }
 
@@ -758,7 +765,7 @@ fp8lm_status fp8lm_init_master_as(fp8lm_ctx* c, const void* w_bf16, void* w_out,
   Timed tm(c, s, FP8LM_K_INIT_MASTER);
   const uint32_t fmax_bits = master_fmt == FP8LM_STATE_F16 ? kBitsF16Max : (master_fmt == FP8LM_STATE_E4M3 ? kBitsE4M3Max : 0u);
   AmaxParams pa{static_cast<const uint16_t*>(w_bf16), w_meta, fmax_bits, 1, 0};
-  launch_walk<AmaxOp<kAmaxForMaster, kSrcBF16>>(c, s, amax_kernel<kAmaxForMaster, kSrcBF16>, pa, kUnRead);
+  launch_amax<kAmaxForMaster, kSrcBF16>(c, s, pa);
   fp8lm_status st = after_launch();
   if (st != FP8LM_OK) return st;
   InitParams pi{static_cast<const uint16_t*>(w_bf16), w_out, w_meta};

@@ -154,3 +154,14 @@ def test_both_rounds_of_a_speculation_cut_the_tensors_alike(lib, sizes):
             assert len(walks) == 2, what
             assert [(t["unit_elems"], t["unit_shift"]) for t in walks[1:]] == [(walks[0]["unit_elems"], walks[0]["unit_shift"])], (what, walks)
         lib.L.fp8lm_destroy(h)
+
+
+@pytest.mark.parametrize("src,size", [(B.SRC_F32, 4), (B.SRC_BF16, 2)])
+def test_amax_passes_of_a_gibibyte_walk_ranges(lib, src, size):
+    """(A workgroup per unit is the faster form below, a persistent grid from there on; both leave the same results.)"""
+    for numel, ranges in (((1 << 30) // size - 16384, False), ((1 << 30) // size, True)):
+        h = lib.context([numel])
+        (name, grid, tables), _ = lib.notes(lib.calls(h)[f"amax {src}"])
+        assert name == "amax" and bool(tables["one_unit"]) is not ranges
+        assert grid == (16 * CUS if ranges else tables["n_chunks"] << tables["unit_shift"])
+        lib.L.fp8lm_destroy(h)
